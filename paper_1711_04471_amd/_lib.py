@@ -69,6 +69,8 @@ SIGNATURES = {
     "sw2d_step_unfused": (ctypes.c_int, [_vp, ctypes.c_int32, _vp, ctypes.c_size_t]),
     "sw2d_set_time_blocking": (ctypes.c_int, [_vp, ctypes.c_int32, ctypes.c_int32]),
     "sw2d_time_blocking": (ctypes.c_int32, [_vp]),
+    "sw2d_set_streaming": (ctypes.c_int, [_vp, ctypes.c_int32]),
+    "sw2d_streaming": (ctypes.c_int32, [_vp]),
     "sw2d_destroy": (ctypes.c_int, [_vp]),
     "sw2d_strerror": (ctypes.c_char_p, [ctypes.c_int]),
     "sw2d_batch_workspace_bytes": (ctypes.c_size_t, [ctypes.c_int32, ctypes.POINTER(sw2d_params),

@@ -26,9 +26,11 @@ struct sw2d_ctx {
     sw2d_red* ring;
     FoldPartial* part;
     int part_capacity;  // partial slots per step
+    size_t part_slots;  // partial slots in all
     StepGeometry geo;   // one step per pass
     StepGeometry geok[kMaxStepsPerPass + 1];  // K steps per pass (K >= 2)
     int steps_per_pass; // 1 .. kMaxStepsPerPass
+    bool streaming;     // row-marching passes also where register tiles would serve
     StepCoef coef;
     int64_t step;             // steps done
     int64_t ring_first;       // first step whose fold is valid in the ring
@@ -75,6 +77,7 @@ bool params_ok(const sw2d_params* p) {
 struct Layout {
     size_t hp, flags, ring, part, total;
     int part_capacity;
+    size_t part_slots;
 };
 
 Layout layout(const sw2d_params* p) {
@@ -95,8 +98,11 @@ Layout layout(const sw2d_params* p) {
     L.ring = off;
     off = align_up(off + (size_t)kRingCap * sizeof(sw2d_red));
     L.part = off;
+    // slots for kFoldChunk steps of the most workgroups; small grids get 64 KiB, so that a call of
+    // many steps folds them in few launches (and the one-off sum of H has its partials)
     size_t part_bytes = (size_t)kFoldChunk * L.part_capacity * sizeof(FoldPartial);
-    if (part_bytes < kHsumBlocks * sizeof(double)) part_bytes = kHsumBlocks * sizeof(double);
+    if (part_bytes < kMinPartBytes) part_bytes = kMinPartBytes;
+    L.part_slots = part_bytes / sizeof(FoldPartial);
     off = align_up(off + part_bytes);
     L.total = off;
     return L;
@@ -122,43 +128,65 @@ StepCoef make_coef(const sw2d_params* p) {
     return k;
 }
 
-int flush_folds(sw2d_ctx* h, int pending, int nparts) {
+int flush_folds(sw2d_ctx* h, int pending, int nparts, int stride) {
     if (pending <= 0) return SW2D_OK;
-    SW2D_HIP(launch_fold(h->part, nparts, h->part_capacity, pending, h->step - pending + 1, h->ring,
-                         kRingCap, h->p.dx * h->p.dy, h->h_sum, h->stream));
+    SW2D_HIP(launch_fold(h->part, nparts, stride, pending, h->step - pending + 1, h->ring, kRingCap,
+                         h->p.dx * h->p.dy, h->h_sum, h->stream));
     return SW2D_OK;
 }
 
-// Enqueue nsteps steps: passes of steps_per_pass steps, a single step for an odd remainder;
-// the fold partials of up to kFoldChunk steps are buffered, then added by one fold launch.
-// With events (2 per pass, at most kFoldChunk passes per chunk) the step kernels are timed.
+// Whether the handle's steps go over register tiles.
+bool uses_tiles(const sw2d_ctx* h) {
+    return !h->streaming && h->p.flags == 0 && (int64_t)h->p.nx * h->p.ny <= kBlockMaxCells;
+}
+
+int add_pass_times(hipEvent_t* ev, int passes, double* total_ms) {
+    SW2D_HIP(hipEventSynchronize(ev[2 * passes - 1]));
+    for (int i = 0; i < passes; ++i) {
+        float ms = 0.f;
+        SW2D_HIP(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]));
+        *total_ms += ms;
+    }
+    return SW2D_OK;
+}
+
+// Enqueue nsteps steps: register tiles take up to kBlockMaxK steps per pass, the row-marching
+// passes steps_per_pass (a remainder takes one shorter pass). The fold partials of successive
+// passes of one grid size are buffered while slots last, then added by one fold launch. With
+// events (2 per pass, at most kFoldChunk passes between folds) the step kernels are timed.
 int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms) {
+    const bool tiles = uses_tiles(h);
+    const int kmax = tiles ? kBlockMaxK : h->steps_per_pass;
+    BlockGeometry bg{};
+    int bg_k = 0;
     int pending = 0, nparts = 0, passes = 0;
     int32_t done = 0;
     while (done < nsteps) {
-        const int k = (nsteps - done < h->steps_per_pass) ? nsteps - done : h->steps_per_pass;
+        const int k = (nsteps - done < kmax) ? nsteps - done : kmax;
+        if (tiles && k != bg_k) {
+            bg = block_geometry(h->p.nx, h->p.ny, k);
+            bg_k = k;
+        }
         const StepGeometry& g = (k >= 2) ? h->geok[k] : h->geo;
-        if (pending + k > kFoldChunk || (pending > 0 && g.nblocks != nparts)) {
-            int rc = flush_folds(h, pending, nparts);
+        const int nblocks = tiles ? bg.nblocks : g.nblocks;
+        if (pending > 0 && (nblocks != nparts || (size_t)(pending + k) * nblocks > h->part_slots ||
+                            pending + k > kRingCap || (ev && passes == kFoldChunk))) {
+            int rc = flush_folds(h, pending, nparts, nparts);
+            if (rc == SW2D_OK && ev) rc = add_pass_times(ev, passes, total_ms);
             if (rc) return rc;
-            if (ev) {
-                SW2D_HIP(hipEventSynchronize(ev[2 * passes - 1]));
-                for (int i = 0; i < passes; ++i) {
-                    float ms = 0.f;
-                    SW2D_HIP(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]));
-                    *total_ms += ms;
-                }
-            }
             pending = 0;
             passes = 0;
         }
         float* const* src = h->state[h->cur];
         float* const* dst = h->state[h->cur ^ 1];
-        FoldPartial* part = h->part + (size_t)pending * h->part_capacity;
+        FoldPartial* part = h->part + (size_t)pending * nblocks;
         if (ev) SW2D_HIP(hipEventRecord(ev[2 * passes], h->stream));
-        if (k >= 2)
+        if (tiles)
+            SW2D_HIP(launch_block(k, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, bg, h->coef,
+                                  h->stream));
+        else if (k >= 2)
             SW2D_HIP(launch_stepk(k, (int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part,
-                                  h->part_capacity, g, h->coef, h->stream));
+                                  nblocks, g, h->coef, h->stream));
         else
             SW2D_HIP(launch_step((int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, g, h->coef,
                                  h->stream));
@@ -166,21 +194,13 @@ int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms)
         h->cur ^= 1;
         h->step += k;
         pending += k;
-        nparts = g.nblocks;
+        nparts = nblocks;
         ++passes;
         done += k;
     }
-    int rc = flush_folds(h, pending, nparts);
-    if (rc) return rc;
-    if (ev && passes > 0) {
-        SW2D_HIP(hipEventSynchronize(ev[2 * passes - 1]));
-        for (int i = 0; i < passes; ++i) {
-            float ms = 0.f;
-            SW2D_HIP(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]));
-            *total_ms += ms;
-        }
-    }
-    return SW2D_OK;
+    int rc = flush_folds(h, pending, nparts, nparts);
+    if (rc == SW2D_OK && ev && passes > 0) rc = add_pass_times(ev, passes, total_ms);
+    return rc;
 }
 
 }  // namespace
@@ -232,10 +252,12 @@ int sw2d_create(const sw2d_params* p, const float* d_H, const uint8_t* d_mask, f
     h->ring = reinterpret_cast<sw2d_red*>(w + L.ring);
     h->part = reinterpret_cast<FoldPartial*>(w + L.part);
     h->part_capacity = L.part_capacity;
+    h->part_slots = L.part_slots;
     h->geo = make_geometry(p->nx, p->ny, default_rows(p->ny), single_strip_out(p->flags));
     for (int K = 2; K <= kMaxStepsPerPass; ++K)
         h->geok[K] = make_geometry(p->nx, p->ny, default_rows(p->ny), kstep_strip_out(K, p->flags));
     h->steps_per_pass = 1;
+    h->streaming = false;
     h->coef = make_coef(p);
     h->step = 0;
     h->ring_first = 1;
@@ -318,12 +340,12 @@ int sw2d_step_unfused(sw2d_t h, int32_t nsteps, float* d_scratch, size_t scratch
         h->cur ^= 1;
         h->step += 1;
         if (++pending == kFoldChunk) {
-            int rc = flush_folds(h, pending, nparts);
+            int rc = flush_folds(h, pending, nparts, h->part_capacity);
             if (rc) return rc;
             pending = 0;
         }
     }
-    return flush_folds(h, pending, nparts);
+    return flush_folds(h, pending, nparts, h->part_capacity);
 }
 
 int sw2d_set_band_rows(sw2d_t h, int32_t rows) {
@@ -347,6 +369,14 @@ int sw2d_set_time_blocking(sw2d_t h, int32_t steps_per_pass, int32_t rows) {
     h->steps_per_pass = steps_per_pass;
     return SW2D_OK;
 }
+
+int sw2d_set_streaming(sw2d_t h, int32_t on) {
+    if (!h) return SW2D_ESTATE;
+    h->streaming = on != 0;
+    return SW2D_OK;
+}
+
+int32_t sw2d_streaming(sw2d_t h) { return h ? (uses_tiles(h) ? 0 : 1) : -1; }
 
 int32_t sw2d_time_blocking(sw2d_t h) { return h ? h->steps_per_pass : -1; }
 

@@ -21,7 +21,8 @@ constexpr int kGroupCols = kStripOut * kWavesPerGroup;  // 240 output columns pe
 constexpr int kFoldThreads = 256;
 constexpr int kXcds = 8;                             // MI355X: 8 XCDs, one L2 each
 constexpr int kMinRows = 8;                          // smallest band height a handle may use
-constexpr int kFoldChunk = 16;                       // steps whose partials are buffered
+constexpr int kFoldChunk = 16;                       // steps whose partials are buffered at least
+constexpr size_t kMinPartBytes = 64 << 10;           // fold partials of the smallest grids
 constexpr int kRingCap = 4096;                       // steps of folds kept for sw2d_reduce
 
 // Per-workgroup fold partial of one step (16 B).
@@ -95,6 +96,57 @@ inline StepGeometry make_geometry(int nx, int ny, int rows, int strip_out = kStr
     g.nblocks = g.groups_x * g.bands;
     return g;
 }
+
+// Register tiles (sw2d_block.h): kBlockWaves waves of R rows x 128 columns, K steps per pass.
+// 8 waves: at 16 the barriers of a tile cost more than they share (us per step of the 2048^2
+// basin, K = 4, tiles of 40-48 rows: 10.3 with 8 waves, 16.4 with 16, 11.4 with 4; of the 66^2
+// basin 2.2, 3.3 and 2.3).
+constexpr int kBlockWaves = 8;
+constexpr int kBlockRowsLow = 3, kBlockRowsHigh = 5;  // rows per wave: tiles of 24 and 40 rows
+constexpr int kBlockMaxK = 4;
+// Largest grid stepped by register tiles: 2^23 cells, whose state and depth (28 B per cell and
+// step, 235 MB) the 256 MB Infinity Cache holds. Tiles re-read and recompute their overlap
+// (1.5-2 x at K = 4), which costs little there; from HBM the row pipelines, which overlap less,
+// are faster (us per step, tiles against the better of 1 and 4 steps per pass streamed:
+// 4096 x 2048 17.5 and 19; 8192 x 4096 60 and 54).
+constexpr int64_t kBlockMaxCells = (int64_t)1 << 23;
+
+struct BlockGeometry {
+    int nx, ny;
+    int rows;  // R, rows per wave
+    int strips, bands, nblocks;
+};
+
+inline BlockGeometry make_block_geometry(int nx, int ny, int K, int R) {
+    // neighbouring tiles overlap by 4K columns or rows
+    const int cols = 2 * kWave, rows = kBlockWaves * R, over = 4 * K;
+    BlockGeometry g;
+    g.nx = nx;
+    g.ny = ny;
+    g.rows = R;
+    g.strips = nx <= cols ? 1 : 1 + (nx - cols + (cols - over) - 1) / (cols - over);
+    g.bands = ny <= rows ? 1 : 1 + (ny - rows + (rows - over) - 1) / (rows - over);
+    g.nblocks = g.strips * g.bands;
+    return g;
+}
+
+// The tile height for K steps. A step of a tile takes about 0.9 us at 3 rows per wave and 1.4 at
+// 5 (66^2), but tiles of 24 rows own only 24 - 4K of them: they win while all of them run at
+// once, with little to spare beyond one per CU (us per step at K = 4, 3 and 5 rows per wave:
+// 300 x 221 with 78 and 27 tiles 2.2 and 2.7; 693 x 700 with 602 and 203 tiles 4.1 and 3.0; at
+// K = 3 there, 348 and 150 tiles, 3.6 and 3.4). One step per pass has little overlap and is
+// bound by its loads: 3 rows win at every size (2048^2: 18.7 and 19.4).
+inline BlockGeometry block_geometry(int nx, int ny, int K) {
+    const BlockGeometry low = make_block_geometry(nx, ny, K, kBlockRowsLow);
+    if (K == 1 || low.nblocks <= 320) return low;
+    return make_block_geometry(nx, ny, K, kBlockRowsHigh);
+}
+
+// K = 1..4 steps of the plain model in one pass over register tiles (geometry from
+// block_geometry); the partials of step s of the pass go to part[s * geo.nblocks + 0..nblocks).
+hipError_t launch_block(int K, const float* eta, const float* u, const float* v, const float* hp, float* eta_o,
+                        float* u_o, float* v_o, FoldPartial* part, const BlockGeometry& geo, const StepCoef& k,
+                        hipStream_t s);
 
 // kvar: the model variants (0 for the plain step).
 hipError_t launch_step(int kvar, const float* eta, const float* u, const float* v, const float* hp,

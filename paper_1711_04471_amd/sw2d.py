@@ -119,6 +119,15 @@ class Sw2d:
     def time_blocking(self) -> int:
         return int(_lib.load().sw2d_time_blocking(self._handle()))
 
+    @property
+    def streaming(self) -> bool:
+        """Whether the steps are streamed through the row pipelines (else: register tiles)."""
+        return int(_lib.load().sw2d_streaming(self._handle())) == 1
+
+    @streaming.setter
+    def streaming(self, on: bool) -> None:
+        check(_lib.load().sw2d_set_streaming(self._handle(), int(bool(on))), "sw2d_set_streaming")
+
     def reduce(self, k: int = 1, allow_unstable: bool = False) -> np.ndarray:
         out = (sw2d_red * int(k))()
         rc = _lib.load().sw2d_reduce(self._handle(), out, int(k))
