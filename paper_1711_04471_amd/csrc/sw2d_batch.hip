@@ -1,17 +1,18 @@
 // sw2d_batch.hip - ensembles of independent 2DSW basins of uneven sizes, advanced by one
-// persistent launch per chunk of steps, with a grid barrier between steps.
+// persistent launch per chunk of steps, with a grid barrier between passes.
 //
-// Work list: every (instance, band, group of 4 strips) is one tile for one workgroup, as
-// in the single-grid kernel (same tile routine, so each instance is bitwise equal to the
-// same basin stepped alone). Tiles are listed instance by instance in blocks of two
-// vertically adjacent bands and handed out costliest first: each workgroup takes the next
-// tile from a work ticket (one atomic per tile) until the pass's tiles run out, so a
-// workgroup that finishes early takes more and the grid reaches the barrier together.
+// A pass advances every member K <= 4 steps over register tiles (sw2d_block.h: the tile routine
+// of the single-grid step, so each instance is bitwise equal to the same basin stepped alone).
+// The tiles of all members, member by member and band by band, form one list; workgroup g of G
+// takes the g-th of G equal runs of it, so its tiles are neighbours (their overlap hits the
+// cache of its XCD) and no list, ticket or descriptor is read: a workgroup looks its first
+// member up once per launch and walks on from there. All tiles cost the same, whatever part of
+// the grid they cover. The grid holds no more workgroups than there are tiles (and folds), so a
+// small ensemble meets at a barrier of few.
 //
-// Per pass: workgroups process tiles and write one fold partial per tile and step, then the
-// grid meets at a barrier, where workgroup 0 also rewinds the ticket of the next pass. After the barrier, workgroup b adds the partials of instances
-// b, b+G, ... in a fixed order and writes their folds to the ring, then goes on with the
-// next step.
+// Per pass: workgroups process tiles and write one fold partial per tile and step, add the
+// partials of the previous pass (one wave per member and step, in a fixed order) and write
+// their folds to the ring, then meet at the barrier.
 //
 // The barrier uses no contended atomics: every workgroup publishes the epoch it has
 // reached in its own flag (after an agent-scope release), workgroup 0 waits for all
@@ -32,34 +33,25 @@
 #include <utility>
 #include <vector>
 
+#include "sw2d_block.h"
 #include "sw2d_internal.h"
-#include "sw2d_tile.h"
 
 namespace sw2d {
+
+// Tiles of a member at K steps per pass: bands of strips, tile_begin the first in the list.
+struct BatchTiles {
+    int strips, bands, tile_begin;
+};
 
 struct BatchInst {
     const float* hp;
     float* state[2][3];
-    int nx, ny, strips;
+    int nx, ny;
     StepCoef k;
     double cell_area;
     double h_sum;
-    int tile_begin, tile_end;  // tiles of this instance in the work list
+    BatchTiles t[kBlockMaxK];  // [K - 1]
 };
-
-// A self-contained tile descriptor (128 B): everything one workgroup needs for one tile,
-// so a tile starts without dependent loads. Copied to LDS once per launch.
-struct alignas(16) BatchTile {
-    const float* hp;
-    float* state[2][3];
-    int nx, ny, strips, j0, j1;
-    int group2;  // 2 * group + 1 if the band marches south
-    int inst;
-    int pad0;
-    StepCoef k;
-    int pad1[3];
-};
-static_assert(sizeof(BatchTile) == 128, "tile descriptor size");
 
 constexpr int kFlagStride = 16;  // 64-bit words between flags: one 128 B line each
 
@@ -68,26 +60,18 @@ struct BatchControl {
     unsigned pad0;
     long long steps_done;   // advanced by the kernel at the end of every launch
     long long passes_done;  // passes over the state so far: its parity picks the current buffer
-    unsigned next_tile[2];  // work tickets of the passes of each parity (position in the order)
-    long long pad1[kFlagStride - 4];
+    long long pad1[kFlagStride - 3];
     unsigned long long go;  // last epoch every workgroup has reached (own line)
     unsigned long long pad2[kFlagStride - 1];
     // followed by one flag line per workgroup
 };
 
-constexpr int kBatchThreads = kGroupThreads;
-constexpr int kMaxBatchK = 3;  // steps per pass of the batched kernel: 1..3
-// Owned columns of a strip for K steps per pass: one column per lane. (Two columns per lane,
-// as the single-grid K-step kernel, measured slower on the ensemble: the members are small,
-// odd widths need 4-byte accesses, and the persistent grid drops from 4 to 3 resident
-// workgroups per CU.)
-constexpr int batch_strip_out(int K) { return K == 1 ? kStripOut : kWave - 4 * K; }
+constexpr int kBatchThreads = kWave * kBlockWaves;
+constexpr int kMaxBatchK = 3;  // steps per pass a caller may ask for: 1..3
 constexpr int kBatchRing = 64;  // steps of per-instance folds kept
 
 struct BatchArgs {
     const BatchInst* inst;
-    const BatchTile* tiles;
-    const int* order;      // tile ids, costliest first: the order in which tiles are handed out
     FoldPartial* part;  // [2][K][n_tiles]
     sw2d_red* ring;     // [kBatchRing][n_inst]
     BatchControl* ctl;
@@ -108,10 +92,8 @@ __device__ __forceinline__ bool spin_until(const unsigned long long* word, unsig
     return true;
 }
 
-// Returns false (for the whole workgroup) if a wait ran past the deadline. Workgroup 0 also
-// rewinds the work ticket of the next pass (`rewind`): its last use, two passes back, is over
-// once every workgroup has arrived.
-__device__ bool grid_barrier(const BatchArgs& a, unsigned long long epoch, unsigned* rewind) {
+// Returns false (for the whole workgroup) if a wait ran past the deadline.
+__device__ bool grid_barrier(const BatchArgs& a, unsigned long long epoch) {
     __shared__ int s_ok;
     const unsigned long long deadline = wall_clock64() + a.timeout_ticks;
     if (threadIdx.x == 0) s_ok = 1;
@@ -127,7 +109,6 @@ __device__ bool grid_barrier(const BatchArgs& a, unsigned long long epoch, unsig
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         __syncthreads();
         if (threadIdx.x == 0 && s_ok) {
-            __hip_atomic_store(rewind, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             __hip_atomic_store(&a.ctl->go, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -140,67 +121,40 @@ __device__ bool grid_barrier(const BatchArgs& a, unsigned long long epoch, unsig
     return s_ok != 0;
 }
 
-// Adds the tile partials of instance i (fixed order) and writes its fold entry for `step`.
-__device__ void fold_instance(const BatchArgs& a, int i, int slot, long long step) {
-    __shared__ double s_disp[kBatchThreads];
-    __shared__ float s_mu[kBatchThreads], s_mv[kBatchThreads];
-    const BatchInst& in = a.inst[i];
-    const FoldPartial* p = a.part + (size_t)slot * a.n_tiles;
-    double disp = 0.0;
-    float mu = 0.f, mv = 0.f;
-    for (int it = in.tile_begin + threadIdx.x; it < in.tile_end; it += kBatchThreads) {
-        disp += p[it].disp;
-        mu = fmaxf(mu, p[it].mu);
-        mv = fmaxf(mv, p[it].mv);
-    }
-    const int t = threadIdx.x;
-    s_disp[t] = disp;
-    s_mu[t] = mu;
-    s_mv[t] = mv;
-    __syncthreads();
-    for (int half = kBatchThreads / 2; half > 0; half >>= 1) {
-        if (t < half) {
-            s_disp[t] += s_disp[t + half];
-            s_mu[t] = fmaxf(s_mu[t], s_mu[t + half]);
-            s_mv[t] = fmaxf(s_mv[t], s_mv[t + half]);
+// Folds of one pass: wave q of the grid adds the tile partials of (member, step) pairs q, q + the
+// grid's waves, ... (a lane every 64th partial, then the lanes) and writes their ring entries. The
+// order does not depend on the grid.
+template <int K>
+__device__ __forceinline__ void fold_pass(const BatchArgs& a, int first_wave, int nwaves, int lane,
+                                          const FoldPartial* __restrict__ part, long long first_step) {
+    for (int q = first_wave; q < a.n_inst * K; q += nwaves) {
+        const int i = q / K, s = q - i * K;
+        const BatchInst& in = a.inst[i];
+        const int t0 = in.t[K - 1].tile_begin, t1 = t0 + in.t[K - 1].strips * in.t[K - 1].bands;
+        const FoldPartial* p = part + (size_t)s * a.n_tiles;
+        BlockFolds F[1];
+        for (int it = t0 + lane; it < t1; it += kWave) {
+            F[0].disp += p[it].disp;
+            F[0].max_u = fmaxf(F[0].max_u, p[it].mu);
+            F[0].max_v = fmaxf(F[0].max_v, p[it].mv);
         }
-        __syncthreads();
+        const BlockFolds f = wave_folds<1>(F);  // complete in lanes 0..15
+        if (lane == 0) {
+            const long long step = first_step + s;
+            sw2d_red* o = a.ring + (size_t)((step - 1) % kBatchRing) * a.n_inst + i;
+            o->step = step;
+            o->vol_total = in.cell_area * (in.h_sum + f.disp);
+            o->vol_disp = in.cell_area * f.disp;
+            o->max_abs_u = f.max_u;
+            o->max_abs_v = f.max_v;
+        }
     }
-    if (t == 0) {
-        sw2d_red* o = a.ring + (size_t)((step - 1) % kBatchRing) * a.n_inst + i;
-        o->step = step;
-        o->vol_total = in.cell_area * (in.h_sum + s_disp[0]);
-        o->vol_disp = in.cell_area * s_disp[0];
-        o->max_abs_u = s_mu[0];
-        o->max_abs_v = s_mv[0];
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ void fold_step(const BatchArgs& a, int logical_wg, int nwg, int slot,
-                                          long long step) {
-    for (int i = logical_wg; i < a.n_inst; i += nwg) fold_instance(a, i, slot, step);
-}
-
-// the K steps of one pass: partial slots slot0 .. slot0 + K - 1, steps first .. first + K - 1
-__device__ __forceinline__ void fold_pass(const BatchArgs& a, int logical_wg, int nwg, int slot0,
-                                          long long first, int K) {
-    for (int s = 0; s < K; ++s) fold_step(a, logical_wg, nwg, slot0 + s, first + s);
 }
 
 __device__ __forceinline__ int logical_block(int b, int n) {
     const int q = n / kXcds, r = n % kXcds;
     const int x = b % kXcds, k = b / kXcds;
     return x * q + min(x, r) + k;
-}
-
-__device__ __forceinline__ void batch_wave_sums(double& disp, float& mu, float& mv) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        disp += __shfl_xor(disp, off, kWave);
-        mu = fmaxf(mu, __shfl_xor(mu, off, kWave));
-        mv = fmaxf(mv, __shfl_xor(mv, off, kWave));
-    }
 }
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -217,122 +171,72 @@ __device__ __forceinline__ float uniform_f(float x) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
-// K steps per pass over each member (temporal blocking as in the single-grid K-step
-// kernel: bands read a 2K-row halo, strips lose 2K columns on each side); the grid meets once
-// per pass.
-template <int K>
+// K steps per pass over tiles of R rows per wave; a.steps is a multiple of K.
+template <int K, int R>
 __global__ __launch_bounds__(kBatchThreads) void sw2d_batch_kernel(BatchArgs a) {
-    __shared__ BatchTile s_tile;
-    __shared__ int s_pos, s_id;
-    __shared__ double s_disp[kWavesPerGroup];
-    __shared__ float s_mu[kWavesPerGroup], s_mv[kWavesPerGroup];
-    constexpr int kOut = batch_strip_out(K);
-    constexpr int kEdge = (K == 1) ? kHalo : 2 * K;  // unowned columns on each side of a strip
+    constexpr int W = kBlockWaves, T = W * R;
+    __shared__ BlockShared<W> sh;
+    __shared__ BlockFoldShared<W> fsh;
     const int nwg = gridDim.x;
     const int lwg = logical_block(blockIdx.x, nwg);
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int wave = uniform(threadIdx.x / kWave), lane = threadIdx.x % kWave;
     const long long base = a.ctl->steps_done;
     const long long pbase = a.ctl->passes_done;
     const int passes = a.steps / K;
+    // this workgroup's run of tiles (none beyond the first n_tiles workgroups)
+    const int workers = min(nwg, a.n_tiles);
+    const int t0 = lwg < workers ? (int)((long long)lwg * a.n_tiles / workers) : 0;
+    const int t1 = lwg < workers ? (int)((long long)(lwg + 1) * a.n_tiles / workers) : 0;
+    int m0 = 0;  // the member of tile t0
+    for (int lo = 0, hi = a.n_inst; hi - lo > 1;) {
+        const int mid = (lo + hi) / 2;
+        if (uniform(a.inst[mid].t[K - 1].tile_begin) <= t0) lo = m0 = mid;
+        else hi = mid;
+    }
+    // the folds start from the last workgroups, which a small ensemble leaves without tiles
+    const int fold_wave = (nwg - 1 - lwg) * W + wave, fold_waves = nwg * W;
 
     for (int ps = 0; ps < passes; ++ps) {
         const long long step0 = base + (long long)ps * K;  // steps made before this pass
-        const long long gpass = pbase + ps;                // passes made before this one
-        const int cur = (int)(gpass & 1);
-        if (ps > 0) fold_pass(a, lwg, nwg, ((ps - 1) & 1) * K, step0 - K + 1, K);
+        const int cur = (int)((pbase + ps) & 1);
         FoldPartial* part = a.part + (size_t)(ps & 1) * K * a.n_tiles;
-        unsigned* ticket = &a.ctl->next_tile[gpass & 1];
-        // Tiles are handed out costliest first, one per request, so a workgroup that finishes
-        // early takes more of them and every workgroup reaches the barrier at about the same
-        // time. Which workgroup steps a tile changes no bit of any result.
-        for (;;) {
-            if (threadIdx.x == 0)
-                s_pos = (int)__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            const int pos = s_pos;
-            if (pos >= a.n_tiles) break;  // the same value in every thread of the workgroup
-            constexpr int kChunks = sizeof(BatchTile) / 16;
-            if (threadIdx.x < kChunks) {
-                const int id = a.order[pos];
-                reinterpret_cast<uint4*>(&s_tile)[threadIdx.x] = reinterpret_cast<const uint4*>(a.tiles + id)[threadIdx.x];
-                if (threadIdx.x == 0) s_id = id;
+        int m = m0;
+        for (int t = t0; t < t1; ++t) {
+            int local = t - uniform(a.inst[m].t[K - 1].tile_begin);
+            int strips = uniform(a.inst[m].t[K - 1].strips), bands = uniform(a.inst[m].t[K - 1].bands);
+            if (local >= strips * bands) {
+                ++m;
+                local = 0;
+                strips = uniform(a.inst[m].t[K - 1].strips);
+                bands = uniform(a.inst[m].t[K - 1].bands);
             }
-            __syncthreads();
-            const BatchTile& t = s_tile;
-            const int nx = uniform(t.nx), ny = uniform(t.ny);
-            const int group2 = uniform(t.group2);
-            const int strip = (group2 >> 1) * kWavesPerGroup + wave;
-            const int c = strip * kOut - kEdge + lane;  // this lane's column
-            const bool col_in = c >= 0 && c < nx;
-            const bool out_lane = col_in && lane >= kEdge && lane < kWave - kEdge;
-            LaneFolds F[K];
-            if (strip < uniform(t.strips)) {
-                StepCoef kc;
-                kc.cx = uniform_f(t.k.cx);
-                kc.cy = uniform_f(t.k.cy);
-                kc.rx = uniform_f(t.k.rx);
-                kc.ry = uniform_f(t.k.ry);
-                kc.e4 = uniform_f(t.k.e4);
-                kc.kf = 0.f;
-                const float* hp = uniform_ptr(t.hp);
-                const float* e0 = uniform_ptr(t.state[cur][0]);
-                const float* u0 = uniform_ptr(t.state[cur][1]);
-                const float* v0 = uniform_ptr(t.state[cur][2]);
-                float* e1 = uniform_ptr(t.state[cur ^ 1][0]);
-                float* u1 = uniform_ptr(t.state[cur ^ 1][1]);
-                float* v1 = uniform_ptr(t.state[cur ^ 1][2]);
-                const int j0 = uniform(t.j0), j1 = uniform(t.j1);
-                if constexpr (K == 1) {
-                    double f_disp = 0.0;
-                    float f_mu = 0.f, f_mv = 0.f;
-                    if (group2 & 1)
-                        march<false>(e0, u0, v0, hp, e1, u1, v1, nx, ny, c, col_in, out_lane, j0, j1, kc, f_disp,
-                                     f_mu, f_mv);
-                    else
-                        march<true>(e0, u0, v0, hp, e1, u1, v1, nx, ny, c, col_in, out_lane, j0, j1, kc, f_disp,
-                                    f_mu, f_mv);
-                    F[0].disp = f_disp;
-                    F[0].max_u = f_mu;
-                    F[0].max_v = f_mv;
-                } else {
-                    if (group2 & 1)
-                        marchK<K, false>(e0, u0, v0, hp, e1, u1, v1, nx, ny, c, col_in, out_lane, j0, j1, kc, F);
-                    else
-                        marchK<K, true>(e0, u0, v0, hp, e1, u1, v1, nx, ny, c, col_in, out_lane, j0, j1, kc, F);
-                }
-            }
-            const int it = s_id;
-#pragma unroll
-            for (int s = 0; s < K; ++s) {
-                double f_disp = F[s].disp;
-                float f_mu = F[s].mu(), f_mv = F[s].mv();
-                batch_wave_sums(f_disp, f_mu, f_mv);
-                if (lane == 0) {
-                    s_disp[wave] = f_disp;
-                    s_mu[wave] = f_mu;
-                    s_mv[wave] = f_mv;
-                }
-                __syncthreads();
-                if (threadIdx.x == 0) {
-                    double d = 0.0;
-                    float m1 = 0.f, m2 = 0.f;
-#pragma unroll
-                    for (int w = 0; w < kWavesPerGroup; ++w) {
-                        d += s_disp[w];
-                        m1 = fmaxf(m1, s_mu[w]);
-                        m2 = fmaxf(m2, s_mv[w]);
-                    }
-                    FoldPartial* q = part + (size_t)s * a.n_tiles + it;
-                    q->disp = d;
-                    q->mu = m1;
-                    q->mv = m2;
-                }
-                __syncthreads();
-            }
+            const BatchInst& in = a.inst[m];
+            const int nx = uniform(in.nx), ny = uniform(in.ny);
+            StepCoef k;
+            k.cx = uniform_f(in.k.cx);
+            k.cy = uniform_f(in.k.cy);
+            k.rx = uniform_f(in.k.rx);
+            k.ry = uniform_f(in.k.ry);
+            k.e4 = uniform_f(in.k.e4);
+            k.kf = 0.f;
+            k.hmin = 0.f;
+            const int band = local / strips, strip = local - band * strips;
+            const int r0 = band * (T - 4 * K), c0 = strip * (kBlockCols - 4 * K) + 2 * lane;
+            const int j0 = band > 0 ? r0 + 2 * K : 0, j1 = band + 1 < bands ? r0 + T - 2 * K : ny;
+            const bool owned = (strip == 0 || lane >= K) && (strip + 1 == strips ? c0 < nx : lane < kWave - K);
+            BlockFolds F[K];
+            block_pass<K, R, W>(uniform_ptr(in.state[cur][0]), uniform_ptr(in.state[cur][1]),
+                                uniform_ptr(in.state[cur][2]), uniform_ptr(in.hp), uniform_ptr(in.state[cur ^ 1][0]),
+                                uniform_ptr(in.state[cur ^ 1][1]), uniform_ptr(in.state[cur ^ 1][2]), nx, ny,
+                                r0 + wave * R, wave, lane, c0, owned, j0, j1, k, sh, F);
+            block_fold<K, W>(F, wave, lane, fsh, part + t, a.n_tiles);
         }
-        if (!grid_barrier(a, (unsigned long long)(step0 + K), &a.ctl->next_tile[(gpass + 1) & 1])) return;
+        if (ps > 0)
+            fold_pass<K>(a, fold_wave, fold_waves, lane, a.part + (size_t)((ps - 1) & 1) * K * a.n_tiles, step0 - K + 1);
+        if (!grid_barrier(a, (unsigned long long)(step0 + K))) return;
     }
-    fold_pass(a, lwg, nwg, ((passes - 1) & 1) * K, base + (long long)(passes - 1) * K + 1, K);
+    fold_pass<K>(a, fold_wave, fold_waves, lane, a.part + (size_t)((passes - 1) & 1) * K * a.n_tiles,
+                 base + (long long)(passes - 1) * K + 1);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.ctl->steps_done = base + a.steps;
         a.ctl->passes_done = pbase + passes;
@@ -353,23 +257,19 @@ struct sw2d_bctx {
     hipStream_t stream;         // the caller's
     hipStream_t capture;        // private stream used only to record graphs
     BatchInst* d_inst;
-    BatchTile* d_tiles;
-    int* d_order;         // tile ids, costliest first
     FoldPartial* d_part;
     sw2d_red* d_ring;
     BatchControl* d_ctl;
     unsigned long long* d_flags;
+    int n_tiles[kBlockMaxK];  // tiles of all members at K = 1.. steps per pass
+    int tile_rows;            // R, rows per wave
     int max_grid;
-    int n_tiles;
     int grid;
     int steps_per_launch;
-    int steps_per_pass;            // K of the batched kernel, 1..kMaxBatchK
+    int steps_per_pass;       // the caller's K, 1..kMaxBatchK: step counts are multiples of it
     bool use_graph;
     int64_t steps_done;
     int64_t passes_done;
-    std::vector<BatchInst> inst;   // host copy (tile ranges for the current K)
-    std::vector<int> rows;         // band height per member
-    size_t tile_capacity;          // descriptors the workspace holds
     hipGraph_t graph;
     hipGraphExec_t exec;
     int graph_n;
@@ -397,47 +297,46 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct BatchLayout {
     std::vector<size_t> hp;  // per instance
-    size_t flags, scratch, inst, tiles, order, part, ring, ctl, gflags, total;
-    int n_tiles;
-    std::vector<int> tiles_of;  // per instance
+    size_t flags, scratch, inst, part, ring, ctl, gflags, total;
+    int tile_rows;
+    int n_tiles[kBlockMaxK];
 };
 
 constexpr int kMaxBatchGrid = 256 * 8;  // flag lines reserved: 8 workgroups on each of 256 CUs
 // Resident workgroups per CU that the grid may count on. The occupancy query counts vector
 // registers and LDS, but a SIMD of this family also holds at most 800 scalar registers, so a
-// kernel near 100 SGPRs fits 7 waves per SIMD even when its vector registers would allow 8;
-// a grid barrier that waits for a workgroup that never became resident would only end at
-// its deadline. 6 keeps a margin below that bound.
-constexpr int kBatchWgPerCu = 6;
-
-
-int rows_for(const sw2d_params& p, const int32_t* band_rows, int i) {
-    int r = band_rows ? band_rows[i] : 16;
-    if (r > p.ny) r = p.ny;
-    return r;
-}
+// kernel near 100 SGPRs fits 7 waves per SIMD even when its vector registers would allow 8 (3
+// workgroups of 8 waves per CU, not 4); a grid barrier that waits for a workgroup that never
+// became resident would only end at its deadline.
+constexpr int kBatchWgPerCu = 3;
 
 bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLayout& L) {
     if (n < 1) return false;
     size_t off = 0;
     L.hp.resize(n);
-    L.tiles_of.resize(n);
-    L.n_tiles = 0;
+    int64_t tiles[2][kBlockMaxK] = {};
+    int64_t sum_rows = 0;
     for (int i = 0; i < n; ++i) {
         if (!sw2d::detail::params_valid(&p[i]) || p[i].flags != 0) return false;  // plain model only
-        const int rows = rows_for(p[i], band_rows, i);
-        if (rows < 1 || (band_rows && band_rows[i] < kMinRows)) return false;
+        const int rows = band_rows ? band_rows[i] : 16;
+        if (rows < kMinRows) return false;
+        sum_rows += rows;
         L.hp[i] = off;
         off = align_up(off + (size_t)p[i].nx * p[i].ny * sizeof(float));
-        // the narrowest strips of any K give the most tiles
-        int narrow = batch_strip_out(1);
-        for (int K = 2; K <= kMaxBatchK; ++K) narrow = std::min(narrow, batch_strip_out(K));
-        const int strips = (p[i].nx + narrow - 1) / narrow;
-        const int groups = (strips + kWavesPerGroup - 1) / kWavesPerGroup;
-        const int bands = (p[i].ny + rows - 1) / rows;
-        L.tiles_of[i] = groups * bands;
-        if ((int64_t)L.n_tiles + L.tiles_of[i] > (1 << 30)) return false;
-        L.n_tiles += L.tiles_of[i];
+        for (int K = 1; K <= kBlockMaxK; ++K) {
+            tiles[0][K - 1] += make_block_geometry(p[i].nx, p[i].ny, K, kBlockRowsLow).nblocks;
+            tiles[1][K - 1] += make_block_geometry(p[i].nx, p[i].ny, K, kBlockRowsHigh).nblocks;
+            if (tiles[0][K - 1] > (1 << 28)) return false;
+        }
+    }
+    // Low tiles (24 rows) for bands below 16 rows, high ones (40 rows) from 16 on; without the
+    // caller's choice low ones while they all run at once (at most 320, as on a single grid).
+    const bool low = band_rows ? sum_rows < 16 * (int64_t)n : tiles[0][kBlockMaxK - 1] <= 320;
+    L.tile_rows = low ? kBlockRowsLow : kBlockRowsHigh;
+    int most = 0;
+    for (int K = 1; K <= kBlockMaxK; ++K) {
+        L.n_tiles[K - 1] = (int)tiles[low ? 0 : 1][K - 1];
+        most = std::max(most, K * L.n_tiles[K - 1]);
     }
     L.flags = off;
     off = align_up(off + (size_t)n * sizeof(PrepFlags));
@@ -445,12 +344,8 @@ bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLa
     off = align_up(off + kHsumBlocks * sizeof(double));
     L.inst = off;
     off = align_up(off + (size_t)n * sizeof(BatchInst));
-    L.tiles = off;
-    off = align_up(off + (size_t)L.n_tiles * sizeof(BatchTile));
-    L.order = off;
-    off = align_up(off + (size_t)L.n_tiles * sizeof(int));
     L.part = off;
-    off = align_up(off + 2 * (size_t)kMaxBatchK * L.n_tiles * sizeof(FoldPartial));
+    off = align_up(off + 2 * (size_t)most * sizeof(FoldPartial));
     L.ring = off;
     off = align_up(off + (size_t)kBatchRing * n * sizeof(sw2d_red));
     L.ctl = off;
@@ -461,108 +356,74 @@ bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLa
     return true;
 }
 
+// The batched kernel for K steps per pass and R rows per wave.
+typedef void (*BatchKernel)(BatchArgs);
+
+BatchKernel batch_kernel(int K, int R) {
+    switch (R == kBlockRowsLow ? K : K + kBlockMaxK) {
+        case 1: return sw2d_batch_kernel<1, kBlockRowsLow>;
+        case 2: return sw2d_batch_kernel<2, kBlockRowsLow>;
+        case 3: return sw2d_batch_kernel<3, kBlockRowsLow>;
+        case 4: return sw2d_batch_kernel<4, kBlockRowsLow>;
+        case 5: return sw2d_batch_kernel<1, kBlockRowsHigh>;
+        case 6: return sw2d_batch_kernel<2, kBlockRowsHigh>;
+        case 7: return sw2d_batch_kernel<3, kBlockRowsHigh>;
+        default: return sw2d_batch_kernel<4, kBlockRowsHigh>;
+    }
+}
+
+// Passes of a chunk of steps: as many of kBlockMaxK steps as it holds, one for the rest.
+int chunk_passes(int32_t steps) { return steps / kBlockMaxK + (steps % kBlockMaxK != 0); }
+
+// Steps per launch chunk: the caller's, rounded down to whole passes of its own K.
+int32_t chunk_steps(const sw2d_bctx* b) {
+    const int K = b->steps_per_pass;
+    return b->steps_per_launch >= K ? b->steps_per_launch / K * K : K;
+}
+
 int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
     BatchArgs a;
     a.inst = b->d_inst;
-    a.tiles = b->d_tiles;
-    a.order = b->d_order;
     a.part = b->d_part;
     a.ring = b->d_ring;
     a.ctl = b->d_ctl;
     a.flags = b->d_flags;
     a.n_inst = b->n;
-    a.n_tiles = b->n_tiles;
     a.timeout_ticks = b->timeout_ticks;
-    const int K = b->steps_per_pass;
-    const int per_launch = b->steps_per_launch >= K ? b->steps_per_launch / K * K : K;
+    const int32_t per_launch = chunk_steps(b);
     for (int32_t done = 0; done < nsteps;) {
-        a.steps = (nsteps - done < per_launch) ? nsteps - done : per_launch;  // a multiple of K
-        switch (K) {
-            case 1:
-                hipLaunchKernelGGL(sw2d_batch_kernel<1>, dim3(b->grid), dim3(kBatchThreads), 0, s, a);
-                break;
-            case 2:
-                hipLaunchKernelGGL(sw2d_batch_kernel<2>, dim3(b->grid), dim3(kBatchThreads), 0, s, a);
-                break;
-            case 3:
-                hipLaunchKernelGGL(sw2d_batch_kernel<3>, dim3(b->grid), dim3(kBatchThreads), 0, s, a);
-                break;
-            default:
-                return SW2D_EINVAL;
+        const int32_t chunk = nsteps - done < per_launch ? nsteps - done : per_launch;
+        const int32_t rest = chunk % kBlockMaxK;
+        for (const int K : {kBlockMaxK, (int)rest}) {
+            a.steps = K == rest ? rest : chunk - rest;
+            if (a.steps == 0) continue;
+            a.n_tiles = b->n_tiles[K - 1];
+            // no more workgroups than have tiles, or folds beside them, to do
+            const int64_t useful = (int64_t)a.n_tiles + ((int64_t)b->n * K + kBlockWaves - 1) / kBlockWaves;
+            const int grid = useful < b->grid ? (int)useful : b->grid;
+            hipLaunchKernelGGL(batch_kernel(K, b->tile_rows), dim3(grid), dim3(kBatchThreads), 0, s, a);
+            SW2D_BHIP(hipGetLastError());
         }
-        SW2D_BHIP(hipGetLastError());
-        done += a.steps;
+        done += chunk;
     }
     return SW2D_OK;
 }
 
-// Tile list of every member for K steps per pass (strips of batch_strip_out(K) columns),
-// written to the device with the members' tile ranges.
-int upload_tiles(sw2d_bctx* b, int K) {
-    std::vector<BatchTile> tiles;
-    std::vector<int> cost;
-    const int out = batch_strip_out(K);
-    for (int i = 0; i < b->n; ++i) {
-        BatchInst& in = b->inst[i];
-        in.strips = (in.nx + out - 1) / out;
-        in.tile_begin = (int)tiles.size();
-        const int rows = b->rows[i];
-        const int groups = (in.strips + kWavesPerGroup - 1) / kWavesPerGroup;
-        const int bands = (in.ny + rows - 1) / rows;
-        for (int blk = 0; blk < bands; blk += 2)
-            for (int gr = 0; gr < groups; ++gr)
-                for (int bd = blk; bd < blk + 2 && bd < bands; ++bd) {
-                    BatchTile t;
-                    std::memset(&t, 0, sizeof t);
-                    t.hp = in.hp;
-                    for (int buf = 0; buf < 2; ++buf)
-                        for (int f = 0; f < 3; ++f) t.state[buf][f] = in.state[buf][f];
-                    t.nx = in.nx;
-                    t.ny = in.ny;
-                    t.strips = in.strips;
-                    t.j0 = bd * rows;
-                    t.j1 = (t.j0 + rows < in.ny) ? t.j0 + rows : in.ny;
-                    t.group2 = 2 * gr + (bd & 1);
-                    t.inst = i;
-                    t.k = in.k;
-                    tiles.push_back(t);
-                    const int strips_here = in.strips - kWavesPerGroup * gr;
-                    cost.push_back((t.j1 - t.j0 + 4 * K) *
-                                   (strips_here < kWavesPerGroup ? strips_here : kWavesPerGroup));
-                }
-        in.tile_end = (int)tiles.size();
-    }
-    if (tiles.size() > b->tile_capacity) return SW2D_ENOSPC;
-    b->n_tiles = (int)tiles.size();
-    // hand-out order: costliest first (rows marched x strips); equal costs keep list order, so
-    // the neighbouring bands of a member go out together
-    std::vector<int> order(tiles.size());
-    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
-    SW2D_BHIP(hipMemcpyAsync(b->d_inst, b->inst.data(), b->n * sizeof(BatchInst), hipMemcpyHostToDevice, b->stream));
-    SW2D_BHIP(hipMemcpyAsync(b->d_tiles, tiles.data(), tiles.size() * sizeof(BatchTile), hipMemcpyHostToDevice,
-                             b->stream));
-    if (!order.empty())
-        SW2D_BHIP(hipMemcpyAsync(b->d_order, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice,
-                                 b->stream));
-    SW2D_BHIP(hipStreamSynchronize(b->stream));
-    return SW2D_OK;
-}
-
-// Workgroups of the K-step kernel the device holds at once (capped, see kBatchWgPerCu).
-int resident_grid(int K, int* out) {
-    int dev = 0, cus = 0, per_cu = 0;
+// Workgroups of the tile kernels the device holds at once (capped, see kBatchWgPerCu): the least
+// of the passes of every length.
+int resident_grid(int R, int* out) {
+    int dev = 0, cus = 0, least = kBatchWgPerCu;
     SW2D_BHIP(hipGetDevice(&dev));
     SW2D_BHIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const void* fn = K == 1   ? reinterpret_cast<const void*>(&sw2d_batch_kernel<1>)
-                     : K == 2 ? reinterpret_cast<const void*>(&sw2d_batch_kernel<2>)
-                              : reinterpret_cast<const void*>(&sw2d_batch_kernel<3>);
-    SW2D_BHIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBatchThreads, 0));
-    if (per_cu < 1 || cus < 1) return SW2D_EINVAL;
-    if (per_cu > kBatchWgPerCu) per_cu = kBatchWgPerCu;
-    int g = cus * per_cu;
-    if (g > kMaxBatchGrid) g = kMaxBatchGrid;
-    *out = g;
+    for (int K = 1; K <= kBlockMaxK; ++K) {
+        int per_cu = 0;
+        SW2D_BHIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void*>(batch_kernel(K, R)), kBatchThreads, 0));
+        if (per_cu < least) least = per_cu;
+    }
+    if (least < 1 || cus < 1) return SW2D_EINVAL;
+    const int g = cus * least;
+    *out = g < kMaxBatchGrid ? g : kMaxBatchGrid;
     return SW2D_OK;
 }
 
@@ -609,11 +470,10 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
     b->steps_per_launch = 50;
     b->use_graph = true;
     b->steps_done = 0;
-    b->n_tiles = L.n_tiles;
+    std::copy(L.n_tiles, L.n_tiles + kBlockMaxK, b->n_tiles);
+    b->tile_rows = L.tile_rows;
     char* w = static_cast<char*>(d_work);
     b->d_inst = reinterpret_cast<BatchInst*>(w + L.inst);
-    b->d_tiles = reinterpret_cast<BatchTile*>(w + L.tiles);
-    b->d_order = reinterpret_cast<int*>(w + L.order);
     b->d_flags = reinterpret_cast<unsigned long long*>(w + L.gflags);
     b->d_part = reinterpret_cast<FoldPartial*>(w + L.part);
     b->d_ring = reinterpret_cast<sw2d_red*>(w + L.ring);
@@ -643,9 +503,8 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return fail(batch_hip_fail(e, "sw2d_batch_create"));
 
-    b->inst.assign(n, BatchInst{});
-    b->rows.assign(n, 0);
-    b->tile_capacity = (size_t)L.n_tiles;
+    std::vector<BatchInst> inst(n);
+    int tile_begin[kBlockMaxK] = {};
     for (int i = 0; i < n; ++i) {
         if (flags[i].bad != 0 || flags[i].hmax_bits == 0) return fail(SW2D_EINVAL);
         float hmax;
@@ -654,7 +513,7 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
         const double courant =
             q.dt * std::sqrt(q.g * (double)hmax) * std::sqrt(1.0 / (q.dx * q.dx) + 1.0 / (q.dy * q.dy));
         if (!(courant <= 1.0)) return fail(SW2D_EINVAL);
-        BatchInst& in = b->inst[i];
+        BatchInst& in = inst[i];
         in.hp = reinterpret_cast<const float*>(w + L.hp[i]);
         const size_t cells = (size_t)q.nx * q.ny;
         for (int buf = 0; buf < 2; ++buf)
@@ -664,16 +523,19 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
         in.k = sw2d::detail::make_coef(&q);
         in.cell_area = q.dx * q.dy;
         in.h_sum = flags[i].h_sum;
-        b->rows[i] = rows_for(q, band_rows, i);
+        for (int K = 1; K <= kBlockMaxK; ++K) {
+            const BlockGeometry g = make_block_geometry(q.nx, q.ny, K, b->tile_rows);
+            in.t[K - 1] = BatchTiles{g.strips, g.bands, tile_begin[K - 1]};
+            tile_begin[K - 1] += g.nblocks;
+        }
     }
     b->steps_per_pass = 1;
     b->passes_done = 0;
-    int rc = upload_tiles(b, 1);
-    if (rc) return fail(rc);
     BatchControl ctl;
     std::memset(&ctl, 0, sizeof ctl);
     std::vector<unsigned long long> zero_flags((size_t)kMaxBatchGrid * kFlagStride, 0ull);
-    e = hipMemcpyAsync(b->d_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice, b->stream);
+    e = hipMemcpyAsync(b->d_inst, inst.data(), n * sizeof(BatchInst), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(b->d_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_flags, zero_flags.data(), zero_flags.size() * sizeof(unsigned long long),
                            hipMemcpyHostToDevice, b->stream);
@@ -685,7 +547,7 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
     e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev);
     if (e != hipSuccess) return fail(batch_hip_fail(e, "device query"));
-    rc = resident_grid(1, &b->max_grid);
+    const int rc = resident_grid(b->tile_rows, &b->max_grid);
     if (rc) return fail(rc);
     b->grid = b->max_grid;
     if (clock_khz <= 0) clock_khz = 100000;
@@ -700,15 +562,7 @@ int sw2d_batch_set_time_blocking(sw2d_batch_t b, int32_t steps_per_pass) {
     if (!b) return SW2D_ESTATE;
     if (steps_per_pass < 1 || steps_per_pass > kMaxBatchK) return SW2D_EINVAL;
     if (steps_per_pass == b->steps_per_pass) return SW2D_OK;
-    SW2D_BHIP(hipStreamSynchronize(b->stream));  // launches in flight read the old tile list
-    int max_grid = 0;
-    int rc = resident_grid(steps_per_pass, &max_grid);
-    if (rc) return rc;
-    rc = upload_tiles(b, steps_per_pass);
-    if (rc) return rc;
     b->steps_per_pass = steps_per_pass;
-    b->max_grid = max_grid;
-    if (b->grid > max_grid || b->grid <= 0) b->grid = max_grid;
     drop_graph(b);
     return SW2D_OK;
 }
@@ -756,7 +610,8 @@ int sw2d_batch_step(sw2d_batch_t b, int32_t nsteps) {
         SW2D_BHIP(hipGraphLaunch(b->exec, b->stream));
     }
     b->steps_done += nsteps;
-    b->passes_done += nsteps / b->steps_per_pass;
+    const int32_t per_launch = chunk_steps(b);
+    b->passes_done += (int64_t)(nsteps / per_launch) * chunk_passes(per_launch) + chunk_passes(nsteps % per_launch);
     return SW2D_OK;
 }
 

@@ -1,8 +1,7 @@
 // sw2d_block.h - K time steps of one register tile (plain model).
 //
 // A workgroup of W waves holds a tile of W * R rows x 128 columns in registers: wave w the R
-// rows from w R on, lane l the columns 2l and 2l + 1 of the tile ("a" and "b", as in
-// sw2d_pair.h). The tile is read once, stepped K times in place and its owned cells written
+// rows from w R on, lane l the columns 2l and 2l + 1 of the tile ("a" and "b"). The tile is read once, stepped K times in place and its owned cells written
 // once. East/west neighbours are the lane's other column and one lane exchange; the rows
 // beyond a wave's own go through LDS, two rows of one field per wave and exchange: the surface
 // (and v of the row below) before the predictor, the predicted surface before the filter. A
@@ -26,7 +25,7 @@
 // cache take 14.5 us at a large copy's rate there, so several steps per pass are what beats it).
 #pragma once
 
-#include "sw2d_pair.h"
+#include "sw2d_tile.h"
 
 namespace sw2d {
 
@@ -40,12 +39,47 @@ struct BlockShared {
     float2 top_s[W + 2][kWave], bot_s[W + 2][kWave];
 };
 
+// Row accesses of a column pair, 8 bytes whatever the row's alignment (multi-dword buffer accesses
+// need dword alignment only). An odd nx leaves the last pair astride the row end: its load takes
+// the first cell of the next row as column b, which is land (depth 0) as every border cell is,
+// and its store writes column a alone. In the grid's last row that pair may read zeros: land too.
+struct BlockIO {
+    int nx, ny;
+    unsigned off;   // byte offset of column a
+    unsigned row_bytes;
+    bool odd;
+
+    __device__ __forceinline__ BlockIO(int nx_, int ny_, int c0)
+        : nx(nx_), ny(ny_), off((unsigned)c0 * 4u), row_bytes((unsigned)nx_ * 4u), odd((nx_ & 1) != 0) {}
+
+    __device__ __forceinline__ void load(const float* __restrict__ p, int r, float (&x)[2]) const {
+        const bool in = r >= 0 && r < ny;
+        const unsigned bytes = in ? row_bytes + (odd && r + 1 < ny ? 4u : 0u) : 0u;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(p + (ptrdiff_t)(in ? r : 0) * nx), 0, (int)bytes, kRsrcWord3);
+        const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+        x[0] = __uint_as_float(q[0]);
+        x[1] = __uint_as_float(q[1]);
+    }
+    // r: a row of the grid; owned: this lane's pair is written
+    __device__ __forceinline__ void store(float* __restrict__ p, int r, bool owned, const float (&x)[2]) const {
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(p + (ptrdiff_t)r * nx, 0, (int)row_bytes, kRsrcWord3);
+        __attribute__((ext_vector_type(2))) unsigned q;
+        q[0] = __float_as_uint(x[0]);
+        q[1] = __float_as_uint(x[1]);
+        __builtin_amdgcn_raw_buffer_store_b64(q, rs, (int)(owned && off + 4u < row_bytes ? off : kNoLane), 0, 0);
+        if (odd)  // wave-uniform
+            __builtin_amdgcn_raw_buffer_store_b32(q[0], rs, (int)(owned && off + 4u == row_bytes ? off : kNoLane), 0, 0);
+    }
+};
+
 struct BlockFolds {
     double disp = 0.0;
     float max_u = 0.f, max_v = 0.f;
 };
 
-template <int K, int R, int W, bool kWide>
+template <int K, int R, int W>
 __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const float* __restrict__ u_i,
                                            const float* __restrict__ v_i, const float* __restrict__ hp_i,
                                            float* __restrict__ eta_o, float* __restrict__ u_o,
@@ -53,7 +87,7 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
                                            int c0, bool owned, int j0, int j1, const StepCoef& k,
                                            BlockShared<W>& sh, BlockFolds (&F)[K]) {
 #pragma clang fp contract(off)
-    const PairIO<kWide> io{nx, ny, (unsigned)c0 * 4u};
+    const BlockIO io(nx, ny, c0);
     float e[R][2], u[R][2], v[R][2], hp[R][2];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -170,15 +204,122 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
             }
         }
     }
-    const unsigned so = owned ? (unsigned)c0 * 4u : kNoLane;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int row = rbase + r;
         if (row >= j0 && row < j1) {
-            io.store(eta_o, row, so, e[r]);
-            io.store(u_o, row, so, u[r]);
-            io.store(v_o, row, so, v[r]);
+            io.store(eta_o, row, owned, e[r]);
+            io.store(u_o, row, owned, u[r]);
+            io.store(v_o, row, owned, v[r]);
         }
+    }
+}
+
+// Sums of the surface and maxima of the velocities of K <= 4 steps over a wave. Swapping half
+// waves of two steps' values and then adding reduces both at once, so the four steps end up in
+// the wave's four rows of 16 lanes (row s: step s, complete in every lane of the row) after one
+// two-step exchange per pair, one four-step exchange and four levels within the rows: 41 vector
+// instructions against 24 LDS exchanges per step for a plain butterfly. The order is fixed.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+template <bool kHalves>  // kHalves: 32-lane halves, otherwise 16-lane rows
+__device__ __forceinline__ void swap_lanes(unsigned& a, unsigned& b) {
+    u32x2 r;
+    if constexpr (kHalves)
+        r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    else
+        r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+template <bool kHalves>
+__device__ __forceinline__ float swap_max(float a, float b) {
+    unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    swap_lanes<kHalves>(x, y);
+    return fmaxf(__uint_as_float(x), __uint_as_float(y));
+}
+
+template <bool kHalves>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const unsigned long long p = __double_as_longlong(a), q = __double_as_longlong(b);
+    unsigned xl = (unsigned)p, xh = (unsigned)(p >> 32), yl = (unsigned)q, yh = (unsigned)(q >> 32);
+    swap_lanes<kHalves>(xl, yl);
+    swap_lanes<kHalves>(xh, yh);
+    return __longlong_as_double((long long)(((unsigned long long)xh << 32) | xl)) +
+           __longlong_as_double((long long)(((unsigned long long)yh << 32) | yl));
+}
+
+template <int kCtrl>
+__device__ __forceinline__ unsigned dpp(unsigned x) {
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)x, kCtrl, 0xf, 0xf, true);
+}
+
+template <int kCtrl>
+__device__ __forceinline__ void row_level(BlockFolds& f) {
+    const unsigned long long p = __double_as_longlong(f.disp);
+    const unsigned lo = dpp<kCtrl>((unsigned)p), hi = dpp<kCtrl>((unsigned)(p >> 32));
+    f.disp += __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    f.max_u = fmaxf(f.max_u, __uint_as_float(dpp<kCtrl>(__float_as_uint(f.max_u))));
+    f.max_v = fmaxf(f.max_v, __uint_as_float(dpp<kCtrl>(__float_as_uint(f.max_v))));
+}
+
+template <bool kHalves>
+__device__ __forceinline__ BlockFolds swap_fold(const BlockFolds& a, const BlockFolds& b) {
+    BlockFolds r;
+    r.disp = swap_add<kHalves>(a.disp, b.disp);
+    r.max_u = swap_max<kHalves>(a.max_u, b.max_u);
+    r.max_v = swap_max<kHalves>(a.max_v, b.max_v);
+    return r;
+}
+
+template <int K>
+__device__ __forceinline__ BlockFolds wave_folds(const BlockFolds (&F)[K]) {
+    static_assert(K <= 4, "one row of lanes per step");
+    const BlockFolds none;
+    const BlockFolds even = swap_fold<true>(F[0], K > 2 ? F[K > 2 ? 2 : 0] : none);
+    const BlockFolds odd = swap_fold<true>(K > 1 ? F[K > 1 ? 1 : 0] : none, K > 3 ? F[K > 3 ? 3 : 0] : none);
+    BlockFolds r = swap_fold<false>(even, odd);
+    row_level<0xB1>(r);   // quad_perm [1, 0, 3, 2]
+    row_level<0x4E>(r);   // quad_perm [2, 3, 0, 1]
+    row_level<0x141>(r);  // row_half_mirror
+    row_level<0x140>(r);  // row_mirror
+    return r;
+}
+
+// A tile's folds of K steps: the waves' sums added in wave order, one partial per step at
+// part[s * stride]. Every wave has passed its last read of the tile's exchange rows when this
+// returns, so the next tile may use them.
+template <int W>
+struct BlockFoldShared {
+    double disp[4][W];
+    float mu[4][W], mv[4][W];
+};
+
+template <int K, int W>
+__device__ __forceinline__ void block_fold(const BlockFolds (&F)[K], int wave, int lane, BlockFoldShared<W>& sh,
+                                           FoldPartial* __restrict__ part, size_t stride) {
+    const BlockFolds f = wave_folds<K>(F);
+    const int s = lane / 16;
+    if (lane % 16 == 0) {
+        sh.disp[s][wave] = f.disp;
+        sh.mu[s][wave] = f.max_u;
+        sh.mv[s][wave] = f.max_v;
+    }
+    __syncthreads();
+    if (wave == 0 && lane < K) {
+        double d = 0.0;
+        float mu = 0.f, mv = 0.f;
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            d += sh.disp[lane][i];
+            mu = fmaxf(mu, sh.mu[lane][i]);
+            mv = fmaxf(mv, sh.mv[lane][i]);
+        }
+        FoldPartial* o = part + (size_t)lane * stride;
+        o->disp = d;
+        o->mu = mu;
+        o->mv = mv;
     }
 }
 
