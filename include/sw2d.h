@@ -159,12 +159,12 @@ int64_t sw2d_steps_done(sw2d_t h);
 int sw2d_set_state(sw2d_t h, const float *d_eta, const float *d_u, const float *d_v, int64_t step);
 
 /* How the steps of a handle are scheduled never changes the state (bit for bit) and regroups
- * the fold sums at most. The plain model (flags = 0) on at most 2^23 cells, whose state and
- * depth stay in the 256 MB last-level cache, is advanced over tiles held in registers, up to 4
- * steps per launch; larger grids and the model variants are streamed through row pipelines as
- * the two settings below say. on != 0 streams a small plain grid as well (0, the default,
- * restores the tiles); sw2d_streaming returns 1 if the handle's steps are streamed, 0 if they
- * go over tiles, -1 for a NULL handle. */
+ * the fold sums at most. The plain model (flags = 0) is advanced over tiles held in registers,
+ * several steps per launch: grids of at most 2^23 cells, whose state and depth stay in the 256 MB
+ * last-level cache, always (up to 4 steps per launch), larger ones at 4 steps per pass. Other
+ * passes are streamed through row pipelines as the two settings below say. on != 0 streams
+ * every pass of the handle (0, the default, restores the tiles); sw2d_streaming returns 1 if its
+ * steps are streamed, 0 if they go over tiles, -1 for a NULL handle. */
 int sw2d_set_streaming(sw2d_t h, int32_t on);
 int32_t sw2d_streaming(sw2d_t h);
 
@@ -174,10 +174,11 @@ int32_t sw2d_streaming(sw2d_t h);
 int sw2d_set_band_rows(sw2d_t h, int32_t rows);
 int32_t sw2d_band_rows(sw2d_t h);
 
-/* Temporal blocking of the streamed steps: steps_per_pass = K in 2..4 makes sw2d_step advance K
- * steps per pass over HBM (the intermediate states stay in registers; a remainder of the step count takes
- * one shorter pass), with its own band height rows in [8, ny]; 1 (the default) restores one
- * step per pass. The state and folds are the same as with single steps (the state bit for
+/* Temporal blocking: steps_per_pass = K in 2..4 makes sw2d_step advance K steps per pass over
+ * HBM (the intermediate states stay in registers; a remainder of the step count takes one
+ * shorter pass), with its own band height rows in [8, ny] where the pass is streamed; 1 (the
+ * default) restores one step per pass. Grids that stay in the cache make no pass over HBM and
+ * take as many steps per launch as is fastest. The state and folds are the same as with single steps (the state bit for
  * bit, the folds up to the order of their sums). SW2D_EINVAL for K or rows out of range, or
  * K > 1 on a handle with SW2D_ADVECTION. */
 int sw2d_set_time_blocking(sw2d_t h, int32_t steps_per_pass, int32_t rows);

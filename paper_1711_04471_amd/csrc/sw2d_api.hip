@@ -135,9 +135,17 @@ int flush_folds(sw2d_ctx* h, int pending, int nparts, int stride) {
     return SW2D_OK;
 }
 
-// Whether the handle's steps go over register tiles.
-bool uses_tiles(const sw2d_ctx* h) {
-    return !h->streaming && h->p.flags == 0 && (int64_t)h->p.nx * h->p.ny <= kBlockMaxCells;
+// Whether the grid's steps and depth stay in the Infinity Cache (kBlockMaxCells).
+bool cached_grid(const sw2d_ctx* h) { return (int64_t)h->p.nx * h->p.ny <= kBlockMaxCells; }
+
+// Whether a pass of k steps goes over register tiles (see kBlockMaxCells).
+bool tile_pass(const sw2d_ctx* h, int k) {
+    return !h->streaming && h->p.flags == 0 && (cached_grid(h) || k == kBlockMaxK);
+}
+
+// Steps per pass of the handle: up to kBlockMaxK over tiles of a cached grid, else the caller's.
+int pass_steps(const sw2d_ctx* h) {
+    return cached_grid(h) && tile_pass(h, 1) ? kBlockMaxK : h->steps_per_pass;
 }
 
 int add_pass_times(hipEvent_t* ev, int passes, double* total_ms) {
@@ -150,19 +158,19 @@ int add_pass_times(hipEvent_t* ev, int passes, double* total_ms) {
     return SW2D_OK;
 }
 
-// Enqueue nsteps steps: register tiles take up to kBlockMaxK steps per pass, the row-marching
-// passes steps_per_pass (a remainder takes one shorter pass). The fold partials of successive
-// passes of one grid size are buffered while slots last, then added by one fold launch. With
+// Enqueue nsteps steps in passes of pass_steps steps (a remainder takes one shorter pass), over
+// register tiles or through the row pipelines. The fold partials of successive passes with the
+// same number of workgroups are buffered while slots last, then added by one fold launch. With
 // events (2 per pass, at most kFoldChunk passes between folds) the step kernels are timed.
 int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms) {
-    const bool tiles = uses_tiles(h);
-    const int kmax = tiles ? kBlockMaxK : h->steps_per_pass;
+    const int kmax = pass_steps(h);
     BlockGeometry bg{};
     int bg_k = 0;
     int pending = 0, nparts = 0, passes = 0;
     int32_t done = 0;
     while (done < nsteps) {
         const int k = (nsteps - done < kmax) ? nsteps - done : kmax;
+        const bool tiles = tile_pass(h, k);
         if (tiles && k != bg_k) {
             bg = block_geometry(h->p.nx, h->p.ny, k);
             bg_k = k;
@@ -376,7 +384,7 @@ int sw2d_set_streaming(sw2d_t h, int32_t on) {
     return SW2D_OK;
 }
 
-int32_t sw2d_streaming(sw2d_t h) { return h ? (uses_tiles(h) ? 0 : 1) : -1; }
+int32_t sw2d_streaming(sw2d_t h) { return h ? (tile_pass(h, pass_steps(h)) ? 0 : 1) : -1; }
 
 int32_t sw2d_time_blocking(sw2d_t h) { return h ? h->steps_per_pass : -1; }
 

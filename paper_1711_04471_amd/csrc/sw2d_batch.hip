@@ -310,11 +310,14 @@ constexpr int kMaxBatchGrid = 256 * 8;  // flag lines reserved: 8 workgroups on 
 // became resident would only end at its deadline.
 constexpr int kBatchWgPerCu = 3;
 
+constexpr int kBatchRows[3] = {kBlockRowsLow, kBlockRowsMid, kBlockRowsHigh};
+constexpr int kBatchHighTiles = 2048;  // fewest tiles of 64 rows chosen without the caller's word
+
 bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLayout& L) {
     if (n < 1) return false;
     size_t off = 0;
     L.hp.resize(n);
-    int64_t tiles[2][kBlockMaxK] = {};
+    int64_t tiles[3][kBlockMaxK] = {};
     int64_t sum_rows = 0;
     for (int i = 0; i < n; ++i) {
         if (!sw2d::detail::params_valid(&p[i]) || p[i].flags != 0) return false;  // plain model only
@@ -324,18 +327,26 @@ bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLa
         L.hp[i] = off;
         off = align_up(off + (size_t)p[i].nx * p[i].ny * sizeof(float));
         for (int K = 1; K <= kBlockMaxK; ++K) {
-            tiles[0][K - 1] += make_block_geometry(p[i].nx, p[i].ny, K, kBlockRowsLow).nblocks;
-            tiles[1][K - 1] += make_block_geometry(p[i].nx, p[i].ny, K, kBlockRowsHigh).nblocks;
+            for (int r = 0; r < 3; ++r)
+                tiles[r][K - 1] += make_block_geometry(p[i].nx, p[i].ny, K, kBatchRows[r]).nblocks;
             if (tiles[0][K - 1] > (1 << 28)) return false;
         }
     }
-    // Low tiles (24 rows) for bands below 16 rows, high ones (40 rows) from 16 on; without the
-    // caller's choice low ones while they all run at once (at most 320, as on a single grid).
-    const bool low = band_rows ? sum_rows < 16 * (int64_t)n : tiles[0][kBlockMaxK - 1] <= 320;
-    L.tile_rows = low ? kBlockRowsLow : kBlockRowsHigh;
+    // The tile height follows the band height: tiles of 24 rows for bands below 16 rows on average,
+    // of 40 rows below 48, of 64 rows from there. Without the caller's choice: the lowest while they
+    // all run at once (as on a single grid), the highest when even those take several rounds (their
+    // overlap is the least).
+    int r = 1;
+    if (band_rows)
+        r = sum_rows < 16 * (int64_t)n ? 0 : sum_rows < 48 * (int64_t)n ? 1 : 2;
+    else if (tiles[0][kBlockMaxK - 1] <= kBlockLowTiles)
+        r = 0;
+    else if (tiles[2][kBlockMaxK - 1] >= kBatchHighTiles)
+        r = 2;
+    L.tile_rows = kBatchRows[r];
     int most = 0;
     for (int K = 1; K <= kBlockMaxK; ++K) {
-        L.n_tiles[K - 1] = (int)tiles[low ? 0 : 1][K - 1];
+        L.n_tiles[K - 1] = (int)tiles[r][K - 1];
         most = std::max(most, K * L.n_tiles[K - 1]);
     }
     L.flags = off;
@@ -359,17 +370,20 @@ bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLa
 // The batched kernel for K steps per pass and R rows per wave.
 typedef void (*BatchKernel)(BatchArgs);
 
-BatchKernel batch_kernel(int K, int R) {
-    switch (R == kBlockRowsLow ? K : K + kBlockMaxK) {
-        case 1: return sw2d_batch_kernel<1, kBlockRowsLow>;
-        case 2: return sw2d_batch_kernel<2, kBlockRowsLow>;
-        case 3: return sw2d_batch_kernel<3, kBlockRowsLow>;
-        case 4: return sw2d_batch_kernel<4, kBlockRowsLow>;
-        case 5: return sw2d_batch_kernel<1, kBlockRowsHigh>;
-        case 6: return sw2d_batch_kernel<2, kBlockRowsHigh>;
-        case 7: return sw2d_batch_kernel<3, kBlockRowsHigh>;
-        default: return sw2d_batch_kernel<4, kBlockRowsHigh>;
+template <int R>
+BatchKernel batch_kernel_of(int K) {
+    switch (K) {
+        case 1: return sw2d_batch_kernel<1, R>;
+        case 2: return sw2d_batch_kernel<2, R>;
+        case 3: return sw2d_batch_kernel<3, R>;
+        default: return sw2d_batch_kernel<4, R>;
     }
+}
+
+BatchKernel batch_kernel(int K, int R) {
+    return R == kBlockRowsLow   ? batch_kernel_of<kBlockRowsLow>(K)
+           : R == kBlockRowsMid ? batch_kernel_of<kBlockRowsMid>(K)
+                                : batch_kernel_of<kBlockRowsHigh>(K);
 }
 
 // Passes of a chunk of steps: as many of kBlockMaxK steps as it holds, one for the rest.

@@ -74,6 +74,9 @@ struct BlockIO {
     }
 };
 
+// This lane's bit of a lane mask held in scalar registers.
+__device__ __forceinline__ bool lane_bit(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 struct BlockFolds {
     double disp = 0.0;
     float max_u = 0.f, max_v = 0.f;
@@ -104,13 +107,15 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
         sh.bot_e[W + 1][lane] = z;
         sh.bot_s[W + 1][lane] = z;
     }
-    bool w[R][2], au[R][2], av[R + 1][2];
+    // water masks of the tile's rows (w[r + 1]: row r) and of the rows beyond the wave's own, one
+    // bit per lane
+    uint64_t w[R + 2][2];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            w[r][c] = hp[r][c] > 0.f;
-            e[r][c] = w[r][c] ? e[r][c] : 0.f;  // the surface of a land cell is never used
+            w[r + 1][c] = __ballot(hp[r][c] > 0.f);
+            e[r][c] = lane_bit(w[r + 1][c]) ? e[r][c] : 0.f;  // the surface of a land cell is never used
         }
     }
     auto publish = [&]() {
@@ -125,22 +130,25 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
     const float2 hpS2 = sh.top_s[wave][lane], hpN2 = sh.bot_s[wave + 2][lane];
     const float hpS[2] = {hpS2.x, hpS2.y}, hpN[2] = {hpN2.x, hpN2.y};
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const bool wEb = from_east(hp[r][0]) > 0.f;
-        au[r][0] = w[r][0] && w[r][1];
-        au[r][1] = w[r][1] && wEb;
-    }
-#pragma unroll
     for (int c = 0; c < 2; ++c) {
-        av[0][c] = hpS[c] > 0.f && w[0][c];
-#pragma unroll
-        for (int r = 1; r < R; ++r) av[r][c] = w[r - 1][c] && w[r][c];
-        av[R][c] = w[R - 1][c] && hpN[c] > 0.f;
+        w[0][c] = __ballot(hpS[c] > 0.f);
+        w[R + 1][c] = __ballot(hpN[c] > 0.f);
     }
+    // Activity of a face = both its cells are water: formed from the water masks by scalar
+    // operations wherever it is used (the scalar unit idles otherwise). Kept for the whole pass, the
+    // faces' masks would not fit the scalar registers; forget() keeps the compiler from trying.
+    auto forget = [&]() {
+#pragma unroll
+        for (int r = 0; r < R + 2; ++r) asm volatile("" : "+s"(w[r][0]), "+s"(w[r][1]));
+    };
+    auto east_a = [&](int r) { return lane_bit(w[r + 1][0] & w[r + 1][1]); };
+    auto east_b = [&](int r) { return lane_bit(w[r + 1][1] & (w[r + 1][0] >> 1)); };
+    auto north = [&](int r, int c) { return lane_bit(w[r + 1][c] & w[r + 2][c]); };  // face between r and r + 1
 #pragma unroll
     for (int s = 0; s < K; ++s) {
         if (s > 0) publish();
         __syncthreads();
+        forget();
         const float2 eS2 = sh.top_e[wave][lane], vS2 = sh.top_v[wave][lane], eN2 = sh.bot_e[wave + 2][lane];
         const float eS[2] = {eS2.x, eS2.y}, vS[2] = {vS2.x, vS2.y}, eN[2] = {eN2.x, eN2.y};
         float es[R][2], sx[R][2];
@@ -148,14 +156,14 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             h[c] = hp[0][c] + e[0][c];
-            fyS[c] = upwind_flux(y_pred(eS[c], e[0][c], vS[c], av[0][c], k), hpS[c] + eS[c], h[c]);
+            fyS[c] = upwind_flux(y_pred(eS[c], e[0][c], vS[c], north(-1, c), k), hpS[c] + eS[c], h[c]);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             // x faces of the row (lane exchanges are taken by every lane)
             const float eEb = from_east(e[r][0]), hEb = from_east(h[0]);
-            const float usa = x_pred(e[r][0], e[r][1], u[r][0], au[r][0], k);
-            const float usb = x_pred(e[r][1], eEb, u[r][1], au[r][1], k);
+            const float usa = x_pred(e[r][0], e[r][1], u[r][0], east_a(r), k);
+            const float usb = x_pred(e[r][1], eEb, u[r][1], east_b(r), k);
             const float fxa = upwind_flux(usa, h[0], h[1]);
             const float fxb = upwind_flux(usb, h[1], hEb);
             const float pe[2] = {x_update(e[r][0], fxa, from_west(fxb), k), x_update(e[r][1], fxb, fxa, k)};
@@ -166,7 +174,7 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
             for (int c = 0; c < 2; ++c) {
                 const float eU = r + 1 < R ? e[r + 1 < R ? r + 1 : r][c] : eN[c];
                 const float hU = (r + 1 < R ? hp[r + 1 < R ? r + 1 : r][c] : hpN[c]) + eU;
-                const float vs = y_pred(e[r][c], eU, v[r][c], av[r + 1][c], k);
+                const float vs = y_pred(e[r][c], eU, v[r][c], north(r, c), k);
                 const float fyN = upwind_flux(vs, h[c], hU);
                 es[r][c] = fmaf(-k.ry, fyN - fyS[c], pe[c]);
                 v[r][c] = vs;
@@ -174,27 +182,28 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
                 h[c] = hU;
             }
             const float esEb = from_east(es[r][0]);
-            const float da = au[r][0] ? es[r][1] - es[r][0] : 0.f;
-            const float db = au[r][1] ? esEb - es[r][1] : 0.f;
+            const float da = east_a(r) ? es[r][1] - es[r][0] : 0.f;
+            const float db = east_b(r) ? esEb - es[r][1] : 0.f;
             sx[r][0] = da - from_west(db);
             sx[r][1] = db - da;
         }
         sh.top_s[wave + 1][lane] = make_float2(es[R - 1][0], es[R - 1][1]);
         sh.bot_s[wave + 1][lane] = make_float2(es[0][0], es[0][1]);
         __syncthreads();
+        forget();
         const float2 sS2 = sh.top_s[wave][lane], sN2 = sh.bot_s[wave + 2][lane];
         const float sS[2] = {sS2.x, sS2.y}, sN[2] = {sN2.x, sN2.y};
         float dS[2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) dS[c] = av[0][c] ? es[0][c] - sS[c] : 0.f;
+        for (int c = 0; c < 2; ++c) dS[c] = north(-1, c) ? es[0][c] - sS[c] : 0.f;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 const float esU = r + 1 < R ? es[r + 1 < R ? r + 1 : r][c] : sN[c];
-                const float dN = av[r + 1][c] ? esU - es[r][c] : 0.f;
+                const float dN = north(r, c) ? esU - es[r][c] : 0.f;
                 const float sum = (sx[r][c] + dN) - dS[c];
-                e[r][c] = w[r][c] ? fmaf(k.e4, sum, es[r][c]) : 0.f;
+                e[r][c] = lane_bit(w[r + 1][c]) ? fmaf(k.e4, sum, es[r][c]) : 0.f;
                 dS[c] = dN;
             }
             if (rbase + r >= j0 && rbase + r < j1 && owned) {

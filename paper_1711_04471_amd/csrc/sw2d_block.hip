@@ -45,8 +45,8 @@ hipError_t launch_block(int K, const float* eta, const float* u, const float* v,
     SW2D_BLOCK_CASE(2, kBlockRowsLow)
     SW2D_BLOCK_CASE(3, kBlockRowsLow)
     SW2D_BLOCK_CASE(4, kBlockRowsLow)
-    SW2D_BLOCK_CASE(2, kBlockRowsHigh)
-    SW2D_BLOCK_CASE(3, kBlockRowsHigh)
+    SW2D_BLOCK_CASE(3, kBlockRowsMid)
+    SW2D_BLOCK_CASE(4, kBlockRowsMid)
     SW2D_BLOCK_CASE(4, kBlockRowsHigh)
 #undef SW2D_BLOCK_CASE
     return hipErrorInvalidValue;

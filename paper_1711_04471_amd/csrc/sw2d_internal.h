@@ -98,17 +98,19 @@ inline StepGeometry make_geometry(int nx, int ny, int rows, int strip_out = kStr
 }
 
 // Register tiles (sw2d_block.h): kBlockWaves waves of R rows x 128 columns, K steps per pass.
-// 8 waves: at 16 the barriers of a tile cost more than they share (us per step of the 2048^2
-// basin, K = 4, tiles of 40-48 rows: 10.3 with 8 waves, 16.4 with 16, 11.4 with 4; of the 66^2
-// basin 2.2, 3.3 and 2.3).
+// 8 waves: at 12 or 16 the barriers of a tile cost more than they share (us per step at K = 4,
+// tiles of 40-48 rows: 2048^2 basin 8.4 with 8 waves, 8.6 with 12, 16.4 with 16; 66^2 basin 2.2,
+// 2.4 and 3.3); 4 waves are no faster.
 constexpr int kBlockWaves = 8;
-constexpr int kBlockRowsLow = 3, kBlockRowsHigh = 5;  // rows per wave: tiles of 24 and 40 rows
+constexpr int kBlockRowsLow = 3, kBlockRowsMid = 5, kBlockRowsHigh = 8;  // tiles of 24, 40 and 64 rows
 constexpr int kBlockMaxK = 4;
-// Largest grid stepped by register tiles: 2^23 cells, whose state and depth (28 B per cell and
-// step, 235 MB) the 256 MB Infinity Cache holds. Tiles re-read and recompute their overlap
-// (1.5-2 x at K = 4), which costs little there; from HBM the row pipelines, which overlap less,
-// are faster (us per step, tiles against the better of 1 and 4 steps per pass streamed:
-// 4096 x 2048 17.5 and 19; 8192 x 4096 60 and 54).
+constexpr int kBlockLowTiles = 320;  // most tiles of 24 rows at K >= 3
+// Grids of at most 2^23 cells, whose state and depth (28 B per cell and step, 235 MB) the 256 MB
+// Infinity Cache holds, take up to kBlockMaxK steps per pass whatever the caller's steps per pass:
+// there is no HBM pass to choose. Larger grids take the caller's, over tiles at 4 steps per pass
+// only (us per step on 8192 x 4096, tiles against the row pipelines: K = 1 197 and 192, K = 2 103
+// and 101, K = 3 71 and 71, K = 4 51.7 and 54.3: overlapping tiles re-read and recompute more,
+// which the fewer instructions per cell outweigh at K = 4 alone).
 constexpr int64_t kBlockMaxCells = (int64_t)1 << 23;
 
 struct BlockGeometry {
@@ -130,16 +132,20 @@ inline BlockGeometry make_block_geometry(int nx, int ny, int K, int R) {
     return g;
 }
 
-// The tile height for K steps. A step of a tile takes about 0.9 us at 3 rows per wave and 1.4 at
-// 5 (66^2), but tiles of 24 rows own only 24 - 4K of them: they win while all of them run at
-// once, with little to spare beyond one per CU (us per step at K = 4, 3 and 5 rows per wave:
-// 300 x 221 with 78 and 27 tiles 2.2 and 2.7; 693 x 700 with 602 and 203 tiles 4.1 and 3.0; at
-// K = 3 there, 348 and 150 tiles, 3.6 and 3.4). One step per pass has little overlap and is
-// bound by its loads: 3 rows win at every size (2048^2: 18.7 and 19.4).
+// The tile height for K steps. A step of a tile takes 0.8 us at 3 rows per wave, 1.2 at 5 and 1.8
+// at 8, but a tile of 24, 40 or 64 rows owns 4K rows less. Low tiles win while all of them run at
+// once, with little to spare beyond one per CU (us per step at K = 4, 3 and 5 rows: 300 x 221 with
+// 78 and 27 tiles 1.8 and 2.3; 693 x 700 with 602 and 203 tiles 3.1 and 2.5; K = 3 there, with 348
+// and 150 tiles, 3.0 and 2.9). With many tiles the recomputed overlap decides: at K <= 2 it is
+// small and low tiles, which load with the most waves, stay ahead (2048^2, K = 2: 10.5, 10.9 and
+// 12.1 us per step at 3, 5 and 8 rows); at K = 3 and 4 it is not (2048^2, K = 4: 12.3, 8.4, 9.0;
+// 4096 x 2048: 22.7, 14.2, 14.4), and from HBM the re-read rows add to it (8192 x 4096, K = 4: 88,
+// 57.9, 51.7).
 inline BlockGeometry block_geometry(int nx, int ny, int K) {
     const BlockGeometry low = make_block_geometry(nx, ny, K, kBlockRowsLow);
-    if (K == 1 || low.nblocks <= 320) return low;
-    return make_block_geometry(nx, ny, K, kBlockRowsHigh);
+    if (K <= 2 || low.nblocks <= kBlockLowTiles) return low;
+    const bool cached = (int64_t)nx * ny <= kBlockMaxCells;
+    return make_block_geometry(nx, ny, K, K == 4 && !cached ? kBlockRowsHigh : kBlockRowsMid);
 }
 
 // K = 1..4 steps of the plain model in one pass over register tiles (geometry from
