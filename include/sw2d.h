@@ -246,17 +246,19 @@ const char *sw2d_strerror(int code);
 const char *sw2d_last_hip_error(void);
 
 /* ---------------------------------------------------------------------------------------
- * Batched ensembles: n independent basins of any sizes advanced together by one
- * persistent launch per chunk of steps (a grid barrier between steps), the launch
- * sequence recorded once in a HIP graph and replayed. Each instance runs the same tile
+ * Batched ensembles: n independent basins of any sizes advanced together, by one launch per
+ * pass of up to 4 steps or, where the caller chooses its grid or its deadline, by one
+ * persistent launch per chunk of steps (a grid barrier between passes); the launch sequence
+ * is recorded once in a HIP graph and replayed. Each instance runs the same tile
  * routine as sw2d_step, so its state is bitwise equal to the same basin stepped alone;
  * its folds are equal up to the order of the sums. This is the same time loop
  * (Sect. 6.2) applied to many problems at once; the paper itself runs one grid at a time.
  * ------------------------------------------------------------------------------------ */
 typedef struct sw2d_bctx *sw2d_batch_t;
 
-/* Workspace bytes for n instances with params p[0..n-1] and band heights band_rows
- * (rows per work item, >= 8, one per instance; NULL = 16). 0 if any argument is bad. */
+/* Workspace bytes for n instances with params p[0..n-1] and band heights band_rows (>= 8, one
+ * per instance): their mean picks the height of the ensemble's tiles, 24 rows for bands below
+ * 16, 40 below 48, else 64; NULL leaves it to the library. 0 if any argument is bad. */
 size_t sw2d_batch_workspace_bytes(int32_t n, const sw2d_params *p, const int32_t *band_rows);
 
 /* Validate and bind n instances. Instance i has its own d_H[i], d_mask[i] and d_state[i]
@@ -269,18 +271,18 @@ int sw2d_batch_create(int32_t n, const sw2d_params *p, const float *const *d_H,
                       const uint8_t *const *d_mask, float *const *d_state, const int32_t *band_rows,
                       void *d_work, size_t work_bytes, void *hip_stream, sw2d_batch_t *out);
 
-/* Launch shape: steps per persistent launch (>= 1, default 50), whether sw2d_batch_step
- * records and replays a HIP graph (default 1), and the persistent grid size in
- * workgroups (0 = the most the device holds at once; larger values are rejected so the
- * grid barrier always has every workgroup resident). Drops any recorded graph. */
+/* Launch shape: whether sw2d_batch_step records and replays a HIP graph (default 1), and the
+ * persistent launch: grid = 0 (the default) takes one launch per pass; another value takes
+ * persistent launches of that many workgroups (at most what the device holds at once, larger
+ * values are rejected so the grid barrier always has every workgroup resident; never more
+ * are launched than have work), each of steps_per_launch steps (>= 1, default 50). Drops any
+ * recorded graph. */
 int sw2d_batch_set_launch(sw2d_batch_t b, int32_t steps_per_launch, int32_t use_graph, int32_t grid);
 
-/* Steps per pass of the batched kernel (temporal blocking as sw2d_set_time_blocking): 1
- * (default), 2 or 3. Each member's strips then own 64 - 4K columns and its bands read a
- * 2K-row halo; the grid meets once per pass; the states equal single steps bit for bit and
- * the folds of every step are kept. Afterwards sw2d_batch_step takes multiples of K only.
- * Synchronises the stream, rebuilds the tile list, drops a recorded graph, and lowers the
- * grid to what the K-step kernel keeps resident. SW2D_EINVAL for K outside 1..3. */
+/* Steps that a caller of the batched kernel takes together: 1 (default), 2 or 3. Afterwards
+ * sw2d_batch_step takes multiples of K only. A pass advances up to 4 steps of a launch
+ * whatever K; the states equal single steps bit for bit and the folds of every step are kept.
+ * Drops a recorded graph. SW2D_EINVAL for K outside 1..3. */
 int sw2d_batch_set_time_blocking(sw2d_batch_t b, int32_t steps_per_pass);
 int32_t sw2d_batch_time_blocking(sw2d_batch_t b);
 
@@ -303,12 +305,13 @@ int sw2d_batch_state(sw2d_batch_t b, int32_t k, float **d_eta, float **d_u, floa
 
 int64_t sw2d_batch_steps_done(sw2d_batch_t b);
 
-/* Deadline of one grid-barrier wait (default 2 s, at most 60 s). A wait past it sets the
+/* Deadline of one grid-barrier wait (default 2 s, at most 60 s); selects the persistent launch
+ * until the next sw2d_batch_set_launch. A wait past it sets the
  * error that sw2d_batch_reduce reports and makes every workgroup return; the tests use a
  * zero deadline to exercise that path. Drops any recorded graph. */
 int sw2d_batch_set_barrier_timeout(sw2d_batch_t b, double seconds);
 
-/* Persistent grid size in workgroups (256 threads each). */
+/* Most workgroups (512 threads each) of a persistent launch. */
 int32_t sw2d_batch_grid(sw2d_batch_t b);
 
 /* Release the handle, its graph and its private stream. NULL is accepted. */

@@ -1,18 +1,22 @@
-// sw2d_batch.hip - ensembles of independent 2DSW basins of uneven sizes, advanced by one
-// persistent launch per chunk of steps, with a grid barrier between passes.
+// sw2d_batch.hip - ensembles of independent 2DSW basins of uneven sizes advanced together.
 //
 // A pass advances every member K <= 4 steps over register tiles (sw2d_block.h: the tile routine
 // of the single-grid step, so each instance is bitwise equal to the same basin stepped alone).
-// The tiles of all members, member by member and band by band, form one list; workgroup g of G
-// takes the g-th of G equal runs of it, so its tiles are neighbours (their overlap hits the
-// cache of its XCD) and no list, ticket or descriptor is read: a workgroup looks its first
-// member up once per launch and walks on from there. All tiles cost the same, whatever part of
-// the grid they cover. The grid holds no more workgroups than there are tiles (and folds), so a
-// small ensemble meets at a barrier of few.
+// The tiles of all members, member by member and band by band, form one list; all cost the same,
+// whatever part of the grid they cover. Each writes one fold partial per step; one wave per
+// member and step adds a pass's partials in a fixed order and writes the ring entry while the
+// next pass runs.
 //
-// Per pass: workgroups process tiles and write one fold partial per tile and step, add the
-// partials of the previous pass (one wave per member and step, in a fixed order) and write
-// their folds to the ring, then meet at the barrier.
+// One launch per pass (sw2d_batch_pass_kernel, a workgroup per tile): the hardware hands tiles out
+// as workgroups end and the stream order is the barrier. The launches of a call are recorded as a
+// HIP graph and replayed.
+//
+// One persistent launch per chunk of steps (sw2d_batch_kernel) where the caller asks for it:
+// workgroup g of G takes the g-th of G equal runs of the list and meets the others at a grid
+// barrier after each pass. Measured slower at either end: 12 members of 64-256 cells a side 200 us
+// per 50 steps (the barrier takes longer than a launch) against 100; 256 members of 128-1024, 48
+// steps, 10.6 ms (equal runs end up to a quarter apart, and the loop's state spills scalar
+// registers) against 7.0.
 //
 // The barrier uses no contended atomics: every workgroup publishes the epoch it has
 // reached in its own flag (after an agent-scope release), workgroup 0 waits for all
@@ -243,6 +247,78 @@ __global__ __launch_bounds__(kBatchThreads) void sw2d_batch_kernel(BatchArgs a) 
     }
 }
 
+// One pass of one launch: workgroup b takes tile b (XCD-contiguous); the workgroups beyond the
+// tiles add the previous pass's partials (fold_steps of them, none before the first pass of a
+// call). pass, step: passes and steps of this call made before this pass.
+struct BatchPass {
+    const BatchInst* inst;
+    const int* member;  // of each tile
+    FoldPartial *part, *prev_part;
+    sw2d_red* ring;
+    const BatchControl* ctl;
+    int n_inst, n_tiles, pass, step;
+    int fold_steps, prev_tiles;
+};
+
+// Folds of a pass of K steps in `part`, K any of 1..kBlockMaxK.
+__device__ __forceinline__ void fold_any(int K, BatchArgs a, int first_wave, int nwaves, int lane,
+                                         const FoldPartial* __restrict__ part, long long first_step) {
+    switch (K) {
+        case 1: fold_pass<1>(a, first_wave, nwaves, lane, part, first_step); break;
+        case 2: fold_pass<2>(a, first_wave, nwaves, lane, part, first_step); break;
+        case 3: fold_pass<3>(a, first_wave, nwaves, lane, part, first_step); break;
+        case 4: fold_pass<4>(a, first_wave, nwaves, lane, part, first_step); break;
+    }
+}
+
+__device__ __forceinline__ void fold_prev(const BatchPass& a, int block, int nblocks) {
+    BatchArgs f{};
+    f.inst = a.inst;
+    f.ring = a.ring;
+    f.n_inst = a.n_inst;
+    f.n_tiles = a.prev_tiles;
+    const int wave = uniform(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    fold_any(a.fold_steps, f, block * kBlockWaves + wave, nblocks * kBlockWaves, lane, a.prev_part,
+             a.ctl->steps_done + a.step - a.fold_steps + 1);
+}
+
+template <int K, int R>
+__global__ __launch_bounds__(kBatchThreads) void sw2d_batch_pass_kernel(const BatchInst* __restrict__ inst,
+                                                                        const int* __restrict__ member, BatchPass a) {
+    constexpr int W = kBlockWaves, T = W * R;
+    __shared__ BlockShared<W> sh;
+    __shared__ BlockFoldShared<W> fsh;
+    if ((int)blockIdx.x >= a.n_tiles) {
+        fold_prev(a, blockIdx.x - a.n_tiles, gridDim.x - a.n_tiles);
+        return;
+    }
+    const int t = logical_block(blockIdx.x, a.n_tiles);
+    const BatchInst& in = inst[member[t]];
+    const int cur = (int)((a.ctl->passes_done + a.pass) & 1);
+    const int wave = uniform(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int strips = in.t[K - 1].strips, bands = in.t[K - 1].bands;
+    const int local = t - in.t[K - 1].tile_begin;
+    const int band = local / strips, strip = local - band * strips;
+    const int r0 = band * (T - 4 * K), c0 = strip * (kBlockCols - 4 * K) + 2 * lane;
+    const int j0 = band > 0 ? r0 + 2 * K : 0, j1 = band + 1 < bands ? r0 + T - 2 * K : in.ny;
+    const bool owned = (strip == 0 || lane >= K) && (strip + 1 == strips ? c0 < in.nx : lane < kWave - K);
+    BlockFolds F[K];
+    block_pass<K, R, W>(in.state[cur][0], in.state[cur][1], in.state[cur][2], in.hp, in.state[cur ^ 1][0],
+                        in.state[cur ^ 1][1], in.state[cur ^ 1][2], in.nx, in.ny, r0 + wave * R, wave, lane, c0, owned,
+                        j0, j1, in.k, sh, F);
+    block_fold<K, W>(F, wave, lane, fsh, a.part + t, a.n_tiles);
+}
+
+// After the last pass of a call: its folds, then the step and pass counts.
+__global__ __launch_bounds__(kBatchThreads) void sw2d_batch_fold_kernel(BatchPass a) {
+    fold_prev(a, blockIdx.x, gridDim.x);
+}
+
+__global__ void sw2d_batch_advance_kernel(BatchControl* ctl, int steps, int passes) {
+    ctl->steps_done += steps;
+    ctl->passes_done += passes;
+}
+
 }  // namespace sw2d
 
 // ---------------------------------------------------------------------------------------
@@ -257,6 +333,7 @@ struct sw2d_bctx {
     hipStream_t stream;         // the caller's
     hipStream_t capture;        // private stream used only to record graphs
     BatchInst* d_inst;
+    int* d_member[kBlockMaxK];  // member of each tile at K = 1.. steps per pass
     FoldPartial* d_part;
     sw2d_red* d_ring;
     BatchControl* d_ctl;
@@ -265,6 +342,7 @@ struct sw2d_bctx {
     int tile_rows;            // R, rows per wave
     int max_grid;
     int grid;
+    bool persistent;          // the caller chose the persistent launch
     int steps_per_launch;
     int steps_per_pass;       // the caller's K, 1..kMaxBatchK: step counts are multiples of it
     bool use_graph;
@@ -297,8 +375,9 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct BatchLayout {
     std::vector<size_t> hp;  // per instance
-    size_t flags, scratch, inst, part, ring, ctl, gflags, total;
+    size_t flags, scratch, inst, member, part, ring, ctl, gflags, total;
     int tile_rows;
+    size_t map_tiles;  // tiles at every K together
     int n_tiles[kBlockMaxK];
 };
 
@@ -309,7 +388,6 @@ constexpr int kMaxBatchGrid = 256 * 8;  // flag lines reserved: 8 workgroups on 
 // workgroups of 8 waves per CU, not 4); a grid barrier that waits for a workgroup that never
 // became resident would only end at its deadline.
 constexpr int kBatchWgPerCu = 3;
-
 constexpr int kBatchRows[3] = {kBlockRowsLow, kBlockRowsMid, kBlockRowsHigh};
 constexpr int kBatchHighTiles = 2048;  // fewest tiles of 64 rows chosen without the caller's word
 
@@ -355,6 +433,10 @@ bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLa
     off = align_up(off + kHsumBlocks * sizeof(double));
     L.inst = off;
     off = align_up(off + (size_t)n * sizeof(BatchInst));
+    L.member = off;
+    L.map_tiles = 0;
+    for (int K = 1; K <= kBlockMaxK; ++K) L.map_tiles += (size_t)L.n_tiles[K - 1];
+    off = align_up(off + L.map_tiles * sizeof(int));
     L.part = off;
     off = align_up(off + 2 * (size_t)most * sizeof(FoldPartial));
     L.ring = off;
@@ -386,16 +468,67 @@ BatchKernel batch_kernel(int K, int R) {
                                 : batch_kernel_of<kBlockRowsHigh>(K);
 }
 
+typedef void (*BatchPassKernel)(const BatchInst*, const int*, BatchPass);
+
+template <int R>
+BatchPassKernel batch_pass_kernel_of(int K) {
+    switch (K) {
+        case 1: return sw2d_batch_pass_kernel<1, R>;
+        case 2: return sw2d_batch_pass_kernel<2, R>;
+        case 3: return sw2d_batch_pass_kernel<3, R>;
+        default: return sw2d_batch_pass_kernel<4, R>;
+    }
+}
+
+BatchPassKernel batch_pass_kernel(int K, int R) {
+    return R == kBlockRowsLow   ? batch_pass_kernel_of<kBlockRowsLow>(K)
+           : R == kBlockRowsMid ? batch_pass_kernel_of<kBlockRowsMid>(K)
+                                : batch_pass_kernel_of<kBlockRowsHigh>(K);
+}
+
 // Passes of a chunk of steps: as many of kBlockMaxK steps as it holds, one for the rest.
 int chunk_passes(int32_t steps) { return steps / kBlockMaxK + (steps % kBlockMaxK != 0); }
 
-// Steps per launch chunk: the caller's, rounded down to whole passes of its own K.
-int32_t chunk_steps(const sw2d_bctx* b) {
+// Steps per launch chunk: the caller's, rounded down to whole passes of its own K (all of a call's
+// steps where every pass is a launch).
+int32_t chunk_steps(const sw2d_bctx* b, int32_t nsteps) {
+    if (!b->persistent) return nsteps;
     const int K = b->steps_per_pass;
     return b->steps_per_launch >= K ? b->steps_per_launch / K * K : K;
 }
 
+int enqueue_passes(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
+    BatchPass a{};
+    a.inst = b->d_inst;
+    a.ring = b->d_ring;
+    a.ctl = b->d_ctl;
+    a.n_inst = b->n;
+    size_t most = 0;
+    for (int K = 1; K <= kBlockMaxK; ++K) most = std::max(most, (size_t)K * b->n_tiles[K - 1]);
+    auto fold_blocks = [&]() { return (b->n * a.fold_steps + kBlockWaves - 1) / kBlockWaves; };
+    while (a.step < nsteps) {
+        const int K = nsteps - a.step < kBlockMaxK ? nsteps - a.step : kBlockMaxK;
+        a.member = b->d_member[K - 1];
+        a.n_tiles = b->n_tiles[K - 1];
+        a.part = b->d_part + (a.pass & 1) * most;
+        hipLaunchKernelGGL(batch_pass_kernel(K, b->tile_rows), dim3(a.n_tiles + fold_blocks()), dim3(kBatchThreads), 0, s,
+                           b->d_inst, a.member, a);
+        SW2D_BHIP(hipGetLastError());
+        a.prev_part = a.part;
+        a.prev_tiles = a.n_tiles;
+        a.fold_steps = K;
+        a.step += K;
+        a.pass += 1;
+    }
+    hipLaunchKernelGGL(sw2d_batch_fold_kernel, dim3(fold_blocks()), dim3(kBatchThreads), 0, s, a);
+    SW2D_BHIP(hipGetLastError());
+    hipLaunchKernelGGL(sw2d_batch_advance_kernel, dim3(1), dim3(1), 0, s, b->d_ctl, (int)nsteps, a.pass);
+    SW2D_BHIP(hipGetLastError());
+    return SW2D_OK;
+}
+
 int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
+    if (!b->persistent) return enqueue_passes(b, nsteps, s);
     BatchArgs a;
     a.inst = b->d_inst;
     a.part = b->d_part;
@@ -404,7 +537,7 @@ int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
     a.flags = b->d_flags;
     a.n_inst = b->n;
     a.timeout_ticks = b->timeout_ticks;
-    const int32_t per_launch = chunk_steps(b);
+    const int32_t per_launch = chunk_steps(b, nsteps);
     for (int32_t done = 0; done < nsteps;) {
         const int32_t chunk = nsteps - done < per_launch ? nsteps - done : per_launch;
         const int32_t rest = chunk % kBlockMaxK;
@@ -481,6 +614,7 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
     b->graph = nullptr;
     b->exec = nullptr;
     b->graph_n = -1;
+    b->persistent = false;
     b->steps_per_launch = 50;
     b->use_graph = true;
     b->steps_done = 0;
@@ -488,6 +622,11 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
     b->tile_rows = L.tile_rows;
     char* w = static_cast<char*>(d_work);
     b->d_inst = reinterpret_cast<BatchInst*>(w + L.inst);
+    int* map = reinterpret_cast<int*>(w + L.member);
+    for (int K = 1; K <= kBlockMaxK; ++K) {
+        b->d_member[K - 1] = map;
+        map += L.n_tiles[K - 1];
+    }
     b->d_flags = reinterpret_cast<unsigned long long*>(w + L.gflags);
     b->d_part = reinterpret_cast<FoldPartial*>(w + L.part);
     b->d_ring = reinterpret_cast<sw2d_red*>(w + L.ring);
@@ -543,12 +682,18 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
             tile_begin[K - 1] += g.nblocks;
         }
     }
+    std::vector<int> member;
+    member.reserve(L.map_tiles);
+    for (int K = 1; K <= kBlockMaxK; ++K)
+        for (int i = 0; i < n; ++i) member.insert(member.end(), (size_t)inst[i].t[K - 1].strips * inst[i].t[K - 1].bands, i);
     b->steps_per_pass = 1;
     b->passes_done = 0;
     BatchControl ctl;
     std::memset(&ctl, 0, sizeof ctl);
     std::vector<unsigned long long> zero_flags((size_t)kMaxBatchGrid * kFlagStride, 0ull);
     e = hipMemcpyAsync(b->d_inst, inst.data(), n * sizeof(BatchInst), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->d_member[0], member.data(), member.size() * sizeof(int), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(b->d_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_flags, zero_flags.data(), zero_flags.size() * sizeof(unsigned long long),
@@ -588,6 +733,7 @@ int sw2d_batch_set_launch(sw2d_batch_t b, int32_t steps_per_launch, int32_t use_
     if (steps_per_launch < 1 || grid < 0) return SW2D_EINVAL;
     if (grid > b->max_grid) return SW2D_EINVAL;  // must stay co-resident
     b->grid = grid > 0 ? grid : b->max_grid;
+    b->persistent = grid > 0;
     b->steps_per_launch = steps_per_launch;
     b->use_graph = use_graph != 0;
     drop_graph(b);
@@ -624,7 +770,7 @@ int sw2d_batch_step(sw2d_batch_t b, int32_t nsteps) {
         SW2D_BHIP(hipGraphLaunch(b->exec, b->stream));
     }
     b->steps_done += nsteps;
-    const int32_t per_launch = chunk_steps(b);
+    const int32_t per_launch = chunk_steps(b, nsteps);
     b->passes_done += (int64_t)(nsteps / per_launch) * chunk_passes(per_launch) + chunk_passes(nsteps % per_launch);
     return SW2D_OK;
 }
@@ -697,6 +843,7 @@ int sw2d_batch_set_barrier_timeout(sw2d_batch_t b, double seconds) {
     SW2D_BHIP(hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev));
     if (clock_khz <= 0) clock_khz = 100000;
     b->timeout_ticks = (unsigned long long)(seconds * clock_khz * 1000.0);
+    b->persistent = true;  // only a persistent launch has a barrier to wait at
     drop_graph(b);
     return SW2D_OK;
 }

@@ -203,3 +203,28 @@ def test_switching_steps_per_pass_mid_run():
         e, u, v, _ = gpu_run(c, nsteps=21, k=1)
         for g, s in zip(states[k], (e, u, v)):
             assert np.array_equal(g, s), k
+
+
+@pytest.mark.parametrize("rows", [8, 24, 64])
+def test_launch_per_pass_equals_persistent_launch(rows):
+    """One launch per pass (the default) against persistent launches of a chosen grid. Same states and folds, at step counts that leave every
+    remainder of the 4 steps of a pass, through graph replays, and equal to single runs. (24-row
+    tiles for 8-row bands, 40 for 24, 64 for 64.)"""
+    shapes = {8: [(701, 523)] * 3 + [(129, 65), (400, 301)], 24: [(1500, 1300)] * 2 + [(701, 523), (129, 65)],
+              64: [(1500, 1301)] * 4 + [(701, 523), (129, 65)]}[rows]
+    cases = [inputs.small_basin(nx, ny, seed=70 + k, n_bumps=2) for k, (nx, ny) in enumerate(shapes)]
+    got = []
+    for grid in (0, 200):
+        with Sw2dBatch(cases, band_rows=[rows] * len(cases)) as b:
+            b.set_launch(steps_per_launch=50, use_graph=True, grid=grid)
+            reds = []
+            for n in (1, 7, 7, 6, 4):
+                b.step(n)
+                reds.append(b.reduce())
+            got.append(([b.state_numpy(k) for k in range(b.n)], reds))
+    for k, c in enumerate(cases):
+        e, u, v, _ = gpu_run(c, nsteps=25, k=1)
+        for x, y, z in zip(got[0][0][k], got[1][0][k], (e, u, v)):
+            assert np.array_equal(x, y) and np.array_equal(x, z), (rows, k)
+    for x, y in zip(got[0][1], got[1][1]):
+        assert np.array_equal(x, y)
