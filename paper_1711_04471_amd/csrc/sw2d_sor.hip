@@ -13,7 +13,10 @@
 // f, and writes its own array - 16 B per cell and iteration, no half-used cache lines. The
 // split and the merge back to [nz][ny][nx] are one pass each per solve. A sweep thread owns one
 // position of its colour per plane (threads run along the rows of a plane, so they coalesce
-// across row ends) and walks kSorPlanes planes. The residual r = f - L p of
+// across row ends) and takes 1 or 4 planes, all of its loads issued before the first is used
+// (walked one after another, 8 planes cost 8 load latencies: a sweep of 65 x 47 x 33 took 7.2 us
+// instead of 2.7, one of 300 x 300 x 90 13.5 us instead of 11.5; its 65 MB take 7.8 us at the
+// rate of a large copy inside the cache). The residual r = f - L p of
 // the state after iteration m is folded without an extra pass: a black cell's neighbours
 // are all red, so the black sweep of iteration m knows its residual right after the update;
 // a red cell's residual needs the black values of iteration m, which the red sweep of
@@ -31,13 +34,7 @@
 namespace sw2d {
 namespace {
 
-#ifndef SW2D_SOR_PLANES
-#define SW2D_SOR_PLANES 8
-#endif
-#ifndef SW2D_SOR_THREADS
-#define SW2D_SOR_THREADS 512
-#endif
-constexpr int kSorThreads = SW2D_SOR_THREADS, kSorPlanes = SW2D_SOR_PLANES;
+constexpr int kSorThreads = 256;
 constexpr int kSorFoldThreads = 256;
 enum SorMode { kSorUpdate = 0, kSorResidualOnly = 1 };
 
@@ -52,8 +49,23 @@ struct alignas(16) SorPartial {
 };
 
 struct SorGeometry {
-    int nx, ny, nz, w, rows_q, gx, gz, nblocks;  // w = ceil(nx / 2); rows_q = (ny - 2) w
+    int nx, ny, nz, w, rows_q, planes, gx, gz, nblocks;  // w = ceil(nx / 2); rows_q = (ny - 2) w
 };
+
+// Planes per thread of a sweep. A thread's loads are all in flight at once, so a sweep of a small
+// grid costs a launch and one load latency, least with its cells spread over the device; a larger
+// one is bound by the cache's rate and its requests, and walking planes reads a z neighbour once
+// for the three cells that use it (us per 50-iteration solve at 1, 2, 4 and 8 planes: 65 x 47 x 33
+// 278, 370, 344, 418; 40 x 300 x 20 (107,000 positions) 292, 335, 368, 431; 128 x 128 x 64 (500,000)
+// 421, 417, 403, 456; 300 x 300 x 90 1699, 1400, 1238, 1211).
+constexpr int sor_planes(int64_t positions) { return positions < (1 << 18) ? 1 : 4; }
+
+// Tile b of n in an order that gives each XCD (workgroup b runs on XCD b % 8) a contiguous range.
+__device__ __forceinline__ int sor_tile(int b, int n) {
+    const int x = b % kXcds;
+    return x * (n / kXcds) + min(x, n % kXcds) + b / kXcds;
+}
+
 
 SorGeometry sor_geometry(int nx, int ny, int nz) {
     SorGeometry g;
@@ -62,105 +74,158 @@ SorGeometry sor_geometry(int nx, int ny, int nz) {
     g.nz = nz;
     g.w = (nx + 1) / 2;
     g.rows_q = (ny - 2) * g.w;
+    g.planes = sor_planes((int64_t)g.rows_q * (nz - 2));
     g.gx = (g.rows_q + kSorThreads - 1) / kSorThreads;
-    g.gz = (nz - 2 + kSorPlanes - 1) / kSorPlanes;
+    g.gz = (nz - 2 + g.planes - 1) / g.planes;
     g.nblocks = g.gx * g.gz;
     return g;
 }
 
-// [nz][ny][nx] -> the two colour arrays (dir = 0), or back (dir = 1)
-__global__ __launch_bounds__(256) void sor_split_kernel(float* __restrict__ nat, float* __restrict__ red,
-                                                        float* __restrict__ black, SorGeometry g, int dir) {
-    const size_t n = (size_t)g.nx * g.ny * g.nz;
-    for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < n; q += (size_t)gridDim.x * 256) {
-        const int i = (int)(q % g.nx);
-        const size_t jk = q / g.nx;  // = k ny + j
-        const int j = (int)(jk % g.ny), k = (int)(jk / g.ny);
-        float* arr = ((i + j + k) & 1) ? black : red;
-        const size_t o = jk * g.w + (i >> 1);
-        if (dir == 0)
-            arr[o] = nat[q];
-        else
-            nat[q] = arr[o];
+// Sum (FP64) and magnitude maximum over a workgroup of N threads in a fixed order, written by
+// thread 0: half waves and 16-lane rows exchanged, four levels within the rows, the waves in order.
+// The maximum is of the bits, so a NaN stays the largest.
+template <int kCtrl>
+__device__ __forceinline__ void sor_row_level(double& sum, unsigned& mx) {
+    const unsigned long long b = __double_as_longlong(sum);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, kCtrl, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), kCtrl, 0xf, 0xf, true);
+    sum += __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    mx = max(mx, (unsigned)__builtin_amdgcn_mov_dpp((int)mx, kCtrl, 0xf, 0xf, true));
+}
+
+template <int N>
+__device__ __forceinline__ void sor_fold_group(double sum, unsigned mx, SorPartial* out) {
+    __shared__ double s_sum[N / kWave];
+    __shared__ unsigned s_max[N / kWave];
+    for (int off = kWave / 2; off >= 16; off >>= 1) {
+        sum += __shfl_xor(sum, off, kWave);
+        mx = max(mx, (unsigned)__shfl_xor((int)mx, off, kWave));
+    }
+    sor_row_level<0xB1>(sum, mx);   // quad_perm [1, 0, 3, 2]
+    sor_row_level<0x4E>(sum, mx);   // quad_perm [2, 3, 0, 1]
+    sor_row_level<0x141>(sum, mx);  // row_half_mirror
+    sor_row_level<0x140>(sum, mx);  // row_mirror
+    __syncthreads();                // an earlier fold's values have been read
+    if (threadIdx.x % kWave == 0) {
+        s_sum[threadIdx.x / kWave] = sum;
+        s_max[threadIdx.x / kWave] = mx;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = s_sum[0];
+        unsigned m = s_max[0];
+#pragma unroll
+        for (int i = 1; i < N / kWave; ++i) {
+            t += s_sum[i];
+            m = max(m, s_max[i]);
+        }
+        *out = SorPartial{t, m, 0u};
     }
 }
 
-template <int COLOR, int MODE>
+// [nz][ny][nx] -> the two colour arrays, for p (and f beside it, into f_red, f_black; a second
+// pair takes p as well where given), a position (two adjacent cells) per thread.
+__global__ __launch_bounds__(256) void sor_split_kernel(const float* __restrict__ p, const float* __restrict__ f,
+                                                        float* __restrict__ red, float* __restrict__ black,
+                                                        float* __restrict__ f_red, float* __restrict__ f_black,
+                                                        float* __restrict__ red2, float* __restrict__ black2,
+                                                        SorGeometry g) {
+    const int per = (g.ny * g.w + 255) / 256;  // workgroups per plane
+    const int k = blockIdx.x / per, q = (blockIdx.x - k * per) * 256 + threadIdx.x;
+    if (q >= g.ny * g.w) return;
+    const int j = q / g.w, m = q - j * g.w;
+    const size_t row = (size_t)k * g.ny + j;
+    const size_t o = row * g.w + m, n = row * g.nx + 2 * m;
+    const bool both = 2 * m + 1 < g.nx, odd = ((j + k) & 1) != 0;  // odd: the first cell is black
+    const float p0 = p[n], p1 = both ? p[n + 1] : 0.f;
+    const float f0 = f[n], f1 = both ? f[n + 1] : 0.f;
+    if (both || !odd) {
+        red[o] = odd ? p1 : p0;
+        f_red[o] = odd ? f1 : f0;
+        if (red2) red2[o] = odd ? p1 : p0;
+    }
+    if (both || odd) {
+        black[o] = odd ? p0 : p1;
+        f_black[o] = odd ? f0 : f1;
+        if (black2) black2[o] = odd ? p0 : p1;
+    }
+}
+
+// The colour arrays back into p.
+__global__ __launch_bounds__(256) void sor_merge_kernel(float* __restrict__ p, const float* __restrict__ red,
+                                                        const float* __restrict__ black, SorGeometry g) {
+    const int per = (g.ny * g.w + 255) / 256;  // workgroups per plane
+    const int k = blockIdx.x / per, q = (blockIdx.x - k * per) * 256 + threadIdx.x;
+    if (q >= g.ny * g.w) return;
+    const int j = q / g.w, m = q - j * g.w;
+    const size_t row = (size_t)k * g.ny + j;
+    const size_t o = row * g.w + m, n = row * g.nx + 2 * m;
+    const bool both = 2 * m + 1 < g.nx, odd = ((j + k) & 1) != 0;
+    if (both || !odd) p[n + (odd ? 1 : 0)] = red[o];
+    if (both || odd) p[n + (odd ? 0 : 1)] = black[o];
+}
+
+// One colour's sweep (or its residual alone). A thread owns position m of a row in P successive
+// planes: its z neighbours are the other colour's values at m one plane down and up, and one of
+// its x neighbours is the value at m itself, so P planes load P + 2 of those, and the outer x
+// neighbour, two y neighbours, p and f of each. Every load is issued before the first is used.
+template <int COLOR, int MODE, int P>
 __global__ __launch_bounds__(kSorThreads) void sor_sweep_kernel(float* __restrict__ own,
                                                                 const float* __restrict__ other,
                                                                 const float* __restrict__ f_own, SorGeometry geo,
                                                                 SorCoef c, SorPartial* __restrict__ part) {
 #pragma clang fp contract(off)
-    __shared__ double s_sum[kSorThreads];
-    __shared__ unsigned s_max[kSorThreads];
     const int nx = geo.nx, ny = geo.ny, nz = geo.nz, w = geo.w;
-    const int q = blockIdx.x * kSorThreads + threadIdx.x;
-    const int jj = q / w;
-    const int m = q - jj * w;
-    const int j = 1 + jj;
+    const int tile = sor_tile(blockIdx.x, geo.nblocks);
+    const int bz = tile / geo.gx, bx = tile - bz * geo.gx;
+    const int q = bx * kSorThreads + threadIdx.x;
     const bool row_ok = q < geo.rows_q;
-    const int k0 = 1 + blockIdx.y * kSorPlanes;
+    const int qc = row_ok ? q : 0;
+    const int jj = qc / w;
+    const int m = qc - jj * w;
+    const int j = 1 + jj;
+    const int k0 = 1 + bz * P;
+    const int planes = min(P, nz - 1 - k0);  // this workgroup's, 1..P
     const size_t plane = (size_t)ny * w;
+    const size_t o0 = ((size_t)k0 * ny + j) * w + m;
+    float z[P + 2], xo[P], yn[P], ys[P], pc[P], fc[P];
+#pragma unroll
+    for (int kk = 0; kk < P + 2; ++kk) z[kk] = other[o0 - plane + (size_t)min(kk, planes + 1) * plane];
+#pragma unroll
+    for (int kk = 0; kk < P; ++kk) {
+        const size_t o = o0 + (size_t)min(kk, planes - 1) * plane;
+        const int s = (COLOR + j + k0 + kk) & 1;  // i = s + 2 m has the sweep's colour
+        xo[kk] = other[s ? o + 1 : o - 1];        // the outer x neighbour
+        yn[kk] = other[o + w];
+        ys[kk] = other[o - w];
+        pc[kk] = own[o];
+        fc[kk] = f_own[o];
+    }
     double acc = 0.0;
     unsigned mx = 0u;
-    // The thread walks the planes at one position m of the other colour's array: its z
-    // neighbours are that array's values at m one plane down and up, and one of its x
-    // neighbours in a plane is the value at m itself, so each plane loads the upper z value
-    // and the outer x value only and passes the rest on.
-    const size_t o_m0 = ((size_t)k0 * ny + (row_ok ? j : 1)) * w + m;
-    float zd = 0.f, xm = 0.f;
-    if (row_ok && k0 <= nz - 2) {
-        zd = other[o_m0 - plane];
-        xm = other[o_m0];
-    }
-    for (int kk = 0; kk < kSorPlanes; ++kk) {
-        const int k = k0 + kk;
-        if (k > nz - 2 || !row_ok) break;
-        const size_t o = o_m0 + (size_t)kk * plane;
-        const float zu = other[o + plane];
-        const int s = (COLOR + j + k) & 1;  // i = s + 2 m has the sweep's colour
+#pragma unroll
+    for (int kk = 0; kk < P; ++kk) {
+        const int s = (COLOR + j + k0 + kk) & 1;
         const int i = s + 2 * m;
-        if (i >= 1 && i <= nx - 2) {
-            const float xo = s ? other[o + 1] : other[o - 1];  // the outer x neighbour
-            const float pE = s ? xo : xm, pW = s ? xm : xo;
-            const float pc = own[o];
-            const float fc = f_own[o];
-            const float sx = pE + pW;
-            const float sy = other[o + w] + other[o - w];
-            const float sz = zu + zd;
-            const float nb = fmaf(c.cz, sz, fmaf(c.cy, sy, c.cx * sx));
-            float r = 0.f;
-            if constexpr (MODE == kSorResidualOnly || COLOR == 0) r = fc - fmaf(-c.diag, pc, nb);
-            if constexpr (MODE == kSorUpdate) {
-                const float g = (nb - fc) * c.inv_diag;
-                const float pn = fmaf(c.omega, g - pc, pc);
-                own[o] = pn;
-                if constexpr (COLOR == 1) r = fc - fmaf(-c.diag, pn, nb);
-            }
-            acc += (double)r * (double)r;
-            mx = max(mx, __float_as_uint(r) & 0x7fffffffu);
+        const float pE = s ? xo[kk] : z[kk + 1], pW = s ? z[kk + 1] : xo[kk];
+        const float sx = pE + pW;
+        const float sy = yn[kk] + ys[kk];
+        const float sz = z[kk + 2] + z[kk];
+        const float nb = fmaf(c.cz, sz, fmaf(c.cy, sy, c.cx * sx));
+        const bool live = row_ok && kk < planes && i >= 1 && i <= nx - 2;
+        float r = 0.f;
+        if constexpr (MODE == kSorResidualOnly || COLOR == 0) r = fc[kk] - fmaf(-c.diag, pc[kk], nb);
+        if constexpr (MODE == kSorUpdate) {
+            const float g = (nb - fc[kk]) * c.inv_diag;
+            const float pn = fmaf(c.omega, g - pc[kk], pc[kk]);
+            if (live) own[o0 + (size_t)kk * plane] = pn;
+            if constexpr (COLOR == 1) r = fc[kk] - fmaf(-c.diag, pn, nb);
         }
-        zd = xm;
-        xm = zu;
+        r = live ? r : 0.f;
+        acc += (double)r * (double)r;
+        mx = max(mx, __float_as_uint(r) & 0x7fffffffu);
     }
-    // fixed-order tree over the workgroup
-    const int t = threadIdx.x;
-    s_sum[t] = acc;
-    s_max[t] = mx;
-    __syncthreads();
-    for (int h = kSorThreads / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            s_sum[t] += s_sum[t + h];
-            s_max[t] = max(s_max[t], s_max[t + h]);
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        const int b = blockIdx.y * gridDim.x + blockIdx.x;
-        part[b].sum_r2 = s_sum[0];
-        part[b].max_bits = s_max[0];
-        part[b].pad = 0u;
-    }
+    sor_fold_group<kSorThreads>(acc, mx, part + tile);
 }
 
 // Residual of state m = red partials of slot m + black partials of slot m, each added in
@@ -233,8 +298,6 @@ __global__ __launch_bounds__(kFuThreads) void sor_iter_kernel(const float* __res
                                                               SorPartial* __restrict__ black_part) {
 #pragma clang fp contract(off)
     __shared__ float s_red[3][kFuHalo];
-    __shared__ double s_sum[kFuThreads];
-    __shared__ unsigned s_max[kFuThreads];
     const int nx = g.nx, ny = g.ny, nz = g.nz, w = g.w;
     const size_t plane = (size_t)ny * w;
     const int b = blockIdx.x;
@@ -330,26 +393,8 @@ __global__ __launch_bounds__(kFuThreads) void sor_iter_kernel(const float* __res
         black_plane(k);
     }
 
-    // fixed-order trees: red residual (previous state) and black residual (new state)
-    for (int pass = 0; pass < 2; ++pass) {
-        __syncthreads();
-        s_sum[t] = pass ? acc_b : acc_r;
-        s_max[t] = pass ? mx_b : mx_r;
-        __syncthreads();
-        for (int hh = kFuThreads / 2; hh > 0; hh >>= 1) {
-            if (t < hh) {
-                s_sum[t] += s_sum[t + hh];
-                s_max[t] = max(s_max[t], s_max[t + hh]);
-            }
-            __syncthreads();
-        }
-        if (t == 0) {
-            SorPartial* q = (pass ? black_part : red_part) + b;
-            q->sum_r2 = s_sum[0];
-            q->max_bits = s_max[0];
-            q->pad = 0u;
-        }
-    }
+    sor_fold_group<kFuThreads>(acc_r, mx_r, red_part + b);    // residual of the previous state
+    sor_fold_group<kFuThreads>(acc_b, mx_b, black_part + b);  // of the new one
 }
 
 __global__ __launch_bounds__(256) void sor_zero_kernel(SorPartial* __restrict__ p, size_t n) {
@@ -378,16 +423,24 @@ bool sor_params_ok(const sw2d_sor_params* p) {
 template <int COLOR, int MODE>
 hipError_t launch_sweep(float* own, const float* other, const float* f_own, const SorGeometry& g, const SorCoef& c,
                         SorPartial* part, hipStream_t s) {
-    hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE>), dim3(g.gx, g.gz), dim3(kSorThreads), 0, s, own, other, f_own,
-                       g, c, part);
+    const dim3 grid(g.nblocks), block(kSorThreads);
+    if (g.planes == 1)
+        hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE, 1>), grid, block, 0, s, own, other, f_own, g, c, part);
+    else
+        hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE, 4>), grid, block, 0, s, own, other, f_own, g, c, part);
     return hipGetLastError();
 }
 
-hipError_t launch_split(float* nat, float* red, float* black, const SorGeometry& g, int dir, hipStream_t s) {
-    const size_t n = (size_t)g.nx * g.ny * g.nz;
-    size_t blocks = (n + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(sor_split_kernel, dim3((unsigned)blocks), dim3(256), 0, s, nat, red, black, g, dir);
+dim3 split_grid(const SorGeometry& g) { return dim3((unsigned)((g.ny * g.w + 255) / 256) * g.nz); }
+
+hipError_t launch_split(const float* p, const float* f, float* red, float* black, float* f_red, float* f_black,
+                        float* red2, float* black2, const SorGeometry& g, hipStream_t s) {
+    hipLaunchKernelGGL(sor_split_kernel, split_grid(g), dim3(256), 0, s, p, f, red, black, f_red, f_black, red2, black2, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_merge(float* p, const float* red, const float* black, const SorGeometry& g, hipStream_t s) {
+    hipLaunchKernelGGL(sor_merge_kernel, split_grid(g), dim3(256), 0, s, p, red, black, g);
     return hipGetLastError();
 }
 
@@ -449,9 +502,7 @@ int sw2d_sor_run(const sw2d_sor_params* p, float* d_p, const float* d_f, int32_t
                            red, nparts);
         hipError_t e = hipGetLastError();
         // both pairs start as the split state: the boundary layer is never written again
-        if (e == hipSuccess) e = launch_split(d_p, R, B, g, 0, s);
-        if (e == hipSuccess) e = launch_split(d_p, R2, B2, g, 0, s);
-        if (e == hipSuccess) e = launch_split(const_cast<float*>(d_f), FR, FB, g, 0, s);  // read only (dir 0)
+        if (e == hipSuccess) e = launch_split(d_p, d_f, R, B, FR, FB, R2, B2, g, s);
         if (e == hipSuccess) e = launch_sweep<1, kSorResidualOnly>(B, R, FB, g, c, black, s);  // black part of state 0
         for (int32_t n = 0; n < iters && e == hipSuccess; ++n) {
             hipLaunchKernelGGL(sor_iter_kernel, dim3(fg.nblocks), dim3(kFuThreads), 0, s, R, B, FR, FB, R2, B2, g, fg,
@@ -461,7 +512,7 @@ int sw2d_sor_run(const sw2d_sor_params* p, float* d_p, const float* d_f, int32_t
             std::swap(B, B2);
         }
         if (e == hipSuccess) e = launch_sweep<0, kSorResidualOnly>(R, B, FR, g, c, red + (size_t)iters * stride, s);
-        if (e == hipSuccess) e = launch_split(d_p, R, B, g, 1, s);
+        if (e == hipSuccess) e = launch_merge(d_p, R, B, g, s);
         if (e == hipSuccess && d_res) {
             hipLaunchKernelGGL(sor_fold_kernel, dim3(iters + 1), dim3(kSorFoldThreads), 0, s, red, black, stride, d_res);
             e = hipGetLastError();
@@ -470,15 +521,14 @@ int sw2d_sor_run(const sw2d_sor_params* p, float* d_p, const float* d_f, int32_t
     }
     auto* red = reinterpret_cast<SorPartial*>(base + 4 * arr);
     SorPartial* black = red + (size_t)(iters + 1) * g.nblocks;
-    hipError_t e = launch_split(d_p, R, B, g, 0, s);
-    if (e == hipSuccess) e = launch_split(const_cast<float*>(d_f), FR, FB, g, 0, s);  // read only (dir 0)
+    hipError_t e = launch_split(d_p, d_f, R, B, FR, FB, nullptr, nullptr, g, s);
     if (e == hipSuccess) e = launch_sweep<1, kSorResidualOnly>(B, R, FB, g, c, black, s);  // black part of state 0
     for (int32_t n = 0; n < iters && e == hipSuccess; ++n) {
         e = launch_sweep<0, kSorUpdate>(R, B, FR, g, c, red + (size_t)n * g.nblocks, s);
         if (e == hipSuccess) e = launch_sweep<1, kSorUpdate>(B, R, FB, g, c, black + (size_t)(n + 1) * g.nblocks, s);
     }
     if (e == hipSuccess) e = launch_sweep<0, kSorResidualOnly>(R, B, FR, g, c, red + (size_t)iters * g.nblocks, s);
-    if (e == hipSuccess) e = launch_split(d_p, R, B, g, 1, s);
+    if (e == hipSuccess) e = launch_merge(d_p, R, B, g, s);
     if (e == hipSuccess && d_res) {
         hipLaunchKernelGGL(sor_fold_kernel, dim3(iters + 1), dim3(kSorFoldThreads), 0, s, red, black, g.nblocks,
                            d_res);

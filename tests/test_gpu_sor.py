@@ -123,3 +123,14 @@ def test_one_pass_iteration_poisson_300():
     assert np.array_equal(a, b)
     assert np.array_equal(ra["max_abs_r"], rb["max_abs_r"])
     np.testing.assert_allclose(rb["sum_r2"], ra["sum_r2"], rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("shape", [(35, 131, 131), (36, 131, 130), (37, 129, 131), (70, 70, 130), (3, 70, 600), (131, 3, 40), (40, 3, 3)])
+def test_sweep_shapes_match_oracle(shape):
+    """Both plane counts of a sweep thread (1 below 2^18 positions of a colour, 4 from there) at
+    interiors that leave every remainder of 4 planes and of 256 positions, odd and even widths,
+    one row and one plane."""
+    c = _random_case(shape, seed=sum(shape), omega=1.5, iters=4)
+    _say(f"sor sweeps {shape}")
+    p, res = _gpu(c)
+    _check(c, p, res, c.iters)
