@@ -340,11 +340,10 @@ struct FuRegion {
 // buffer A holds layer 1's map, then layer 3's; buffer B the packed input, then layer 2's map
 constexpr int kFuBufA = FuRegion<1>::kBytes;
 constexpr int kFuBufB = FuRegion<0>::kBytes > FuRegion<2>::kBytes ? FuRegion<0>::kBytes : FuRegion<2>::kBytes;
-static_assert(FuRegion<3>::kBytes <= kFuBufA, "layer 3 map in buffer A");
+static_assert(FuRegion<3>::kBytes + 9 * 32 * 16 * 2 <= kFuBufA, "layer 3 map and layer 1 weights in buffer A");
 constexpr int kFuWSlot = 9 * 32 * 32 * 2;  // one layer's BF16 weights (the widest)
 constexpr int kFuBiasBytes = 4 * 32 * 4;
 constexpr int kFuLds = kFuBufA + kFuBufB + 2 * kFuWSlot + kFuBiasBytes;
-constexpr int kFuWPer = (kFuWSlot / 16 + kFuThreads - 1) / kFuThreads;  // 16 B weight chunks per thread
 constexpr int kFuRawPer = (FuRegion<0>::kPix + kFuThreads - 1) / kFuThreads;  // input pixels per thread
 
 typedef short i16x2 __attribute__((ext_vector_type(2)));
@@ -366,75 +365,120 @@ __device__ __forceinline__ f32x16 bias_pattern(const float* __restrict__ bias, i
     return b;
 }
 
-// One layer over its region: input map in_lds (region L - 1), output map out_lds (region L),
-// or, for the last layer, channels 0..2 to the FP32 planes out_f [3][H][W]. bias: the layer's
-// 32 biases in LDS; a lane's output channels start from theirs. A block's B
-// operands (all taps and channel chunks) are read from LDS before its first product, so the
-// reads overlap the products instead of waiting one by one.
-template <int L, int KIN, bool kLast>
-__device__ __forceinline__ void fused_layer(const unsigned char* __restrict__ in_lds, unsigned char* __restrict__ out_lds,
-                                            const bf16x8 (&a)[9][2], const float* __restrict__ bias, float* __restrict__ out_f,
-                                            int y0, int x0, int H, int W, int wave, int half, int j) {
-    using In = FuRegion<L - 1>;
+// Output of a block row: pixel (ry, rx) of the region, channels 8 q + 4 half + (0..3) of this lane.
+template <int L, bool kLast>
+__device__ __forceinline__ void fused_store(const f32x16& acc, unsigned char* __restrict__ out_lds,
+                                            float* __restrict__ out_f, int ry, int rx, bool valid, int y0, int x0,
+                                            int H, int W, int half) {
     using Out = FuRegion<L>;
-    constexpr int kK = KIN / 16;
-    constexpr int kBlocks = (Out::kPix + 31) / 32;
-    const int oy = y0 - Out::kHalo, ox = x0 - Out::kHalo;  // image coordinates of the region's first pixel
-    for (int blk = wave; blk < kBlocks; blk += kFuWaves) {
-        const int P = blk * 32 + j;
-        const bool valid = P < Out::kPix;
-        const int Pc = valid ? P : Out::kPix - 1;  // the last block's spare lanes read a real pixel
-        const int ry = Pc / Out::kCols, rx = Pc - ry * Out::kCols;
-        const unsigned char* base = in_lds + (ry * In::kCols + rx) * In::kStride + half * 16;
-        bf16x8 bv[9][kK];
+    const int gy = y0 - Out::kHalo + ry, gx = x0 - Out::kHalo + rx;
+    const bool inside = valid && gy >= 0 && gy < H && gx >= 0 && gx < W;
+    if constexpr (!kLast) {
+        // A lane has 4 of every 8 channels; exchanging halves of the wave gives each lane all 8 of
+        // every second group (half h: groups h and 2 + h), written 16 B at a time.
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int ky = t / 3, kx = t - 3 * (t / 3);
+        for (int q = 0; q < 4; q += 2) {
+            unsigned w[2][2];
 #pragma unroll
-            for (int kc = 0; kc < kK; ++kc)
-                bv[t][kc] = *reinterpret_cast<const bf16x8*>(base + (ky * In::kCols + kx) * In::kStride + kc * 32);
+            for (int i = 0; i < 2; ++i) {
+                unsigned x = relu_bf2(f2bf2(acc[4 * q + 2 * i], acc[4 * q + 2 * i + 1]));
+                unsigned y = relu_bf2(f2bf2(acc[4 * q + 4 + 2 * i], acc[4 * q + 4 + 2 * i + 1]));
+                const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+                w[0][i] = r[0];
+                w[1][i] = r[1];
+            }
+            uint4 o = make_uint4(w[0][0], w[0][1], w[1][0], w[1][1]);
+            if (!inside) o = make_uint4(0u, 0u, 0u, 0u);
+            if (valid)
+                *reinterpret_cast<uint4*>(out_lds + (ry * Out::kCols + rx) * Out::kStride + (q + half) * 16) = o;
         }
-        f32x16 acc = bias_pattern(bias, half);
+    } else {
+        if (inside && half == 0) {
 #pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int kc = 0; kc < kK; ++kc) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][kc], bv[t][kc], acc, 0, 0, 0);
-        // the scheduler is told to issue the block's LDS reads before its products
-        __builtin_amdgcn_sched_group_barrier(0x100, 9 * kK, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 9 * kK, 0);
-        const int gy = oy + ry, gx = ox + rx;
-        const bool inside = valid && gy >= 0 && gy < H && gx >= 0 && gx < W;
-        if constexpr (!kLast) {
-            // lane holds pixel P, output channels n = 8 q + 4 half + (0..3)
-            if (valid) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n0 = 8 * q + 4 * half;
-                    uint2 w;
-                    w.x = relu_bf2(f2bf2(acc[4 * q + 0], acc[4 * q + 1]));
-                    w.y = relu_bf2(f2bf2(acc[4 * q + 2], acc[4 * q + 3]));
-                    if (!inside) w = make_uint2(0u, 0u);
-                    *reinterpret_cast<uint2*>(out_lds + P * Out::kStride + n0 * 2) = w;
-                }
-            }
-        } else {
-            if (inside && half == 0) {
-#pragma unroll
-                for (int e = 0; e < 3; ++e) out_f[(size_t)e * H * W + (size_t)gy * W + gx] = acc[e];
-            }
+            for (int e = 0; e < 3; ++e) out_f[(size_t)e * H * W + (size_t)gy * W + gx] = acc[e];
         }
     }
 }
 
-// A operands of one layer (lane: output channel j, channels 8 half.. of each 16-chunk) from
-// the layer's weights staged in LDS ([9][32][KIN] BF16).
+// A operands of one layer from its LDS slot, where tap t's and 16-channel chunk kc's operands lie in
+// lane order (16 B each), so a read touches every bank once.
 template <int KIN>
-__device__ __forceinline__ void fused_weights(bf16x8 (&a)[9][2], const unsigned char* __restrict__ slot, int half, int j) {
+__device__ __forceinline__ void fused_weights(bf16x8 (&a)[9][2], const unsigned char* __restrict__ slot, int lane) {
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int kc = 0; kc < KIN / 16; ++kc)
-            a[t][kc] = *reinterpret_cast<const bf16x8*>(slot + (((t * 32 + j) * KIN) + kc * 16 + half * 8) * 2);
+            a[t][kc] = *reinterpret_cast<const bf16x8*>(slot + ((t * (KIN / 16) + kc) * 64 + lane) * 16);
+}
+
+// One layer over its region: input map in_lds (region L - 1), output map out_lds (region L),
+// or, for the last layer, channels 0..2 to the FP32 planes out_f [3][H][W]. A block is 32 columns
+// of two rows (the region's row pairs end to end): input row i of its four feeds tap row i of the
+// upper output row and tap row i - 1 of the lower one, so 24 operand reads serve 36 products
+// (at 32 channels), in two independent chains, each in tap order. The next input row's operands
+// (or the next block's first) are read while the current row's products run. The weights a are
+// replaced by the next layer's (KNEXT channels, in next_slot) once the wave's last products are
+// issued, beside its last stores.
+template <int L, int KIN, bool kLast, int KNEXT>
+__device__ __forceinline__ void fused_layer(const unsigned char* __restrict__ in_lds, unsigned char* __restrict__ out_lds,
+                                            bf16x8 (&a)[9][2], const unsigned char* __restrict__ next_slot, const float* __restrict__ bias_lds,
+                                            float* __restrict__ out_f, int y0, int x0, int H, int W, int wave,
+                                            int half, int j) {
+    using In = FuRegion<L - 1>;
+    using Out = FuRegion<L>;
+    constexpr int kK = KIN / 16;
+    constexpr int kPairs = Out::kRows / 2 * Out::kCols;
+    constexpr int kBlocks = (kPairs + 31) / 32;
+    static_assert(Out::kRows % 2 == 0, "row pairs");
+    static_assert(kBlocks >= kFuWaves, "every wave has a block");
+    const f32x16 bias = bias_pattern(bias_lds, half);
+    bf16x8 b[2][3][kK];
+    auto place = [&](int blk, int& ry, int& rx) {
+        const int P = blk * 32 + j;
+        const int Pc = P < kPairs ? P : kPairs - 1;  // the last block's spare lanes read a real pixel
+        ry = 2 * (Pc / Out::kCols);
+        rx = Pc % Out::kCols;
+        return in_lds + (ry * In::kCols + rx) * In::kStride + half * 16;
+    };
+    auto read = [&](const unsigned char* base, int i) {
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+            for (int kc = 0; kc < kK; ++kc)
+                b[i & 1][kx][kc] = *reinterpret_cast<const bf16x8*>(base + (i * In::kCols + kx) * In::kStride + kc * 32);
+    };
+    int ry, rx;
+    const unsigned char* base = place(wave, ry, rx);
+    read(base, 0);
+    for (int blk = wave; blk < kBlocks; blk += kFuWaves) {
+        f32x16 up = bias, low = bias;
+        const int cy = ry, cx = rx;
+        const bool valid = blk * 32 + j < kPairs;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i < 3) {
+                read(base, i + 1);
+            } else if (blk + kFuWaves < kBlocks) {
+                base = place(blk + kFuWaves, ry, rx);
+                read(base, 0);
+            }
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int kc = 0; kc < kK; ++kc) {
+                    if (i < 3)
+                        up = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[3 * (i < 3 ? i : 0) + kx][kc], b[i & 1][kx][kc], up, 0, 0, 0);
+                    if (i > 0)
+                        low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[3 * (i > 0 ? i - 1 : 0) + kx][kc], b[i & 1][kx][kc], low, 0, 0, 0);
+                }
+        }
+        if (blk + kFuWaves >= kBlocks) {
+            fused_weights<KNEXT>(a, next_slot, 32 * half + j);
+            if constexpr (kLast) __builtin_amdgcn_s_waitcnt(0);  // the staged weights, before the stores
+        }
+        fused_store<L, kLast>(up, out_lds, out_f, cy, cx, valid, y0, x0, H, W, half);
+        fused_store<L, kLast>(low, out_lds, out_f, cy + 1, cx, valid, y0, x0, H, W, half);
+    }
 }
 
 __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputNorm nrm, FusedNet net,
@@ -446,37 +490,46 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
     float* bias_lds = reinterpret_cast<float*>(lds + kFuBufA + kFuBufB + 2 * kFuWSlot);
     const int tiles_x = (W + kFuTW - 1) / kFuTW;
     const int total = tiles_x * ((H + kFuTH - 1) / kFuTH);
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int half = lane / 32, j = lane % 32;
     if (threadIdx.x < 128) bias_lds[threadIdx.x] = net.bias[threadIdx.x / 32][threadIdx.x % 32];
 
-    // the packed input of a tile: raw values fetched into registers, packed into buffer B
-    float rx_[kFuRawPer][5];
-    bool rin[kFuRawPer];
-    auto fetch = [&](int tile) {
+    // the packed input of a tile: raw values fetched into registers (a pixel outside the image reads
+    // the first one, so that no load sits in a branch and all are in flight together), packed into
+    // buffer B
+    float rx_[kFuRawPer][4];
+    unsigned rm_[kFuRawPer];
+    auto raw_pixel = [&](int tile, int q, bool& in) -> unsigned {
         const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-        const int y0 = ty * kFuTH - FuRegion<0>::kHalo, x0 = tx * kFuTW - FuRegion<0>::kHalo;
+        const int e = threadIdx.x + q * kFuThreads;
+        const int r = e / FuRegion<0>::kCols, c = e - r * FuRegion<0>::kCols;
+        const int gy = ty * kFuTH - FuRegion<0>::kHalo + r, gx = tx * kFuTW - FuRegion<0>::kHalo + c;
+        in = e < FuRegion<0>::kPix && gy >= 0 && gy < H && gx >= 0 && gx < W;
+        return in ? (unsigned)gy * (unsigned)W + (unsigned)gx : 0u;
+    };
+    auto fetch = [&](int tile) {
 #pragma unroll
         for (int q = 0; q < kFuRawPer; ++q) {
-            const int e = threadIdx.x + q * kFuThreads;
-            const int r = e / FuRegion<0>::kCols, c = e - r * FuRegion<0>::kCols;
-            const int gy = y0 + r, gx = x0 + c;
-            rin[q] = e < FuRegion<0>::kPix && gy >= 0 && gy < H && gx >= 0 && gx < W;
-            const size_t p = rin[q] ? (size_t)gy * W + gx : 0;
-            rx_[q][0] = rin[q] ? raw.eta[p] : 0.f;
-            rx_[q][1] = rin[q] ? raw.u[p] : 0.f;
-            rx_[q][2] = rin[q] ? raw.v[p] : 0.f;
-            rx_[q][3] = rin[q] ? raw.H[p] : 0.f;
-            rx_[q][4] = rin[q] ? (raw.mask[p] ? 1.f : 0.f) : 0.f;
+            bool in;
+            const unsigned p = raw_pixel(tile, q, in);
+            rx_[q][0] = raw.eta[p];
+            rx_[q][1] = raw.u[p];
+            rx_[q][2] = raw.v[p];
+            rx_[q][3] = raw.H[p];
+            rm_[q] = raw.mask[p];
         }
     };
-    auto commit = [&]() {
+    auto commit = [&](int tile) {
 #pragma unroll
         for (int q = 0; q < kFuRawPer; ++q) {
             const int e = threadIdx.x + q * kFuThreads;
+            bool in;
+            raw_pixel(tile, q, in);
             if (e < FuRegion<0>::kPix) {
-                uint4 ca = make_uint4(0u, 0u, 0u, 0u), cb = make_uint4(0u, 0u, 0u, 0u);
-                if (rin[q]) pack_values(rx_[q], 0, nrm, ca, cb);  // no noise at inference
+                const float x[5] = {rx_[q][0], rx_[q][1], rx_[q][2], rx_[q][3], rm_[q] ? 1.f : 0.f};
+                uint4 ca, cb;
+                pack_values(x, 0, nrm, ca, cb);  // no noise at inference
+                if (!in) ca = cb = make_uint4(0u, 0u, 0u, 0u);
                 uint4* dst = reinterpret_cast<uint4*>(bufB + e * FuRegion<0>::kStride);
                 dst[0] = ca;
                 dst[1] = cb;
@@ -484,17 +537,22 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
         }
     };
     // The next layer's weights go from global memory straight into the free LDS slot while
-    // the current layer runs (a wave copies 64 consecutive 16 B chunks per load; the chunk
-    // counts are multiples of 64); the wait and the barrier after the layer publish them, and
-    // each wave then reads its A operands from LDS.
+    // the current layer runs, one tap and 16-channel chunk per wave and load (this lane: output
+    // channel j, channels 8 half.. of the chunk); the wait and the barrier after the layer publish
+    // them, and each wave then reads its A operands from LDS.
     auto wstage = [&](int layer, unsigned char* slot) {
-        const int chunks = 9 * 32 * (layer == 0 ? 16 : 32) / 8;
-        const uint4* src = reinterpret_cast<const uint4*>(net.wk[layer]);
+        const int chunks = layer == 0 ? 1 : 2, kin = 16 * chunks;
+        unsigned off = (unsigned)(j * kin + half * 8);
+        asm volatile("" : "+v"(off));  // formed here, not kept across the layers as 64-bit addresses
 #pragma unroll
-        for (int q = 0; q < kFuWPer; ++q) {
-            const int first = q * kFuThreads + wave * 64;  // wave-uniform
-            if (first < chunks)
-                __builtin_amdgcn_global_load_lds(src + first + lane, reinterpret_cast<uint4*>(slot) + first, 16, 0, 0);
+        for (int q = 0; q < (18 + kFuWaves - 1) / kFuWaves; ++q) {
+            const int g = q * kFuWaves + wave;  // wave-uniform: tap and chunk
+            if (g < 9 * chunks) {
+                const int t = g / chunks, kc = g - t * chunks;
+                const uint16_t* group = net.wk[layer] + t * 32 * kin + kc * 16;  // wave-uniform
+                __builtin_amdgcn_global_load_lds(group + off,
+                                                 reinterpret_cast<uint4*>(slot) + g * 64, 16, 0, 0);
+            }
         }
     };
     auto publish = [&]() {
@@ -502,36 +560,46 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
         __syncthreads();
     };
 
+    // Staging: a layer's weights are in LDS, landed and published by a barrier, before the layer in
+    // front of it ends (each wave reads them then); a slot is refilled once a barrier has passed since
+    // its last read. Layers 2-4 take two slots in turn, whose roles swap from tile to tile; layer 1
+    // has the tail of buffer A, free from layer 3 on. All copies land beside a long layer, and none
+    // is waited for behind layer 4's stores.
+    unsigned char* const s1 = bufA + FuRegion<3>::kBytes;
     bf16x8 w[9][2];
-    wstage(0, wslot[0]);
+    wstage(0, s1);
+    wstage(1, wslot[0]);
+    wstage(2, wslot[1]);
     if ((int)blockIdx.x < total) {
         fetch(blockIdx.x);
-        commit();
+        commit(blockIdx.x);
     }
-    __builtin_amdgcn_s_waitcnt(0);
+    publish();
+    fused_weights<16>(w, s1, lane);
     for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
         const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
         const int y0 = ty * kFuTH, x0 = tx * kFuTW;
         const int next = tile + (int)gridDim.x;
-        __syncthreads();  // packed input and layer 1's weights in place; the last tile's layer 4 done
-        fused_weights<16>(w, wslot[0], half, j);
+        __syncthreads();  // packed input, layer 2's and 3's weights in place; the last tile's layer 4 done
+        fused_layer<1, 16, false, 32>(bufB, bufA, w, wslot[0], bias_lds, nullptr, y0, x0, H, W, wave, half, j);
+        __syncthreads();
+        wstage(3, wslot[0]);
+        fetch(next < total ? next : tile);  // no branch: its loads stay in flight
+        fused_layer<2, 32, false, 32>(bufA, bufB, w, wslot[1], bias_lds + 32, nullptr, y0, x0, H, W, wave, half, j);
+        publish();
+        wstage(0, s1);
+        fused_layer<3, 32, false, 32>(bufB, bufA, w, wslot[0], bias_lds + 64, nullptr, y0, x0, H, W, wave, half, j);
+        publish();
         wstage(1, wslot[1]);
-        fused_layer<1, 16, false>(bufB, bufA, w, bias_lds, nullptr, y0, x0, H, W, wave, half, j);
-        publish();
-        fused_weights<32>(w, wslot[1], half, j);
         wstage(2, wslot[0]);
-        if (next < total) fetch(next);
-        fused_layer<2, 32, false>(bufA, bufB, w, bias_lds + 32, nullptr, y0, x0, H, W, wave, half, j);
-        publish();
-        fused_weights<32>(w, wslot[0], half, j);
-        wstage(3, wslot[1]);
-        fused_layer<3, 32, false>(bufB, bufA, w, bias_lds + 64, nullptr, y0, x0, H, W, wave, half, j);
-        publish();
-        fused_weights<32>(w, wslot[1], half, j);
-        wstage(0, wslot[0]);
-        if (next < total) commit();  // buffer B is free: layer 4 reads buffer A only
-        fused_layer<4, 32, true>(bufA, nullptr, w, bias_lds + 96, out_f, y0, x0, H, W, wave, half, j);
-        __builtin_amdgcn_s_waitcnt(0);
+        // buffer B is free: layer 4 reads buffer A only. One half of the waves packs the next input
+        // before its products, the other after, so the two share a SIMD's units.
+        if (next < total && wave < kFuWaves / 2) commit(next);
+        fused_layer<4, 32, true, 16>(bufA, nullptr, w, s1, bias_lds + 96, out_f, y0, x0, H, W, wave, half, j);
+        if (next < total && wave >= kFuWaves / 2) commit(next);
+        unsigned char* const t = wslot[0];
+        wslot[0] = wslot[1];
+        wslot[1] = t;
     }
 }
 
