@@ -544,6 +544,7 @@ def variants_leg(case, steps, log):
                         ("wetdry", WETDRY)):
         with Sw2d.from_case(case, flags=flags, cd=0.0025, hmin=0.0625) as sim:
             sim.band_rows = VARIANT_ROWS[name]
+            sim.set_time_blocking(1)
             sim.step(10)
             torch.cuda.synchronize()
             ms = sim.step_timed(steps)
@@ -744,10 +745,8 @@ def main():
     sim = Sw2d.from_case(case, device=dev)
     spp = args.steps_per_pass
     rows = args.band_rows or TUNED_ROWS[(args.workload, spp)]
-    if spp == 1:
-        sim.band_rows = rows
-    else:
-        sim.set_time_blocking(spp, rows=rows)
+    sim.band_rows = rows
+    sim.set_time_blocking(spp, rows=rows)
     print(f"# {case.name} {case.nx}x{case.ny} steps_per_pass={spp} band_rows={rows} warmup {args.warmup}",
           file=sys.stderr, flush=True)
     sim.step(args.warmup)

@@ -80,7 +80,7 @@ enum {
  *                  holds: H is the depth below the datum, which may sit above the still-water
  *                  level, so ground that can flood is a water cell whose surface starts at
  *                  eta = -H (zero total depth). Taken alone (no other flag).
- * A handle with SW2D_ADVECTION steps one step per pass (sw2d_set_time_blocking refuses
+ * With SW2D_ADVECTION the streamed passes take one step each (sw2d_set_time_blocking refuses
  * K > 1: its upwind differences reach one face further per step); every other combination
  * may take K steps per pass. The batched and unfused paths take flags = 0 only. */
 #define SW2D_FRICTION 1u
@@ -159,12 +159,13 @@ int64_t sw2d_steps_done(sw2d_t h);
 int sw2d_set_state(sw2d_t h, const float *d_eta, const float *d_u, const float *d_v, int64_t step);
 
 /* How the steps of a handle are scheduled never changes the state (bit for bit) and regroups
- * the fold sums at most. The plain model (flags = 0) is advanced over tiles held in registers,
- * several steps per launch: grids of at most 2^23 cells, whose state and depth stay in the 256 MB
- * last-level cache, always (up to 4 steps per launch), larger ones at 4 steps per pass. Other
- * passes are streamed through row pipelines as the two settings below say. on != 0 streams
- * every pass of the handle (0, the default, restores the tiles); sw2d_streaming returns 1 if its
- * steps are streamed, 0 if they go over tiles, -1 for a NULL handle. */
+ * the fold sums at most. Steps go over tiles held in registers, several per launch: on grids of at
+ * most 2^23 cells, whose state and depth stay in the 256 MB last-level cache, always (up to 4 steps
+ * per launch whatever the handle's steps per pass); on larger ones with as many steps per pass as
+ * are fastest unless sw2d_set_time_blocking has chosen, and then where tiles are the faster way
+ * for that many. Other passes are streamed through row pipelines as the two settings below say.
+ * on != 0 streams every pass of the handle (0, the default, restores the tiles); sw2d_streaming
+ * returns 1 if its steps are streamed, 0 if they go over tiles, -1 for a NULL handle. */
 int sw2d_set_streaming(sw2d_t h, int32_t on);
 int32_t sw2d_streaming(sw2d_t h);
 
@@ -176,11 +177,12 @@ int32_t sw2d_band_rows(sw2d_t h);
 
 /* Temporal blocking: steps_per_pass = K in 2..4 makes sw2d_step advance K steps per pass over
  * HBM (the intermediate states stay in registers; a remainder of the step count takes one
- * shorter pass), with its own band height rows in [8, ny] where the pass is streamed; 1 (the
- * default) restores one step per pass. Grids that stay in the cache make no pass over HBM and
- * take as many steps per launch as is fastest. The state and folds are the same as with single steps (the state bit for
- * bit, the folds up to the order of their sums). SW2D_EINVAL for K or rows out of range, or
- * K > 1 on a handle with SW2D_ADVECTION. */
+ * shorter pass), with its own band height rows in [8, ny] where the pass is streamed; 1 makes it
+ * one step per pass. A handle for which this was never called takes as many steps per pass as are
+ * fastest (sw2d_time_blocking returns 1, the count its streamed passes take), and so does every
+ * grid that stays in the cache, which makes no pass over HBM. The state and folds are the same as
+ * with single steps (the state bit for bit, the folds up to the order of their sums). SW2D_EINVAL
+ * for K or rows out of range, or K > 1 on a handle with SW2D_ADVECTION. */
 int sw2d_set_time_blocking(sw2d_t h, int32_t steps_per_pass, int32_t rows);
 int32_t sw2d_time_blocking(sw2d_t h);
 

@@ -30,6 +30,7 @@ struct sw2d_ctx {
     StepGeometry geo;   // one step per pass
     StepGeometry geok[kMaxStepsPerPass + 1];  // K steps per pass (K >= 2)
     int steps_per_pass; // 1 .. kMaxStepsPerPass
+    bool spp_chosen;    // by the caller (sw2d_set_time_blocking)
     bool streaming;     // row-marching passes also where register tiles would serve
     StepCoef coef;
     int64_t step;             // steps done
@@ -140,12 +141,17 @@ bool cached_grid(const sw2d_ctx* h) { return (int64_t)h->p.nx * h->p.ny <= kBloc
 
 // Whether a pass of k steps goes over register tiles (see kBlockMaxCells).
 bool tile_pass(const sw2d_ctx* h, int k) {
-    return !h->streaming && h->p.flags == 0 && (cached_grid(h) || k == kBlockMaxK);
+    if (h->streaming) return false;
+    if (cached_grid(h) || k == kBlockMaxK) return true;
+    return h->p.flags != 0 && (h->p.flags != kVarWetDry || k >= 2);
 }
 
-// Steps per pass of the handle: up to kBlockMaxK over tiles of a cached grid, else the caller's.
+// Steps per pass of the handle: over tiles of a cached grid, or when the caller has chosen none, as
+// many as are fastest, else the caller's.
 int pass_steps(const sw2d_ctx* h) {
-    return cached_grid(h) && tile_pass(h, 1) ? kBlockMaxK : h->steps_per_pass;
+    if (h->streaming || (h->spp_chosen && !cached_grid(h))) return h->steps_per_pass;
+    const bool divides = (h->p.flags & kVarFriction) && (int64_t)h->p.nx * h->p.ny > kBlockFrictionCells;
+    return divides ? 2 : kBlockMaxK;
 }
 
 int add_pass_times(hipEvent_t* ev, int passes, double* total_ms) {
@@ -172,7 +178,7 @@ int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms)
         const int k = (nsteps - done < kmax) ? nsteps - done : kmax;
         const bool tiles = tile_pass(h, k);
         if (tiles && k != bg_k) {
-            bg = block_geometry(h->p.nx, h->p.ny, k);
+            bg = block_geometry(h->p.nx, h->p.ny, k, (int)h->p.flags);
             bg_k = k;
         }
         const StepGeometry& g = (k >= 2) ? h->geok[k] : h->geo;
@@ -190,7 +196,7 @@ int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms)
         FoldPartial* part = h->part + (size_t)pending * nblocks;
         if (ev) SW2D_HIP(hipEventRecord(ev[2 * passes], h->stream));
         if (tiles)
-            SW2D_HIP(launch_block(k, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, bg, h->coef,
+            SW2D_HIP(launch_block(k, (int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, bg, h->coef,
                                   h->stream));
         else if (k >= 2)
             SW2D_HIP(launch_stepk(k, (int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part,
@@ -265,6 +271,7 @@ int sw2d_create(const sw2d_params* p, const float* d_H, const uint8_t* d_mask, f
     for (int K = 2; K <= kMaxStepsPerPass; ++K)
         h->geok[K] = make_geometry(p->nx, p->ny, default_rows(p->ny), kstep_strip_out(K, p->flags));
     h->steps_per_pass = 1;
+    h->spp_chosen = false;
     h->streaming = false;
     h->coef = make_coef(p);
     h->step = 0;
@@ -375,6 +382,7 @@ int sw2d_set_time_blocking(sw2d_t h, int32_t steps_per_pass, int32_t rows) {
             h->geok[K] = make_geometry(h->p.nx, h->p.ny, rows, kstep_strip_out(K, h->p.flags));
     }
     h->steps_per_pass = steps_per_pass;
+    h->spp_chosen = true;
     return SW2D_OK;
 }
 

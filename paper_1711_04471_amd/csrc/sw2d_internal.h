@@ -19,6 +19,7 @@ constexpr int kWavesPerGroup = 4;                    // strips per workgroup
 constexpr int kGroupThreads = kWave * kWavesPerGroup;
 constexpr int kGroupCols = kStripOut * kWavesPerGroup;  // 240 output columns per workgroup
 constexpr int kFoldThreads = 256;
+constexpr int kCus = 256;                            // MI355X
 constexpr int kXcds = 8;                             // MI355X: 8 XCDs, one L2 each
 constexpr int kMinRows = 8;                          // smallest band height a handle may use
 constexpr int kFoldChunk = 16;                       // steps whose partials are buffered at least
@@ -104,14 +105,22 @@ inline StepGeometry make_geometry(int nx, int ny, int rows, int strip_out = kStr
 constexpr int kBlockWaves = 8;
 constexpr int kBlockRowsLow = 3, kBlockRowsMid = 5, kBlockRowsHigh = 8;  // tiles of 24, 40 and 64 rows
 constexpr int kBlockMaxK = 4;
-constexpr int kBlockLowTiles = 320;  // most tiles of 24 rows at K >= 3
+constexpr int kBlockLowTiles = 320;     // most tiles of 24 rows at K >= 3
+constexpr int kBlockLowTilesVar = 768;  // at K <= 2 with model variants
 // Grids of at most 2^23 cells, whose state and depth (28 B per cell and step, 235 MB) the 256 MB
-// Infinity Cache holds, take up to kBlockMaxK steps per pass whatever the caller's steps per pass:
-// there is no HBM pass to choose. Larger grids take the caller's, over tiles at 4 steps per pass
-// only (us per step on 8192 x 4096, tiles against the row pipelines: K = 1 197 and 192, K = 2 103
-// and 101, K = 3 71 and 71, K = 4 51.7 and 54.3: overlapping tiles re-read and recompute more,
-// which the fewer instructions per cell outweigh at K = 4 alone).
+// Infinity Cache holds, take several steps per pass whatever the caller's steps per pass: there is
+// no HBM pass to choose. Larger grids take the caller's, if one was chosen, and else kBlockMaxK:
+// the plain model over tiles at 4 steps per pass only (us per step on 8192 x 4096, tiles against the
+// row pipelines: K = 1 197 and 192, K = 2 103 and 101, K = 3 71 and 71, K = 4 51.7 and 54.3:
+// overlapping tiles re-read and recompute more, which the fewer instructions per cell outweigh at
+// K = 4 alone), the variants at any, wetting and drying from 2 steps per pass on (K = 1 199 and
+// 195).
 constexpr int64_t kBlockMaxCells = (int64_t)1 << 23;
+// Friction divides four times per cell and step, so that a pass of 4 steps, which recomputes a third
+// of a tile or more, is bound by its vector issue: beyond 2^21 cells two steps per pass are faster (all
+// variants, us per step at K = 2 and 4: 2047 x 1531 22.7 and 23.7, 8192 x 4096 164 and 200); below,
+// where a launch has few tiles per CU, four are (1024^2 11.4 and 9.8).
+constexpr int64_t kBlockFrictionCells = (int64_t)1 << 21;
 
 struct BlockGeometry {
     int nx, ny;
@@ -119,15 +128,21 @@ struct BlockGeometry {
     int strips, bands, nblocks;
 };
 
-inline BlockGeometry make_block_geometry(int nx, int ny, int K, int R) {
-    // neighbouring tiles overlap by 4K columns or rows
-    const int cols = 2 * kWave, rows = kBlockWaves * R, over = 4 * K;
+// Rows a step of a tile spoils on an open south side (2 on the others, and as many columns west):
+// the advection's upwind differences reach one face further.
+constexpr int block_south(int kVar) { return (kVar & kVarAdvection) ? 3 : 2; }
+constexpr int block_west_lanes(int K, int kVar) { return (block_south(kVar) * K + 1) / 2; }
+
+inline BlockGeometry make_block_geometry(int nx, int ny, int K, int R, int kvar = 0) {
+    // neighbouring tiles overlap by what K steps spoil on their sides
+    const int cols = 2 * kWave, rows = kBlockWaves * R;
+    const int own_cols = cols - 2 * (block_west_lanes(K, kvar) + K), own_rows = rows - (block_south(kvar) + 2) * K;
     BlockGeometry g;
     g.nx = nx;
     g.ny = ny;
     g.rows = R;
-    g.strips = nx <= cols ? 1 : 1 + (nx - cols + (cols - over) - 1) / (cols - over);
-    g.bands = ny <= rows ? 1 : 1 + (ny - rows + (rows - over) - 1) / (rows - over);
+    g.strips = nx <= cols ? 1 : 1 + (nx - cols + own_cols - 1) / own_cols;
+    g.bands = ny <= rows ? 1 : 1 + (ny - rows + own_rows - 1) / own_rows;
     g.nblocks = g.strips * g.bands;
     return g;
 }
@@ -141,18 +156,36 @@ inline BlockGeometry make_block_geometry(int nx, int ny, int K, int R) {
 // 12.1 us per step at 3, 5 and 8 rows); at K = 3 and 4 it is not (2048^2, K = 4: 12.3, 8.4, 9.0;
 // 4096 x 2048: 22.7, 14.2, 14.4), and from HBM the re-read rows add to it (8192 x 4096, K = 4: 88,
 // 57.9, 51.7).
-inline BlockGeometry block_geometry(int nx, int ny, int K) {
-    const BlockGeometry low = make_block_geometry(nx, ny, K, kBlockRowsLow);
-    if (K <= 2 || low.nblocks <= kBlockLowTiles) return low;
+//
+// The variants take more time per cell, so the recomputed overlap weighs more: 64 rows at 4 steps
+// per pass once the 40-row tiles are more than one per CU (friction 1024^2 6.7 us per step against
+// 7.5 at 40 rows; all variants 9.8 against 11.1, 693 x 700 with 238 tiles 9.5 against 6.5), 40 rows
+// for many tiles at K <= 2 (all variants, K = 2, 2047 x 1531: 22.7 against 27.7 at 24 rows; 1024^2,
+// 657 low tiles: 12.5 against 11.9). Wetting and drying is as cheap as the plain step and keeps 40
+// rows (4096 x 2048 20.0 us, 21.8 at 64).
+inline BlockGeometry block_geometry(int nx, int ny, int K, int kvar = 0) {
+    const BlockGeometry low = make_block_geometry(nx, ny, K, kBlockRowsLow, kvar);
+    if ((K <= 2 && kvar == 0) || low.nblocks <= (K <= 2 ? kBlockLowTilesVar : kBlockLowTiles)) return low;
     const bool cached = (int64_t)nx * ny <= kBlockMaxCells;
-    return make_block_geometry(nx, ny, K, K == 4 && !cached ? kBlockRowsHigh : kBlockRowsMid);
+    const BlockGeometry mid = make_block_geometry(nx, ny, K, kBlockRowsMid, kvar);
+    const bool high = kvar == 0 ? K == 4 && !cached
+                                : kvar != kVarWetDry && (cached ? K == 4 && mid.nblocks > kCus : K >= 2);
+    return high ? make_block_geometry(nx, ny, K, kBlockRowsHigh, kvar) : mid;
 }
 
-// K = 1..4 steps of the plain model in one pass over register tiles (geometry from
-// block_geometry); the partials of step s of the pass go to part[s * geo.nblocks + 0..nblocks).
-hipError_t launch_block(int K, const float* eta, const float* u, const float* v, const float* hp, float* eta_o,
-                        float* u_o, float* v_o, FoldPartial* part, const BlockGeometry& geo, const StepCoef& k,
-                        hipStream_t s);
+// The shapes that block_geometry chooses.
+constexpr bool block_shape(int K, int R, int kVar) {
+    if (R == kBlockRowsLow) return true;
+    if (R == kBlockRowsMid) return kVar != 0 || K >= 3;
+    return kVar == 0 ? K == 4 : kVar != kVarWetDry && K >= 2;
+}
+
+// K = 1..4 steps of the model (kvar: its variants, 0 for the plain step) in one pass over register
+// tiles (geometry from block_geometry); the partials of step s of the pass go to
+// part[s * geo.nblocks + 0..nblocks).
+hipError_t launch_block(int K, int kvar, const float* eta, const float* u, const float* v, const float* hp,
+                        float* eta_o, float* u_o, float* v_o, FoldPartial* part, const BlockGeometry& geo,
+                        const StepCoef& k, hipStream_t s);
 
 // kvar: the model variants (0 for the plain step).
 hipError_t launch_step(int kvar, const float* eta, const float* u, const float* v, const float* hp,

@@ -128,3 +128,37 @@ def test_state_off_8_bytes_steps_alike():
     off = (ptr.value - buf.data_ptr()) // 4
     assert np.array_equal(buf[off:off + n].cpu().numpy().reshape(c.ny, c.nx), want[0][0])
     L.sw2d_destroy(h)
+
+
+def _variant_state(case, flags, calls, streaming, spp=1):
+    from paper_1711_04471_amd.sw2d import Sw2d
+    with Sw2d.from_case(case, flags=flags, cd=0.0025, hmin=0.0625) as sim:
+        sim.streaming = streaming
+        if spp > 1:
+            sim.set_time_blocking(spp, rows=min(8, case.ny))
+        for n in calls:
+            sim.step(n)
+        return sim.state_numpy(), sim.reduce(sum(calls))
+
+
+def _variant_case(shape, flags):
+    make = inputs.shore_basin if flags == 8 else inputs.small_basin
+    return make(*shape, seed=sum(shape) + flags)
+
+
+# 24-row tiles; 40-row tiles; 64-row tiles at 4 steps per pass; two steps per pass with friction
+@pytest.mark.parametrize("shape", [(66, 66), (117, 33), (251, 61), (693, 700), (1024, 1000), (2047, 1100)])
+@pytest.mark.parametrize("flags", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_variant_tiles_equal_streamed_steps(flags, shape):
+    c = _variant_case(shape, flags)
+    calls = [1, 2, 3, 15]
+    _same(_variant_state(c, flags, calls, False), _variant_state(c, flags, calls, True), c)
+
+
+@pytest.mark.parametrize("flags", [0, 2, 7, 8])
+def test_grids_past_the_cache_equal_streamed_steps(flags):
+    """More than 2^23 cells: 64-row tiles, the caller's steps per pass where one is chosen."""
+    c = _variant_case((3001, 2900), flags)
+    _same(_variant_state(c, flags, [1, 2, 3, 4], False), _variant_state(c, flags, [1, 2, 3, 4], True), c)
+    if not flags & 4:
+        _same(_variant_state(c, flags, [7], False, 3), _variant_state(c, flags, [7], True), c)
