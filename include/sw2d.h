@@ -424,12 +424,20 @@ int sw2d_conv3x3_dgrad(const uint16_t *dy, const uint16_t *wd, const uint16_t *a
                        int32_t nimg, int32_t ny, int32_t nx, void *stream);
 
 /* Weight gradient dW[t][o][c] = sum_p dy[p][o] x[p + off_t][c] and db[o] = sum_p dy[p][o]
- * (FP32 outputs [9][32][cin] and [32]), summed over pixel chunks in a fixed order. x: BF16
+ * (FP32 outputs [9][32][cin] and [32]), summed over pixel tiles in a fixed order. x: BF16
  * NHWC cin channels; dy: BF16 NHWC 32 channels. work: FP32 partials, sized by
- * sw2d_wgrad_workspace_bytes (0 for bad sizes). */
+ * sw2d_wgrad_workspace_bytes (0 for bad sizes); it sets how many workgroups share the tiles. */
 size_t sw2d_wgrad_workspace_bytes(int32_t cin, int32_t nimg, int32_t ny, int32_t nx);
 int sw2d_conv3x3_wgrad(const uint16_t *x, int32_t cin, const uint16_t *dy, int32_t nimg, int32_t ny, int32_t nx,
                        float *dW, float *db, void *work, size_t work_bytes, void *stream);
+
+/* Both gradients of a layer with 32 inputs in one pass over x and dy: dW and db as
+ * sw2d_conv3x3_wgrad (cin = 32, the same work), dx as sw2d_conv3x3_dgrad with act_in = x (bitwise).
+ * dy_channels: 32, or 4 for a dy of 4 channels per pixel, the others taken as zero (the last layer).
+ * dx may not overlap x or dy. */
+int sw2d_conv3x3_backward(const uint16_t *x, const uint16_t *dy, int32_t dy_channels, const uint16_t *wd, uint16_t *dx,
+                          int32_t nimg, int32_t ny, int32_t nx, float *dW, float *db, void *work, size_t work_bytes,
+                          void *stream);
 
 /* Masked squared error: for each image and channel (eta on water cells, u on active east
  * faces, v on active north faces of mask), r = out - target_scale[c] * target; *loss_sum
@@ -439,6 +447,11 @@ size_t sw2d_mse_workspace_bytes(void);
 int sw2d_mse_grad(const float *out, const float *target, const float *target_scale, const uint8_t *mask,
                   int32_t nimg, int32_t ny, int32_t nx, float inv_n, uint16_t *d_out, double *loss_sum, void *work,
                   size_t work_bytes, void *stream);
+
+/* The same with d_out of 4 channels per pixel (the fourth zero), for sw2d_conv3x3_backward. */
+int sw2d_mse_grad4(const float *out, const float *target, const float *target_scale, const uint8_t *mask,
+                   int32_t nimg, int32_t ny, int32_t nx, float inv_n, uint16_t *d_out, double *loss_sum, void *work,
+                   size_t work_bytes, void *stream);
 
 /* Training targets: out[c][p] = a_c[p] - b_c[p] for c = 0, 1, 2 (out: FP32 [3][n]). */
 int sw2d_sub3(const float *a0, const float *a1, const float *a2, const float *b0, const float *b1,
@@ -457,6 +470,14 @@ int sw2d_adam(float *theta, const float *grad, float *m, float *v, int32_t n, in
 /* BF16 working copies of one layer's FP32 master [9][32][cin]: wk (same layout) and, when
  * wd is not NULL (cin = 32 only), the data-gradient layout wd[8 - t][c][o] = W[t][o][c]. */
 int sw2d_cast_weights(const float *master, int32_t cin, uint16_t *wk, uint16_t *wd, void *stream);
+
+/* Adam on a whole network and its BF16 copies in one launch: layers (1..4) of cin[l] (16 or 32)
+ * inputs lie one after another in theta, grad, m and v, each as [9][32][cin] weights, then [32] biases;
+ * wk[l] and, where not NULL (cin 32), wd[l] get layer l's copies as from sw2d_cast_weights. The same
+ * result as sw2d_adam over all parameters, then sw2d_cast_weights on each layer. */
+int sw2d_adam_net(float *theta, const float *grad, float *m, float *v, int32_t layers, const int32_t *cin, int32_t t,
+                  float lr, float beta1, float beta2, float eps, uint16_t *const *wk, uint16_t *const *wd,
+                  void *stream);
 
 /* state += t_std[c] * out[c] on active entries (eta: water cells, u/v: active faces). t_std:
  * host array of 3. */

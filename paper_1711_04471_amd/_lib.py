@@ -106,15 +106,21 @@ SIGNATURES = {
                          [ctypes.c_int32] * 3 + [_vp]),
     "sw2d_conv3x3_dgrad": (ctypes.c_int, [_vp] * 4 + [ctypes.c_int32] * 3 + [_vp]),
     "sw2d_wgrad_workspace_bytes": (ctypes.c_size_t, [ctypes.c_int32] * 4),
+    "sw2d_conv3x3_backward": (ctypes.c_int, [_vp, _vp, ctypes.c_int32, _vp, _vp] + [ctypes.c_int32] * 3 +
+                              [_vp, _vp, _vp, ctypes.c_size_t, _vp]),
     "sw2d_conv3x3_wgrad": (ctypes.c_int, [_vp, ctypes.c_int32, _vp] + [ctypes.c_int32] * 3 +
                            [_vp, _vp, _vp, ctypes.c_size_t, _vp]),
     "sw2d_mse_workspace_bytes": (ctypes.c_size_t, []),
     "sw2d_mse_grad": (ctypes.c_int, [_vp, _vp, _fp, _vp] + [ctypes.c_int32] * 3 +
                       [ctypes.c_float, _vp, _vp, _vp, ctypes.c_size_t, _vp]),
+    "sw2d_mse_grad4": (ctypes.c_int, [_vp, _vp, _fp, _vp] + [ctypes.c_int32] * 3 +
+                      [ctypes.c_float, _vp, _vp, _vp, ctypes.c_size_t, _vp]),
     "sw2d_sub3": (ctypes.c_int, [_vp] * 6 + [ctypes.c_int32, _vp, _vp]),
     "sw2d_moments_workspace_bytes": (ctypes.c_size_t, []),
     "sw2d_moments": (ctypes.c_int, [_vp, _vp, ctypes.c_int64, _vp, _vp, ctypes.c_size_t, _vp]),
     "sw2d_adam": (ctypes.c_int, [_vp] * 4 + [ctypes.c_int32] * 2 + [ctypes.c_float] * 4 + [_vp]),
+    "sw2d_adam_net": (ctypes.c_int, [_vp] * 4 + [ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), ctypes.c_int32] +
+                      [ctypes.c_float] * 4 + [_pp, _pp, _vp]),
     "sw2d_cast_weights": (ctypes.c_int, [_vp, ctypes.c_int32, _vp, _vp, _vp]),
     "sw2d_apply_correction": (ctypes.c_int, [_vp] * 5 + [ctypes.c_int32] * 2 + [_fp, _vp]),
     "sw2d_rmse_workspace_bytes": (ctypes.c_size_t, []),

@@ -21,6 +21,16 @@ struct AdamHyper {
     float inv_bc1, inv_bc2;  // 1 / (1 - beta^t), computed in double on the host
 };
 
+// The layers of a flat parameter buffer and their BF16 copies (layers 0: none).
+struct NetCopies {
+    static constexpr int kMax = 4;
+    int layers;
+    int begin[kMax];  // layer l: [9][32][cin] weights from begin[l] on, then [32] biases
+    int cin[kMax];
+    uint16_t* wk[kMax];
+    uint16_t* wd[kMax];  // or null
+};
+
 hipError_t launch_restrict4(const float* eta, const float* u, const float* v, const float* H,
                             const uint8_t* mask, int NX, int NY, float* eta_c, float* u_c, float* v_c,
                             float* H_c, uint8_t* mask_c, hipStream_t s);
@@ -59,18 +69,21 @@ hipError_t launch_cnn_fused(const RawIn& raw, const InputNorm& nrm, const FusedN
 hipError_t launch_conv3x3(int kin, int mode, const uint16_t* in, const uint16_t* Wk, const float* bias,
                           uint16_t* out_bf, float* out_f, const uint16_t* relu_src, int nimg, int H, int W,
                           hipStream_t s);
-int wgrad_chunks(int nimg, int H, int W);
-hipError_t launch_wgrad(int kin, const uint16_t* x, const uint16_t* dy, int nimg, int H, int W, float* part_w,
-                        float* part_b, float* dW, float* db, hipStream_t s);
+// A layer's gradients: dW, db and, with dx (32 channels), the data gradient masked by x > 0. part:
+// max_parts partials of 9 * 32 * kin + 32 floats, as many workgroups at most. dch: dY's channels per
+// pixel (32, or 4 with dx).
+int64_t backward_tiles(int nimg, int H, int W);
+hipError_t launch_backward(int kin, const uint16_t* x, const uint16_t* dy, int dch, const uint16_t* wd, uint16_t* dx,
+                           int nimg, int H, int W, float* part, int max_parts, float* dW, float* db, hipStream_t s);
 hipError_t launch_mse_grad(const float* out, const float* target, const uint8_t* mask, int nimg, int H, int W,
-                           float inv_n, const float* tscale, uint16_t* d_out, double* partial, int nblocks,
+                           float inv_n, const float* tscale, uint16_t* d_out, int dch, double* partial, int nblocks,
                            double* loss, hipStream_t s);
 hipError_t launch_sub3(const float* a0, const float* a1, const float* a2, const float* b0, const float* b1,
                        const float* b2, int n, float* out, hipStream_t s);
 hipError_t launch_moments(const float* x, const uint8_t* mask, int64_t n, double* partial, int nblocks, double* out,
                           hipStream_t s);
 hipError_t launch_adam(float* theta, const float* grad, float* m, float* v, int n, const AdamHyper& hp,
-                       hipStream_t s);
+                       const NetCopies& copies, hipStream_t s);
 hipError_t launch_cast_weights(const float* master, int kin, int dkin, uint16_t* wk, uint16_t* wd, hipStream_t s);
 hipError_t launch_correct(float* eta, float* u, float* v, const float* out, const uint8_t* mask, int H, int W,
                           const float* t_std, hipStream_t s);

@@ -13,10 +13,10 @@
 //                    used for the forward layers (bias + ReLU + BF16 store, or bias + FP32
 //                    planar store of 3 channels) and for the data gradient (flipped,
 //                    transposed weights; fused ReLU-mask of the layer input);
-//   * wgrad          dW[t][o][c] = sum_p dY[p][o] X[p + off_t][c], split over pixel
-//                    chunks on MFMA, FP32 partials, then a fixed-order reduction;
-//   * mse_grad       masked squared error and its gradient (BF16 NHWC, 32 channels);
-//   * adam           Adam on FP32 master weights, then BF16 working copies in the forward
+//   * backward       a layer's weight gradient dW[t][o][c] = sum_p dY[p][o] X[p + off_t][c] on MFMA
+//                    (FP32 partials, then a fixed-order reduction), with the data gradient beside it;
+//   * mse_grad       masked squared error and its gradient (BF16 NHWC, 32 or 4 channels);
+//   * adam           Adam on FP32 master weights and their BF16 working copies in the forward
 //                    and data-gradient layouts;
 //   * correct        state += activity * t_std * out;
 //   * rmse           sum over water of (a - b)^2 in FP64, fixed-order.
@@ -24,6 +24,8 @@
 // row, so one lane's MFMA operand (8 consecutive channels) is one 16 B load.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "sw2d_internal.h"
 #include "sw2d_surrogate.h"
@@ -34,6 +36,8 @@ namespace sur {
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
@@ -603,206 +607,441 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
     }
 }
 
-// ------------------------------------------------------------------------------ wgrad
-// dW[t][o][c] = sum_p dY[p][o] X[p + off_t][c] on the MFMA with K = pixels: A = dY (32
-// outputs x 16 pixels), B = X shifted by the tap (16 pixels x 32 channels). Both operands
-// take 8 consecutive pixels of one channel per lane while the maps are NHWC (channels
-// contiguous), so a tile is staged in LDS pair-packed: a dword holds two horizontally
-// adjacent pixels of one channel, dword (r * pairs + q) * 32 + c for row r, pair q,
-// channel c. A lane reads one row's pixels c0 - 1 .. c0 + 8 of its channel as 5 dwords and
-// forms the three horizontal taps' operands from them (the odd tap by byte alignment); the
-// dY operand is 4 dwords. Workgroup g takes tiles g * kWgTiles ... of all images' 4 x 128
-// pixel tiles, fetching the next tile into registers while the current one is multiplied.
-// Its 12 waves (3 per SIMD) split the work by tile row and tap row: wave w accumulates the
-// three taps of tap row ky = w / 4 over tile row w % 4 (3 accumulators of 32 x 32); the four
-// tile rows of a tap are added in LDS in row order, and the chunk's partial [9][32][KIN]
-// (and the bias partial [32]) goes to global memory.
-constexpr int kWgTH = 4;                    // rows per tile
-constexpr int kWgTW = 128;                  // pixels per tile row
-constexpr int kWgTiles = 8;                 // tiles per chunk
-constexpr int kWgWaves = 12;                // (tile row, tap row) pairs
-constexpr int kWgThreads = 64 * kWgWaves;
-constexpr int kWgXPairs = (kWgTW + 2) / 2;  // pairs of the input rows: pixels -1 .. kWgTW
-constexpr int kWgDPairs = kWgTW / 2;        // pairs of the dY rows
-constexpr int kWgXRows = kWgTH + 2;
-constexpr int kWgXItems = kWgXRows * kWgXPairs * 4;  // (row, pair, 8-channel group), 32 channels
-constexpr int kWgDItems = kWgTH * kWgDPairs * 4;
-constexpr int kWgXPer = (kWgXItems + kWgThreads - 1) / kWgThreads;
-constexpr int kWgDPer = (kWgDItems + kWgThreads - 1) / kWgThreads;
+// ------------------------------------------------------------------------------ backward
+// One layer's backward over its input map x and output gradient dY (both NHWC), each read once:
+//   dW[t][o][c] = sum_p dY[p][o] x[p + off_t][c]   (MFMA, K = pixels),  db[o] = sum_p dY[p][o];
+//   dX[p][c] = sum_t,o dY[p + off_t][o] Wd[t][c][o] where x[p][c] > 0   (kDgrad; K = channels).
+// A workgroup walks kBwTH x kBwTW tiles. A tile of x (with its 1-pixel rim) and of dY (with the rim
+// when the data gradient reads it) lies in LDS as it does in memory, a pixel's channels contiguous;
+// the next tile is fetched into registers while the current one is multiplied. With kDgrad the
+// workgroup's waves 0-3 take the data gradient and waves 4-7 the weight gradient (one of each per
+// SIMD, 72 products each per tile), otherwise all eight the weight gradient.
+//   * data gradient: blocks of 32 columns x 2 rows as in the fused forward (an operand of an input
+//     row serves both output rows), each output a chain in tap order: bitwise the data gradient of
+//     conv3x3_kernel;
+//   * weight gradient: both operands are 8 consecutive pixels of one channel per lane, read by the
+//     LDS transpose read (ds_read_b64_tr_b16: 16 lanes address 4 pixels x 16 channels, each receives
+//     4 pixels of its channel). A row of x serves the dY rows above, at and below it. With 16 input
+//     channels a product takes two taps (columns 0-15 the first, 16-31 the second).
+// The last layer has three outputs: its dY may come with 4 channels per pixel (kDch = 4, 8 B in place
+// of 64), which are laid into the LDS tile's pixels, whose other channels stay zero.
+// Bound by memory: 805 MB for 4 x 1024^2 pixels of 32 + 32 channels, 174 us at a large copy's rate,
+// take 197 us (the separate data and weight gradients 176 + 165, reading both maps twice); the last
+// layer's thin dY 169, 16 input channels 99 (before 341 and 137). A thread's loads of a tile lie at
+// fixed distances (BwMap), so that fetching and staging a tile takes a few vector instructions per
+// load: with a division and a 64-bit address for each they took as long as the products (221 us).
+// Each workgroup's partial [9][32][KIN] (and the bias partial [32]) goes to global memory.
+constexpr int kBwTH = 16, kBwTW = 32;
+constexpr int kBwThreads = 512, kBwWaves = kBwThreads / 64;
 
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ const u32x4 kBwZeros = {0u, 0u, 0u, 0u};  // what a pixel outside the image reads
 
-// Channels 2m, 2m+1 of pixels p0 (x) and p1 (y) -> dwords (p0 c, p1 c) for c = 2m and 2m+1.
-__device__ __forceinline__ void pair_pack(const uint4& x, const uint4& y, uint4& lo, uint4& hi) {
-    lo.x = __builtin_amdgcn_perm(y.x, x.x, 0x05040100u);
-    lo.y = __builtin_amdgcn_perm(y.x, x.x, 0x07060302u);
-    lo.z = __builtin_amdgcn_perm(y.y, x.y, 0x05040100u);
-    lo.w = __builtin_amdgcn_perm(y.y, x.y, 0x07060302u);
-    hi.x = __builtin_amdgcn_perm(y.z, x.z, 0x05040100u);
-    hi.y = __builtin_amdgcn_perm(y.z, x.z, 0x07060302u);
-    hi.z = __builtin_amdgcn_perm(y.w, x.w, 0x05040100u);
-    hi.w = __builtin_amdgcn_perm(y.w, x.w, 0x07060302u);
+// One map's tile as a workgroup loads it, kChunks x 16 B per pixel: the 32 inner columns a few rows at a
+// time (all threads), then, with the rim, the two last rows and the rim's columns in one more load. A
+// row's bytes times the tile's rows stay below kBwRange; wider images are addressed pixel by pixel.
+constexpr unsigned kBwRange = 1u << 30;
+constexpr int kBwWide = (kBwRange >> 6) / (kBwTH + 2);  // widest row of 64 B pixels
+
+template <int kChunks, int kRim, int kStride>
+struct BwMap {
+    static constexpr int kStep = kBwThreads / (kBwTW * kChunks);  // rows per load
+    static constexpr int kFull = kBwTH / kStep, kLoads = kFull + kRim;
+    static constexpr int kCols = kBwTW + 2 * kRim;
+    static_assert(kFull * kStep == kBwTH, "whole loads");
+    static constexpr int kTail = 2 * kBwTW * kChunks, kSides = 2 * (kBwTH + 2) * kChunks;
+    static_assert(kTail + kSides <= kBwThreads, "one load for the rest");
+    int row, col, lrow, lcol, ch;  // this thread's first pixel, and its last load's
+    bool last;                     // it has one
+
+    __device__ __forceinline__ explicit BwMap(int tid) {
+        ch = tid % kChunks;
+        row = tid / (kBwTW * kChunks);
+        col = kRim + tid / kChunks % kBwTW;
+        const int i = (tid - kTail) / kChunks;  // of the rim's columns
+        const bool tail = tid < kTail;
+        lrow = tail ? kBwTH + row : i % (kBwTH + 2);
+        lcol = tail ? col : i < kBwTH + 2 ? 0 : kCols - 1;
+        last = tid < kTail + kSides;
+    }
+    __device__ __forceinline__ int lds() const { return (row * kCols + col) * kStride + ch * 16; }
+    __device__ __forceinline__ int lds_last() const { return (lrow * kCols + lcol) * kStride + ch * 16; }
+
+    // The tile at (y0, x0) of image img. Rows outside the image lie outside the buffer resource, and a
+    // column outside it is given an offset there: both read zeros.
+    __device__ __forceinline__ void fetch(const uint16_t* __restrict__ map, int img, int y0, int x0, int H, int W,
+                                          u32x4 (&regs)[kLoads]) const {
+        const int yb = max(y0 - kRim, 0), down = y0 - kRim - yb;  // -1: the tile's first row is above the image
+        const unsigned pitch = (unsigned)W * (16u * kChunks);
+        const uint64_t left = (uint64_t)(H - yb) * pitch;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(map) + ((size_t)img * H + yb) * W * (8 * kChunks), 0,
+            (int)(left < kBwRange ? (unsigned)left : kBwRange), 0x00020000);
+        auto offset = [&](int r, int c) {
+            const int gx = x0 - kRim + c;
+            return (unsigned)gx < (unsigned)W ? (unsigned)(r + down) * pitch + (unsigned)(gx * kChunks + ch) * 16u
+                                              : 2u * kBwRange;
+        };
+        const unsigned off = offset(row, col);
+#pragma unroll
+        for (int q = 0; q < kFull; ++q)
+            regs[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + (unsigned)(q * kStep) * pitch), 0, 0);
+        if constexpr (kRim != 0)
+            regs[kFull] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(last ? offset(lrow, lcol) : 2u * kBwRange), 0, 0);
+    }
+    __device__ __forceinline__ void commit(unsigned char* tile, const u32x4 (&regs)[kLoads]) const {
+        unsigned char* const at = tile + lds();
+#pragma unroll
+        for (int q = 0; q < kFull; ++q) *reinterpret_cast<u32x4*>(at + q * kStep * kCols * kStride) = regs[q];
+        if constexpr (kRim != 0)
+            if (last) *reinterpret_cast<u32x4*>(tile + lds_last()) = regs[kFull];
+    }
+};
+
+// A tile of a map with 4 channels (8 B) per pixel, one pixel per load.
+template <int kRim, int kStride>
+struct BwThinMap {
+    static constexpr int kCols = kBwTW + 2 * kRim, kPix = (kBwTH + 2 * kRim) * kCols;
+    static constexpr int kLoads = (kPix + kBwThreads - 1) / kBwThreads;
+    int tid;
+    __device__ __forceinline__ explicit BwThinMap(int t) : tid(t) {}
+    __device__ __forceinline__ void fetch(const uint16_t* __restrict__ map, int img, int y0, int x0, int H, int W,
+                                          u32x2 (&regs)[kLoads]) const {
+        const int yb = max(y0 - kRim, 0), down = y0 - kRim - yb;
+        const unsigned pitch = (unsigned)W * 8u;
+        const uint64_t left = (uint64_t)(H - yb) * pitch;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(map) + ((size_t)img * H + yb) * W * 4, 0,
+                                              (int)(left < kBwRange ? (unsigned)left : kBwRange), 0x00020000);
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            const int pix = tid + q * kBwThreads, r = pix / kCols, gx = x0 - kRim + pix % kCols;
+            const bool in = (pix < kPix) & ((unsigned)gx < (unsigned)W);
+            regs[q] = __builtin_amdgcn_raw_buffer_load_b64(
+                rs, (int)(in ? (unsigned)(r + down) * pitch + (unsigned)gx * 8u : 2u * kBwRange), 0, 0);
+        }
+    }
+    __device__ __forceinline__ void commit(unsigned char* tile, const u32x2 (&regs)[kLoads]) const {
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            const int pix = tid + q * kBwThreads;
+            if (pix < kPix) *reinterpret_cast<u32x2*>(tile + pix * kStride) = regs[q];
+        }
+    }
+};
+
+template <int KIN, bool kDgrad>
+struct BwLds {
+    static constexpr int kXStride = KIN * 2 + 16, kDStride = 64 + 16;  // bytes per pixel, spreads banks
+    static constexpr int kXCols = kBwTW + 2, kXPix = (kBwTH + 2) * kXCols;
+    static constexpr int kRim = kDgrad ? 1 : 0;
+    static constexpr int kDCols = kBwTW + 2 * kRim, kDPix = (kBwTH + 2 * kRim) * kDCols;
+    static constexpr int kXBytes = kXPix * kXStride, kDBytes = kDPix * kDStride;
+    static constexpr int kSum = 9 * 32 * 32 * 4;
+    static constexpr int kBytes = kXBytes + kDBytes;
+    static_assert(kBytes >= kSum + kBwWaves * 64 * 4, "the partial sums reuse the tile");
+};
+
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+
+// 8 pixels of one channel per lane from the LDS map whose lane's pixel and channels start at src.
+template <int kStride>
+__device__ __forceinline__ bf16x8 read_transposed(const unsigned char* src) {
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)src);
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(src + 4 * kStride));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-__device__ __forceinline__ bf16x8 as_bf16x8(unsigned a, unsigned b, unsigned c, unsigned d) {
-    return __builtin_bit_cast(bf16x8, (u32x4){a, b, c, d});
-}
-
-template <int KIN>
-__global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const uint16_t* __restrict__ x,
-                                                           const uint16_t* __restrict__ dy, int nimg, int H, int W,
-                                                           float* __restrict__ part_w, float* __restrict__ part_b) {
-    constexpr int G = KIN / 8;  // 8-channel groups of the input map
-    __shared__ __attribute__((aligned(16))) unsigned xs[kWgXRows * kWgXPairs * 32];
-    __shared__ __attribute__((aligned(16))) unsigned ds[kWgTH * kWgDPairs * 32];
-    __shared__ float red[kWgTH][2][32];
-    __shared__ float tapsum[3][32 * 32];
-    const int tiles_x = (W + kWgTW - 1) / kWgTW, tiles_y = (H + kWgTH - 1) / kWgTH;
-    const int tiles = tiles_x * tiles_y * nimg;
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+template <int KIN, bool kDgrad, int kDch, bool kWide>
+__global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __restrict__ x,
+                                                              const uint16_t* __restrict__ dy,
+                                                              const uint16_t* __restrict__ wd,
+                                                              uint16_t* __restrict__ dx, int nimg, int H, int W,
+                                                              float* __restrict__ part_w, float* __restrict__ part_b) {
+    static_assert(KIN == 32 || (KIN == 16 && !kDgrad), "data gradients exist for 32-channel inputs only");
+    using L = BwLds<KIN, kDgrad>;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[L::kBytes];
+    unsigned char* const xs = lds;
+    unsigned char* const ds = lds + L::kXBytes;
+    const int tiles_x = (W + kBwTW - 1) / kBwTW, tiles_y = (H + kBwTH - 1) / kBwTH;
+    const int per_img = tiles_x * tiles_y, total = per_img * nimg;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int half = lane / 32, j = lane % 32;
-    const int row = wave % kWgTH, ky = wave / kWgTH;  // this wave's tile row and tap row
-    const int first = blockIdx.x * kWgTiles;
-    const int ntiles = min(kWgTiles, tiles - first);
 
-    if constexpr (KIN < 32) {
-        // channels KIN .. 31 of the input rows stay zero: they are the B columns j >= KIN
-        for (int e = threadIdx.x; e < kWgXRows * kWgXPairs * 32; e += kWgThreads)
-            if (e % 32 >= KIN) xs[e] = 0u;
-    }
+    // workgroup b runs on XCD b % 8: each XCD walks a contiguous range of tiles, whose shared rims
+    // its L2 then holds
+    const int groups = gridDim.x, xcd = blockIdx.x % kXcds;
+    const int lead = min(groups, kXcds);  // XCDs in use
+    const int stride = groups / kXcds + (xcd < groups % kXcds ? 1 : 0);
+    const int first = (int)((int64_t)total * xcd / lead) + (int)blockIdx.x / kXcds;
+    const int last = (int)((int64_t)total * (xcd + 1) / lead);
 
-    // the tile's rows in registers: input items (row, pair, group) and dY items
-    uint4 rx[kWgXPer][2], rd[kWgDPer][2];
-    auto fetch = [&](int k) {
-        const int tile = first + k;
-        const int img = tile / (tiles_x * tiles_y);
-        const int tt = tile - img * tiles_x * tiles_y;
-        const int ty = tt / tiles_x, tx = tt - ty * tiles_x;
-        const int y0 = ty * kWgTH, x0 = tx * kWgTW;
-        const size_t img_off = (size_t)img * H * W;
-#pragma unroll
-        for (int i = 0; i < kWgXPer; ++i) {
-            const int e = threadIdx.x + kWgThreads * i;
-            const int g = e % 4, rq = e / 4;
-            const int r = rq / kWgXPairs, q = rq - r * kWgXPairs;
-            const int gy = y0 - 1 + r, gx = x0 - 1 + 2 * q;
-            const bool row_ok = e < kWgXItems && g < G && gy >= 0 && gy < H;
-            const uint4* src = reinterpret_cast<const uint4*>(x + (img_off + (size_t)gy * W + gx) * KIN) + g;
-            rx[i][0] = (row_ok && gx >= 0 && gx < W) ? src[0] : make_uint4(0u, 0u, 0u, 0u);
-            rx[i][1] = (row_ok && gx + 1 < W) ? src[G] : make_uint4(0u, 0u, 0u, 0u);
-        }
-#pragma unroll
-        for (int i = 0; i < kWgDPer; ++i) {
-            const int e = threadIdx.x + kWgThreads * i;
-            const int g = e % 4, rq = e / 4;
-            const int r = rq / kWgDPairs, q = rq - r * kWgDPairs;
-            const int gy = y0 + r, gx = x0 + 2 * q;
-            const bool row_ok = e < kWgDItems && gy < H;
-            const uint4* src = reinterpret_cast<const uint4*>(dy + (img_off + (size_t)gy * W + gx) * 32) + g;
-            rd[i][0] = (row_ok && gx < W) ? src[0] : make_uint4(0u, 0u, 0u, 0u);
-            rd[i][1] = (row_ok && gx + 1 < W) ? src[4] : make_uint4(0u, 0u, 0u, 0u);
-        }
+    struct Place {
+        int img, y0, x0;
     };
-    auto stage = [&]() {
-#pragma unroll
-        for (int i = 0; i < kWgXPer; ++i) {
-            const int e = threadIdx.x + kWgThreads * i;
-            const int g = e % 4, rq = e / 4;
-            if (e < kWgXItems && g < G) {
-                uint4 lo, hi;
-                pair_pack(rx[i][0], rx[i][1], lo, hi);
-                uint4* dst = reinterpret_cast<uint4*>(xs + rq * 32 + 8 * g);
-                dst[0] = lo;
-                dst[1] = hi;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kWgDPer; ++i) {
-            const int e = threadIdx.x + kWgThreads * i;
-            const int g = e % 4, rq = e / 4;
-            if (e < kWgDItems) {
-                uint4 lo, hi;
-                pair_pack(rd[i][0], rd[i][1], lo, hi);
-                uint4* dst = reinterpret_cast<uint4*>(ds + rq * 32 + 8 * g);
-                dst[0] = lo;
-                dst[1] = hi;
-            }
-        }
+    auto place = [&](int tile) {
+        const int img = tile / per_img, t = tile - img * per_img;
+        const int ty = t / tiles_x;
+        return Place{img, ty * kBwTH, (t - ty * tiles_x) * kBwTW};
     };
 
-    f32x16 acc[3];
+    using XMap = BwMap<KIN / 8, 1, L::kXStride>;
+    using DMap = std::conditional_t<kDch == 32, BwMap<4, L::kRim, L::kDStride>, BwThinMap<L::kRim, L::kDStride>>;
+    // The items' places are formed where they are used: kept across the loop they would not fit the
+    // registers beside the sums.
+    auto thread = [&]() {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    // A wide image's chunk at a time: one that lies outside the image reads kBwZeros.
+    auto each = [&](auto item, const uint16_t* map, const Place& p, auto chunks_c, auto rim_c, int e) {
+        using Item = decltype(item);
+        constexpr int kChunks = chunks_c.value, kRim = rim_c.value, kCols = kBwTW + 2 * kRim;
+        const int pix = e / kChunks, ch = e % kChunks, r = pix / kCols, c = pix % kCols;
+        const bool in = (r < kBwTH + 2 * kRim) & ((unsigned)(p.y0 - kRim + r) < (unsigned)H) &
+                        ((unsigned)(p.x0 - kRim + c) < (unsigned)W);
+        const Item* const base = reinterpret_cast<const Item*>(map) +
+                                 (((int64_t)p.img * H + p.y0 - kRim) * W + p.x0 - kRim) * kChunks;
+        const Item* const src = base + ((uint64_t)(unsigned)r * (unsigned)W * kChunks + (unsigned)(c * kChunks + ch));
+        return *(in ? src : reinterpret_cast<const Item*>(&kBwZeros));
+    };
+    constexpr int kXWide = (L::kXPix * (KIN / 8) + kBwThreads - 1) / kBwThreads;
+    constexpr int kDChunks = kDch == 32 ? 4 : 1, kDWide = (L::kDPix * kDChunks + kBwThreads - 1) / kBwThreads;
+    u32x4 rx[kWide ? kXWide : XMap::kLoads];
+    std::conditional_t<kDch == 32, u32x4, u32x2> rd[kWide ? kDWide : DMap::kLoads];
+    auto fetch = [&](int tile) {
+        const Place p = place(tile);
+        const int tid = thread();
+        constexpr std::integral_constant<int, KIN / 8> xchunks{};
+        constexpr std::integral_constant<int, kDChunks> dchunks{};
+        if constexpr (kWide) {
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
+            for (int q = 0; q < kXWide; ++q)
+                rx[q] = each(u32x4{}, x, p, xchunks, std::integral_constant<int, 1>{}, tid + q * kBwThreads);
+        } else {
+            XMap(tid).fetch(x, p.img, p.y0, p.x0, H, W, rx);
+        }
+        if constexpr (kWide) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-    float bsum = 0.f;  // bias gradient: channel j over this lane's pixels (tap row 0 only)
+            for (int q = 0; q < kDWide; ++q)
+                rd[q] = each(rd[0], dy, p, dchunks, std::integral_constant<int, L::kRim>{}, tid + q * kBwThreads);
+        } else {
+            DMap(tid).fetch(dy, p.img, p.y0, p.x0, H, W, rd);
+        }
+    };
+    auto commit = [&]() {
+        const int tid = thread();
+        if constexpr (kWide) {
+#pragma unroll
+            for (int q = 0; q < kXWide; ++q) {
+                const int e = tid + q * kBwThreads, pix = e / (KIN / 8);
+                if (pix < L::kXPix) *reinterpret_cast<u32x4*>(xs + pix * L::kXStride + e % (KIN / 8) * 16) = rx[q];
+            }
+        } else {
+            XMap(tid).commit(xs, rx);
+        }
+        if constexpr (kWide) {
+#pragma unroll
+            for (int q = 0; q < kDWide; ++q) {
+                const int e = tid + q * kBwThreads, pix = e / kDChunks;
+                if (pix < L::kDPix)
+                    *reinterpret_cast<std::remove_reference_t<decltype(rd[0])>*>(ds + pix * L::kDStride +
+                                                                                e % kDChunks * 16) = rd[q];
+            }
+        } else {
+            DMap(tid).commit(ds, rd);
+        }
+    };
 
-    if (ntiles > 0) fetch(0);
-    for (int k = 0; k < ntiles; ++k) {
-        __syncthreads();  // every wave is done with the previous tile
-        stage();
+    constexpr int kWgradWaves = kDgrad ? kBwWaves / 2 : kBwWaves;
+    float* const sums = reinterpret_cast<float*>(lds);               // [9][32][32], after the last tile
+    float* const bsums = reinterpret_cast<float*>(lds + L::kSum);    // [waves][64]
+
+    if constexpr (kDch < 32) {
+        for (int e = threadIdx.x; e < L::kDPix * 4; e += kBwThreads)
+            *reinterpret_cast<u32x4*>(ds + e / 4 * L::kDStride + e % 4 * 16) = (u32x4){0u, 0u, 0u, 0u};
         __syncthreads();
-        if (k + 1 < ntiles) fetch(k + 1);
-        // K steps of 16 pixels along the tile row; lane: pixels c0 .. c0 + 7
-#pragma unroll 2
-        for (int ks = 0; ks < kWgTW / 16; ++ks) {
-            const int q0 = ks * 8 + half * 4;  // pair of pixel c0 = 16 ks + 8 half
-            const unsigned* dq = ds + (row * kWgDPairs + q0) * 32 + j;
-            const unsigned a0 = dq[0], a1 = dq[32], a2 = dq[64], a3 = dq[96];
-            // input pixels c0 - 1 .. c0 + 8 of image row row + ky - 1 (pairs q0 .. q0 + 4)
-            const unsigned* xq = xs + ((row + ky) * kWgXPairs + q0) * 32 + j;
-            const unsigned d0 = xq[0], d1 = xq[32], d2 = xq[64], d3 = xq[96], d4 = xq[128];
-            const bf16x8 av = as_bf16x8(a0, a1, a2, a3);
-            if (ky == 0) {
-                bsum += __uint_as_float(a0 << 16);
-                bsum += __uint_as_float(a0 & 0xffff0000u);
-                bsum += __uint_as_float(a1 << 16);
-                bsum += __uint_as_float(a1 & 0xffff0000u);
-                bsum += __uint_as_float(a2 << 16);
-                bsum += __uint_as_float(a2 & 0xffff0000u);
-                bsum += __uint_as_float(a3 << 16);
-                bsum += __uint_as_float(a3 & 0xffff0000u);
-            }
-            const bf16x8 b0 = as_bf16x8(d0, d1, d2, d3);
-            const bf16x8 b1 = as_bf16x8(__builtin_amdgcn_alignbyte(d1, d0, 2), __builtin_amdgcn_alignbyte(d2, d1, 2),
-                                        __builtin_amdgcn_alignbyte(d3, d2, 2), __builtin_amdgcn_alignbyte(d4, d3, 2));
-            const bf16x8 b2 = as_bf16x8(d1, d2, d3, d4);
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b0, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b1, acc[1], 0, 0, 0);
-            acc[2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b2, acc[2], 0, 0, 0);
-        }
     }
-    // for each horizontal tap kx: the four tile rows of every tap row added in row order in
-    // LDS, then the three taps 3 ky + kx written out
-    float* out = part_w + (size_t)blockIdx.x * 9 * 32 * KIN;
+    if (first < last) fetch(first);
+    // Both roles pass the same barriers: one before and one after each commit, one before the sums
+    // and one after each wave's turn. Each commits in its own loop, so that a wave waits for its
+    // loads alone, not for its stores.
+    if (kDgrad && wave < kBwWaves / 2) {
+        bf16x8 a[9][2];
 #pragma unroll
-    for (int kx = 0; kx < 3; ++kx) {
-        for (int r = 0; r < kWgTH; ++r) {
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int kc = 0; kc < 2; ++kc)
+                a[t][kc] = *reinterpret_cast<const bf16x8*>(wd + ((size_t)t * 32 + j) * 32 + kc * 16 + half * 8);
+        __builtin_amdgcn_s_waitcnt(0);  // the weights: else the loop would wait for them, and the next tile
+        for (int tile = first; tile < last; tile += stride) {
             __syncthreads();
-            if (row == r) {
-                // acc[kx][e]: o = 8 (e / 4) + 4 half + e % 4, c = j
+            commit();
+            __syncthreads();
+            if (tile + stride < last) fetch(tile + stride);
+            const Place p = place(tile);
+            u32x4* const to = reinterpret_cast<u32x4*>(dx) + (((size_t)p.img * H + p.y0) * W + p.x0 + j) * 4 + half;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int o = 8 * (e / 4) + 4 * half + (e % 4);
-                    if (r == 0) tapsum[ky][o * 32 + j] = acc[kx][e];
-                    else tapsum[ky][o * 32 + j] += acc[kx][e];
+            for (int pair = 0; pair < 2; ++pair) {
+                const int ry = 4 * wave + 2 * pair;
+                const unsigned char* base = ds + (ry * L::kDCols + j) * L::kDStride + half * 16;
+                bf16x8 b[2][3][2];
+                auto read = [&](int i) {
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                        for (int kc = 0; kc < 2; ++kc)
+                            b[i & 1][kx][kc] = *reinterpret_cast<const bf16x8*>(
+                                base + (i * L::kDCols + kx) * L::kDStride + kc * 32);
+                };
+                f32x16 acc[2];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.f;
+                read(0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (i < 3) read(i + 1);
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                        for (int kc = 0; kc < 2; ++kc) {
+                            if (i < 3)
+                                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[3 * (i < 3 ? i : 0) + kx][kc],
+                                                                                 b[i & 1][kx][kc], acc[0], 0, 0, 0);
+                            if (i > 0)
+                                acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[3 * (i > 0 ? i - 1 : 0) + kx][kc],
+                                                                                 b[i & 1][kx][kc], acc[1], 0, 0, 0);
+                        }
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const unsigned char* m = xs + ((ry + i + 1) * L::kXCols + j + 1) * L::kXStride + half * 8;
+                    const bool in = p.y0 + ry + i < H && p.x0 + j < W;
+#pragma unroll
+                    for (int q = 0; q < 4; q += 2) {
+                        unsigned w[2][2];  // [group q, q + 1][pair of channels]
+#pragma unroll
+                        for (int g = 0; g < 2; ++g) {
+                            const uint2 mv = *reinterpret_cast<const uint2*>(m + (q + g) * 16);
+                            const unsigned mw[2] = {mv.x, mv.y};
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                const float lo = acc[i][4 * (q + g) + 2 * h], hi = acc[i][4 * (q + g) + 2 * h + 1];
+                                w[g][h] = f2bf2(__uint_as_float(mw[h] << 16) > 0.f ? lo : 0.f,
+                                                __uint_as_float(mw[h] & 0xffff0000u) > 0.f ? hi : 0.f);
+                            }
+                        }
+                        // exchanging halves of the wave gives each lane all 8 channels of group q + half
+                        const auto r0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+                        const auto r1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                        if (in) to[(size_t)(ry + i) * W * 4 + q] = (u32x4){r0[0], r1[0], r0[1], r1[1]};
+                    }
                 }
             }
         }
         __syncthreads();
-        for (int e = threadIdx.x; e < 3 * 32 * KIN; e += kWgThreads) {
-            const int yy = e / (32 * KIN), rem = e - yy * 32 * KIN;
-            const int o = rem / KIN, c = rem - o * KIN;
-            out[(size_t)(3 * yy + kx) * 32 * KIN + rem] = tapsum[yy][o * 32 + c];
+        for (int r = 0; r < kWgradWaves; ++r) __syncthreads();
+    } else {
+        constexpr int kRows = kBwTH / kWgradWaves;
+        constexpr int kAcc = KIN == 32 ? 9 : 5;
+        const int turn = kDgrad ? wave - kBwWaves / 2 : wave, row0 = turn * kRows;
+        // the lane's pixel and channels in a transpose read: 4 pixels x 16 channels per 16 lanes
+        const int tp = 8 * half + lane % 16 / 4, tc = 4 * (lane % 4), upper = lane / 16 % 2;
+        const unsigned char* const dbase =
+            ds + ((row0 + L::kRim) * L::kDCols + tp + L::kRim) * L::kDStride + (16 * upper + tc) * 2;
+        const unsigned char* const xbase =
+            xs + (row0 * L::kXCols + tp) * L::kXStride + (KIN == 32 ? 16 * upper + tc : tc) * 2;
+        f32x16 acc[kAcc];
+#pragma unroll
+        for (int t = 0; t < kAcc; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+        float bsum = 0.f;  // this lane's channel and pixels
+        auto read_d = [&](int d, int kb) {
+            const bf16x8 av = read_transposed<L::kDStride>(dbase + (d * L::kDCols + 16 * kb) * L::kDStride);
+            const u32x4 w = __builtin_bit_cast(u32x4, av);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                bsum += __uint_as_float(w[q] << 16);
+                bsum += __uint_as_float(w[q] & 0xffff0000u);
+            }
+            return av;
+        };
+        for (int tile = first; tile < last; tile += stride) {
+            __syncthreads();
+            commit();
+            __syncthreads();
+            if (tile + stride < last) fetch(tile + stride);
+#pragma unroll
+            for (int kb = 0; kb < kBwTW / 16; ++kb) {
+                if constexpr (KIN == 32) {
+                    bf16x8 av[kRows], b[2][3];
+                    auto read_x = [&](int r) {
+#pragma unroll
+                        for (int kx = 0; kx < 3; ++kx)
+                            b[r & 1][kx] =
+                                read_transposed<L::kXStride>(xbase + (r * L::kXCols + 16 * kb + kx) * L::kXStride);
+                    };
+                    read_x(0);
+#pragma unroll
+                    for (int r = 0; r < kRows + 2; ++r) {  // rows of x from the one below row0 on
+                        if (r < kRows) av[r < kRows ? r : 0] = read_d(r, kb);
+                        if (r + 1 < kRows + 2) read_x(r + 1);
+#pragma unroll
+                        for (int ky = 0; ky < 3; ++ky) {
+                            const int d = r - ky;
+                            if (d < 0 || d >= kRows) continue;
+#pragma unroll
+                            for (int kx = 0; kx < 3; ++kx)
+                                acc[3 * ky + kx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                    av[d < 0 || d >= kRows ? 0 : d], b[r & 1][kx], acc[3 * ky + kx], 0, 0, 0);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int d = 0; d < kRows; ++d) {
+                        const bf16x8 av = read_d(d, kb);
+#pragma unroll
+                        for (int q = 0; q < kAcc; ++q) {
+                            const int t0 = 2 * q, t1 = q + 1 < kAcc ? 2 * q + 1 : t0;  // taps of the two halves
+                            const int o0 = t0 / 3 * L::kXCols + t0 % 3, o1 = t1 / 3 * L::kXCols + t1 % 3;
+                            const bf16x8 b = read_transposed<L::kXStride>(
+                                xbase + (d * L::kXCols + 16 * kb + (upper ? o1 : o0)) * L::kXStride);
+                            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b, acc[q], 0, 0, 0);
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        // the waves' sums added in wave order: acc[t][e] is output 8 (e / 4) + 4 half + e % 4, column j
+#pragma unroll 1  // one copy of the code, in the instruction cache after the first wave's turn
+        for (int r = 0; r < kWgradWaves; ++r) {
+            if (r == turn) {
+#pragma unroll
+                for (int t = 0; t < kAcc; ++t) {
+                    float* const at = sums + (t * 32 + 4 * half) * 32 + j;
+                    float sum[16];  // a product's reads in flight together
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sum[e] = r == 0 ? 0.f : at[(8 * (e / 4) + e % 4) * 32];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) at[(8 * (e / 4) + e % 4) * 32] = sum[e] + acc[t][e];
+                }
+                bsums[turn * 64 + lane] = bsum;
+            }
+            __syncthreads();
         }
     }
-    if (ky == 0) red[row][half][j] = bsum;
-    __syncthreads();
+    float* const out = part_w + (size_t)blockIdx.x * 9 * 32 * KIN;
+    for (int e = threadIdx.x; e < 9 * 32 * KIN; e += kBwThreads) {
+        const int t = e / (32 * KIN), o = e / KIN % 32, c = e % KIN;
+        out[e] = KIN == 32 ? sums[e] : sums[(t / 2 * 32 + o) * 32 + t % 2 * 16 + c];
+    }
     if (threadIdx.x < 32) {
-        float b = 0.f;
-#pragma unroll
-        for (int r = 0; r < kWgTH; ++r) b += red[r][0][threadIdx.x] + red[r][1][threadIdx.x];
-        part_b[(size_t)blockIdx.x * 32 + threadIdx.x] = b;
+        float s = 0.f;
+        for (int r = 0; r < kWgradWaves; ++r) s += bsums[r * 64 + threadIdx.x] + bsums[r * 64 + 32 + threadIdx.x];
+        part_b[(size_t)blockIdx.x * 32 + threadIdx.x] = s;
     }
 }
 
@@ -840,36 +1079,73 @@ __global__ __launch_bounds__(kRedW* kRedSlices) void wgrad_reduce_kernel(const f
 
 // ------------------------------------------------------------------------------ mse_grad
 // out, target: FP32 planes [img][3][H][W]; mask: coarse water mask [img][H][W].
-// d_out (BF16 NHWC, 32 channels, 3..31 zero) = 2 act (out - target) * inv_n;
+// d_out (BF16 NHWC, kDch = 32 or 4 channels, 3.. zero) = 2 act (out - target) * inv_n;
 // partial[block] = sum act (out - target)^2.
+// Bound by memory: 4 x 1024^2 pixels take 24 us with 4 channels (138 MB). A lane takes a pixel; of
+// the 64 B that 32 channels take, the wave writes 16 pixels at a time, four lanes to a pixel (1 KB
+// contiguous per store). One lane writing its own pixel's four chunks, one pixel at a time and with
+// 64-bit divisions, took 136 us (372 MB).
+template <int kDch>
 __global__ __launch_bounds__(256) void mse_grad_kernel(const float* __restrict__ out, const float* __restrict__ target,
                                                        const uint8_t* __restrict__ mask, int nimg, int H, int W,
                                                        float inv_n, float ts0, float ts1, float ts2,
                                                        uint16_t* __restrict__ d_out, double* __restrict__ partial) {
     const float tscale[3] = {ts0, ts1, ts2};
     __shared__ double lds[256];
-    const size_t npix = (size_t)nimg * H * W;
+    const unsigned plane = (unsigned)H * W, npix = nimg * plane;  // < 2^31
+    const int lane = threadIdx.x % 64;
     double s = 0.0;
-    for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < npix; q += (size_t)gridDim.x * 256) {
-        const size_t img = q / ((size_t)H * W);
-        const size_t pin = q - img * H * W;
-        const int y = (int)(pin / W), x = (int)(pin - (size_t)y * W);
-        const uint8_t* m = mask + img * H * W;
-        const bool wet = m[pin] != 0;
-        const bool act[3] = {wet, wet && x + 1 < W && m[pin + 1] != 0, wet && y + 1 < H && m[pin + W] != 0};
-        uint16_t o[3];
+    // A wave takes 4 x 64 pixels at a time. No load depends on another, so that all are in flight
+    // together; whole waves stay in the loop: their lanes write each other's pixels.
+    constexpr int kPer = 4;
+    for (unsigned q0 = (blockIdx.x * 256 + threadIdx.x - lane) * kPer; q0 < npix; q0 += gridDim.x * 256 * kPer) {
+        float r[kPer][3];
+        unsigned m[kPer][3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const size_t f = (img * 3 + c) * H * W + pin;
-            const float r = act[c] ? out[f] - target[f] * tscale[c] : 0.f;
-            s += (double)r * (double)r;
-            o[c] = f2bf(2.f * r * inv_n);
+        for (int k = 0; k < kPer; ++k) {
+            const unsigned q = min(q0 + 64 * k + lane, npix - 1);
+            const unsigned img = q / plane, pin = q - img * plane;
+            const int y = (int)(pin / W), x = (int)(pin - (unsigned)y * W);
+            const uint8_t* const at = mask + (size_t)img * plane + pin;
+            const bool east = x + 1 < W, north = y + 1 < H;
+            m[k][0] = at[0];
+            m[k][1] = at[east ? 1 : 0];
+            m[k][2] = at[north ? W : 0];
+            if (!east) m[k][1] = 0;
+            if (!north) m[k][2] = 0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const size_t f = ((size_t)img * 3 + c) * plane + pin;
+                r[k][c] = out[f] - target[f] * tscale[c];
+            }
         }
-        uint4* dst = reinterpret_cast<uint4*>(d_out + q * 32);
-        dst[0] = make_uint4(o[0] | ((uint32_t)o[1] << 16), o[2], 0u, 0u);
-        dst[1] = make_uint4(0u, 0u, 0u, 0u);
-        dst[2] = make_uint4(0u, 0u, 0u, 0u);
-        dst[3] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const unsigned q = q0 + 64 * k + lane;
+            uint16_t g[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const bool act = q < npix && m[k][0] != 0 && (c == 0 || m[k][c] != 0);
+                const float e = act ? r[k][c] : 0.f;
+                s += (double)e * (double)e;
+                g[c] = f2bf(2.f * e * inv_n);
+            }
+            const uint2 o = make_uint2(g[0] | ((uint32_t)g[1] << 16), g[2]);
+            if constexpr (kDch == 4) {
+                if (q < npix) *reinterpret_cast<uint2*>(d_out + (size_t)q * 4) = o;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int from = 16 * i + lane / 4;
+                    const unsigned a = __shfl(o.x, from), b = __shfl(o.y, from);
+                    const bool head = lane % 4 == 0;
+                    const unsigned first = q0 + 64 * k + 16 * i;
+                    if (first + lane / 4 < npix)
+                        reinterpret_cast<uint4*>(d_out)[(size_t)first * 4 + lane] =
+                            make_uint4(head ? a : 0u, head ? b : 0u, 0u, 0u);
+                }
+            }
+        }
     }
     lds[threadIdx.x] = s;
     __syncthreads();
@@ -895,9 +1171,24 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* __restr
 }
 
 // ------------------------------------------------------------------------------ adam
+// BF16 working copies of weight i of one layer: forward Wk[t][n][k] and data-gradient Wd[t'][k][n] with
+// t' = 8 - t (flipped taps), from the FP32 master in forward layout [9][32][kin].
+__device__ __forceinline__ void cast_weight(float w, int i, int kin, int dkin, uint16_t* __restrict__ wk,
+                                            uint16_t* __restrict__ wd) {
+    const int t = i / (32 * kin), rem = i - t * 32 * kin;
+    const int n = rem / kin, k = rem - n * kin;
+    const uint16_t b = f2bf(w);
+    wk[i] = b;
+    // data gradient: output channels are the forward input channels k (32 of them, kin
+    // may be 16 or 32), reduced channels are the forward outputs n (dkin of them)
+    if (wd && n < dkin) wd[((size_t)(8 - t) * 32 + k) * dkin + n] = b;
+}
+
+// With copies, each updated weight is also laid out for the next forward and backward pass: a launch
+// of their own per layer would take longer than all of this kernel (four of 4.5 us beside 4.7 us).
 __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, const float* __restrict__ grad,
                                                    float* __restrict__ m, float* __restrict__ v, int n,
-                                                   AdamHyper hp) {
+                                                   AdamHyper hp, NetCopies copies) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float g = grad[i];
@@ -905,22 +1196,20 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, co
     const float vi = hp.beta2 * v[i] + (1.f - hp.beta2) * g * g;
     m[i] = mi;
     v[i] = vi;
-    theta[i] -= hp.lr * (mi * hp.inv_bc1) / (sqrtf(vi * hp.inv_bc2) + hp.eps);
+    const float w = theta[i] - hp.lr * (mi * hp.inv_bc1) / (sqrtf(vi * hp.inv_bc2) + hp.eps);
+    theta[i] = w;
+#pragma unroll
+    for (int l = 0; l < NetCopies::kMax; ++l) {
+        const int at = i - copies.begin[l];
+        if (l < copies.layers && at >= 0 && at < 9 * 32 * copies.cin[l])
+            cast_weight(w, at, copies.cin[l], 32, copies.wk[l], copies.wd[l]);
+    }
 }
 
-// BF16 working copies of one layer: forward Wk[t][n][k] and data-gradient Wd[t'][k][n] with
-// t' = 8 - t (flipped taps), from the FP32 master in forward layout [9][32][kin].
 __global__ __launch_bounds__(256) void cast_weights_kernel(const float* __restrict__ master, int kin, int dkin,
                                                            uint16_t* __restrict__ wk, uint16_t* __restrict__ wd) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 9 * 32 * kin) return;
-    const int t = i / (32 * kin), rem = i - t * 32 * kin;
-    const int n = rem / kin, k = rem - n * kin;
-    const uint16_t b = f2bf(master[i]);
-    wk[i] = b;
-    // data gradient: output channels are the forward input channels k (32 of them, kin
-    // may be 16 or 32), reduced channels are the forward outputs n (dkin of them)
-    if (wd && n < dkin) wd[((size_t)(8 - t) * 32 + k) * dkin + n] = b;
+    if (i < 9 * 32 * kin) cast_weight(master[i], i, kin, dkin, wk, wd);
 }
 
 // ------------------------------------------------------------------------------ correct
@@ -1061,7 +1350,7 @@ hipError_t launch_pack_input(const float* eta, const float* u, const float* v, c
 // Workgroups of `kernel` the current device holds at once (CUs x occupancy), cached per
 // device and kernel; 0 when the query fails.
 int resident_groups(const void* kernel, int threads) {
-    constexpr int kDevs = 16, kSlots = 8;
+    constexpr int kDevs = 16, kSlots = 16;
     static thread_local const void* keys[kDevs][kSlots] = {};
     static thread_local int vals[kDevs][kSlots] = {};
     int dev = 0;
@@ -1135,33 +1424,47 @@ hipError_t launch_conv3x3(int kin, int mode, const uint16_t* in, const uint16_t*
     return hipErrorInvalidValue;
 }
 
-int wgrad_chunks(int nimg, int H, int W) {
-    const int tiles = ((W + kWgTW - 1) / kWgTW) * ((H + kWgTH - 1) / kWgTH) * nimg;
-    return (tiles + kWgTiles - 1) / kWgTiles;
+int64_t backward_tiles(int nimg, int H, int W) {
+    return (int64_t)((W + kBwTW - 1) / kBwTW) * ((H + kBwTH - 1) / kBwTH) * nimg;
 }
 
-hipError_t launch_wgrad(int kin, const uint16_t* x, const uint16_t* dy, int nimg, int H, int W, float* part_w,
-                        float* part_b, float* dW, float* db, hipStream_t s) {
-    const int chunks = wgrad_chunks(nimg, H, W);
-    if (kin == 16)
-        hipLaunchKernelGGL(wgrad_kernel<16>, dim3(chunks), dim3(kWgThreads), 0, s, x, dy, nimg, H, W, part_w, part_b);
-    else if (kin == 32)
-        hipLaunchKernelGGL(wgrad_kernel<32>, dim3(chunks), dim3(kWgThreads), 0, s, x, dy, nimg, H, W, part_w, part_b);
-    else
-        return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+hipError_t launch_backward(int kin, const uint16_t* x, const uint16_t* dy, int dch, const uint16_t* wd, uint16_t* dx,
+                           int nimg, int H, int W, float* part, int max_parts, float* dW, float* db, hipStream_t s) {
+    if (max_parts < 1) return hipErrorInvalidValue;
+    const int64_t tiles = backward_tiles(nimg, H, W);
     const int nw = 9 * 32 * kin;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((nw + 32 + kRedW - 1) / kRedW), dim3(kRedW * kRedSlices), 0, s, part_w,
-                       part_b, chunks, nw, dW, db);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        int groups = resident_groups(reinterpret_cast<const void*>(kernel), kBwThreads);
+        if (groups < 1) return hipErrorInvalidDeviceFunction;
+        if (groups > max_parts) groups = max_parts;
+        if (groups > tiles) groups = (int)tiles;
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(kBwThreads), 0, s, x, dy, wd, dx, nimg, H, W, part,
+                           part + (size_t)groups * nw);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((nw + 32 + kRedW - 1) / kRedW), dim3(kRedW * kRedSlices), 0, s,
+                           part, part + (size_t)groups * nw, groups, nw, dW, db);
+        return hipGetLastError();
+    };
+    const bool wide = W > kBwWide;
+    if (dch == 4) {
+        if (kin != 32 || !dx) return hipErrorInvalidValue;
+        return wide ? go(&backward_kernel<32, true, 4, true>) : go(&backward_kernel<32, true, 4, false>);
+    }
+    if (kin == 16 && !dx)
+        return wide ? go(&backward_kernel<16, false, 32, true>) : go(&backward_kernel<16, false, 32, false>);
+    if (kin == 32 && dx)
+        return wide ? go(&backward_kernel<32, true, 32, true>) : go(&backward_kernel<32, true, 32, false>);
+    if (kin == 32)
+        return wide ? go(&backward_kernel<32, false, 32, true>) : go(&backward_kernel<32, false, 32, false>);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_mse_grad(const float* out, const float* target, const uint8_t* mask, int nimg, int H, int W,
-                           float inv_n, const float* tscale, uint16_t* d_out, double* partial, int nblocks,
+                           float inv_n, const float* tscale, uint16_t* d_out, int dch, double* partial, int nblocks,
                            double* loss, hipStream_t s) {
-    hipLaunchKernelGGL(mse_grad_kernel, dim3(nblocks), dim3(256), 0, s, out, target, mask, nimg, H, W, inv_n,
-                       tscale[0], tscale[1], tscale[2], d_out, partial);
+    hipLaunchKernelGGL((dch == 4 ? mse_grad_kernel<4> : mse_grad_kernel<32>), dim3(nblocks), dim3(256), 0, s, out,
+                       target, mask, nimg, H, W, inv_n, tscale[0], tscale[1], tscale[2], d_out, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, partial, nblocks, loss);
@@ -1169,8 +1472,8 @@ hipError_t launch_mse_grad(const float* out, const float* target, const uint8_t*
 }
 
 hipError_t launch_adam(float* theta, const float* grad, float* m, float* v, int n, const AdamHyper& hp,
-                       hipStream_t s) {
-    hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, s, theta, grad, m, v, n, hp);
+                       const NetCopies& copies, hipStream_t s) {
+    hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, s, theta, grad, m, v, n, hp, copies);
     return hipGetLastError();
 }
 

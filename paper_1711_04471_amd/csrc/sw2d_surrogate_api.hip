@@ -83,6 +83,57 @@ int advance_corrected(sw2d_t coarse, hipStream_t s, int nx, int ny, int32_t nste
     return SW2D_OK;
 }
 
+bool adam_hyper(int32_t t, float lr, float beta1, float beta2, float eps, AdamHyper* hp) {
+    if (t < 1) return false;
+    if (!(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f) || !(eps > 0.f) || !(lr >= 0.f)) return false;
+    hp->lr = lr;
+    hp->beta1 = beta1;
+    hp->beta2 = beta2;
+    hp->eps = eps;
+    hp->inv_bc1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)t)));
+    hp->inv_bc2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t)));
+    return true;
+}
+
+size_t partial_bytes(int cin) { return (9 * 32 * (size_t)cin + 32) * sizeof(float); }
+
+// The fewest partials a caller may bring room for: one per eight 4 x 128 pixel blocks.
+int64_t least_partials(int nimg, int ny, int nx) {
+    return ((int64_t)((nx + 127) / 128) * ((ny + 3) / 4) * nimg + 7) / 8;
+}
+
+// Partials of a weight gradient that the workspace is sized for: one per 4096 pixels or per tile of
+// the backward kernel, up to one workgroup per CU.
+int64_t partials(int nimg, int ny, int nx) {
+    const int64_t tiles = backward_tiles(nimg, ny, nx), groups = tiles < kCus ? tiles : kCus;
+    const int64_t least = least_partials(nimg, ny, nx);
+    return least > groups ? least : groups;
+}
+
+int backward(const uint16_t* x, int cin, const uint16_t* dy, int dch, const uint16_t* wd, uint16_t* dx, int nimg, int ny, int nx,
+             float* dW, float* db, void* work, size_t work_bytes, void* stream, const char* what) {
+    if ((cin != 16 && cin != 32) || !dims_ok(nimg, ny, nx)) return SW2D_EINVAL;
+    if (work_bytes < (size_t)least_partials(nimg, ny, nx) * partial_bytes(cin)) return SW2D_ENOSPC;
+    const size_t fit = work_bytes / partial_bytes(cin);
+    return fail(launch_backward(cin, x, dy, dch, wd, dx, nimg, ny, nx, static_cast<float*>(work),
+                                fit < (1 << 20) ? (int)fit : 1 << 20, dW, db, static_cast<hipStream_t>(stream)),
+                what);
+}
+
+int mse_grad(const float* out, const float* target, const float* target_scale, const uint8_t* mask, int nimg, int ny,
+             int nx, float inv_n, uint16_t* d_out, int dch, double* loss_sum, void* work, size_t work_bytes,
+             void* stream, const char* what) {
+    if (!out || !target || !target_scale || !mask || !d_out || !loss_sum || !work || !aligned16(d_out))
+        return SW2D_EINVAL;
+    if (!dims_ok(nimg, ny, nx) || !(inv_n >= 0.f) || !std::isfinite(inv_n)) return SW2D_EINVAL;
+    for (int c = 0; c < 3; ++c)
+        if (!std::isfinite(target_scale[c])) return SW2D_EINVAL;
+    if (work_bytes < kMseBlocks * sizeof(double)) return SW2D_ENOSPC;
+    return fail(launch_mse_grad(out, target, mask, nimg, ny, nx, inv_n, target_scale, d_out, dch,
+                                static_cast<double*>(work), kMseBlocks, loss_sum, static_cast<hipStream_t>(stream)),
+                what);
+}
+
 }  // namespace
 
 extern "C" {
@@ -220,21 +271,23 @@ int sw2d_conv3x3_dgrad(const uint16_t* dy, const uint16_t* wd, const uint16_t* a
 
 size_t sw2d_wgrad_workspace_bytes(int32_t cin, int32_t nimg, int32_t ny, int32_t nx) {
     if ((cin != 16 && cin != 32) || !dims_ok(nimg, ny, nx)) return 0;
-    const size_t chunks = (size_t)wgrad_chunks(nimg, ny, nx);
-    return chunks * (9 * 32 * (size_t)cin + 32) * sizeof(float);
+    return (size_t)partials(nimg, ny, nx) * partial_bytes(cin);
 }
 
 int sw2d_conv3x3_wgrad(const uint16_t* x, int32_t cin, const uint16_t* dy, int32_t nimg, int32_t ny, int32_t nx,
                        float* dW, float* db, void* work, size_t work_bytes, void* stream) {
     if (!x || !dy || !dW || !db || !work || !aligned16(x) || !aligned16(dy) || !aligned16(work)) return SW2D_EINVAL;
-    const size_t need = sw2d_wgrad_workspace_bytes(cin, nimg, ny, nx);
-    if (need == 0) return SW2D_EINVAL;
-    if (work_bytes < need) return SW2D_ENOSPC;
-    const size_t chunks = (size_t)wgrad_chunks(nimg, ny, nx);
-    float* part_w = static_cast<float*>(work);
-    float* part_b = part_w + chunks * 9 * 32 * cin;
-    return fail(launch_wgrad(cin, x, dy, nimg, ny, nx, part_w, part_b, dW, db, static_cast<hipStream_t>(stream)),
-                "sw2d_conv3x3_wgrad");
+    return backward(x, cin, dy, 32, nullptr, nullptr, nimg, ny, nx, dW, db, work, work_bytes, stream, "sw2d_conv3x3_wgrad");
+}
+
+int sw2d_conv3x3_backward(const uint16_t* x, const uint16_t* dy, int32_t dy_channels, const uint16_t* wd, uint16_t* dx,
+                          int32_t nimg, int32_t ny, int32_t nx, float* dW, float* db, void* work, size_t work_bytes, void* stream) {
+    if (!x || !dy || !wd || !dx || !dW || !db || !work || !aligned16(x) || !aligned16(dy) || !aligned16(wd) ||
+        !aligned16(dx) || !aligned16(work))
+        return SW2D_EINVAL;
+    if (dy_channels != 32 && dy_channels != 4) return SW2D_EINVAL;
+    if (dx == x || dx == dy) return SW2D_EINVAL;  // neighbouring tiles still read them
+    return backward(x, 32, dy, dy_channels, wd, dx, nimg, ny, nx, dW, db, work, work_bytes, stream, "sw2d_conv3x3_backward");
 }
 
 size_t sw2d_mse_workspace_bytes(void) { return kMseBlocks * sizeof(double); }
@@ -242,15 +295,15 @@ size_t sw2d_mse_workspace_bytes(void) { return kMseBlocks * sizeof(double); }
 int sw2d_mse_grad(const float* out, const float* target, const float* target_scale, const uint8_t* mask,
                   int32_t nimg, int32_t ny, int32_t nx, float inv_n, uint16_t* d_out, double* loss_sum, void* work,
                   size_t work_bytes, void* stream) {
-    if (!out || !target || !target_scale || !mask || !d_out || !loss_sum || !work || !aligned16(d_out))
-        return SW2D_EINVAL;
-    if (!dims_ok(nimg, ny, nx) || !(inv_n >= 0.f) || !std::isfinite(inv_n)) return SW2D_EINVAL;
-    for (int c = 0; c < 3; ++c)
-        if (!std::isfinite(target_scale[c])) return SW2D_EINVAL;
-    if (work_bytes < sw2d_mse_workspace_bytes()) return SW2D_ENOSPC;
-    return fail(launch_mse_grad(out, target, mask, nimg, ny, nx, inv_n, target_scale, d_out,
-                                static_cast<double*>(work), kMseBlocks, loss_sum, static_cast<hipStream_t>(stream)),
-                "sw2d_mse_grad");
+    return mse_grad(out, target, target_scale, mask, nimg, ny, nx, inv_n, d_out, 32, loss_sum, work, work_bytes, stream,
+                    "sw2d_mse_grad");
+}
+
+int sw2d_mse_grad4(const float* out, const float* target, const float* target_scale, const uint8_t* mask,
+                   int32_t nimg, int32_t ny, int32_t nx, float inv_n, uint16_t* d_out, double* loss_sum, void* work,
+                   size_t work_bytes, void* stream) {
+    return mse_grad(out, target, target_scale, mask, nimg, ny, nx, inv_n, d_out, 4, loss_sum, work, work_bytes, stream,
+                    "sw2d_mse_grad4");
 }
 
 int sw2d_sub3(const float* a0, const float* a1, const float* a2, const float* b0, const float* b1, const float* b2,
@@ -272,17 +325,30 @@ int sw2d_moments(const float* x, const uint8_t* mask, int64_t n, double* out2, v
 
 int sw2d_adam(float* theta, const float* grad, float* m, float* v, int32_t n, int32_t t, float lr, float beta1,
               float beta2, float eps, void* stream) {
-    if (!theta || !grad || !m || !v || n < 1 || t < 1) return SW2D_EINVAL;
-    if (!(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f) || !(eps > 0.f) || !(lr >= 0.f))
-        return SW2D_EINVAL;
     AdamHyper hp;
-    hp.lr = lr;
-    hp.beta1 = beta1;
-    hp.beta2 = beta2;
-    hp.eps = eps;
-    hp.inv_bc1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)t)));
-    hp.inv_bc2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t)));
-    return fail(launch_adam(theta, grad, m, v, n, hp, static_cast<hipStream_t>(stream)), "sw2d_adam");
+    if (!theta || !grad || !m || !v || n < 1 || !adam_hyper(t, lr, beta1, beta2, eps, &hp)) return SW2D_EINVAL;
+    return fail(launch_adam(theta, grad, m, v, n, hp, NetCopies{}, static_cast<hipStream_t>(stream)), "sw2d_adam");
+}
+
+int sw2d_adam_net(float* theta, const float* grad, float* m, float* v, int32_t layers, const int32_t* cin, int32_t t,
+                  float lr, float beta1, float beta2, float eps, uint16_t* const* wk, uint16_t* const* wd,
+                  void* stream) {
+    AdamHyper hp;
+    if (!theta || !grad || !m || !v || !cin || !wk || !wd || !adam_hyper(t, lr, beta1, beta2, eps, &hp))
+        return SW2D_EINVAL;
+    if (layers < 1 || layers > NetCopies::kMax) return SW2D_EINVAL;
+    NetCopies c{};
+    int n = 0;
+    for (int l = 0; l < layers; ++l) {
+        if ((cin[l] != 16 && cin[l] != 32) || !wk[l] || (wd[l] && cin[l] != 32)) return SW2D_EINVAL;
+        c.begin[l] = n;
+        c.cin[l] = cin[l];
+        c.wk[l] = wk[l];
+        c.wd[l] = wd[l];
+        n += 9 * 32 * cin[l] + 32;
+    }
+    c.layers = layers;
+    return fail(launch_adam(theta, grad, m, v, n, hp, c, static_cast<hipStream_t>(stream)), "sw2d_adam_net");
 }
 
 int sw2d_cast_weights(const float* master, int32_t cin, uint16_t* wk, uint16_t* wd, void* stream) {

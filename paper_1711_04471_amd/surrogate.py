@@ -170,31 +170,36 @@ class ConvNet:
         check(self.lib.sw2d_conv3x3_correct(_p(hidden), _p(self.wk[3]), _p(self.weight(3)[1]), tstd_ptr, _p(mask),
                                             _p(eta), _p(u), _p(v), w, h, self.stream()), "sw2d_conv3x3_correct")
 
-    def backward(self, x16, d_out, n, h, w, work):
-        """Gradients of every layer into self.grad, for dL/dout = d_out (BF16 NHWC, 32 ch)."""
+    def backward(self, x16, d_out, n, h, w, work, channels=32):
+        """Gradients of every layer into self.grad, for dL/dout = d_out (BF16 NHWC with
+        32 or 4 channels per pixel)."""
         _, acts, _, dz = self._buffers(n, h, w)
         s = self.stream()
-        dy = d_out
+        dy, dy_channels = d_out, channels
         layer_in = [x16, acts[0], acts[1], acts[2]]
         for layer in range(3, -1, -1):
             gw, gb = self.weight(layer, "grad")
             cin = CIN[layer]
             need = self.lib.sw2d_wgrad_workspace_bytes(cin, n, h, w)
             assert need <= work.numel()
-            check(self.lib.sw2d_conv3x3_wgrad(_p(layer_in[layer]), cin, _p(dy), n, h, w, _p(gw), _p(gb),
-                                              _p(work), work.numel(), s), "sw2d_conv3x3_wgrad")
             if layer > 0:
                 dx = dz[layer % 2]
-                check(self.lib.sw2d_conv3x3_dgrad(_p(dy), _p(self.wd[layer]), _p(layer_in[layer]), _p(dx),
-                                                  n, h, w, s), "sw2d_conv3x3_dgrad")
-                dy = dx
+                check(self.lib.sw2d_conv3x3_backward(_p(layer_in[layer]), _p(dy), dy_channels, _p(self.wd[layer]),
+                                                     _p(dx), n, h, w, _p(gw), _p(gb), _p(work), work.numel(), s),
+                      "sw2d_conv3x3_backward")
+                dy, dy_channels = dx, 32
+            else:
+                check(self.lib.sw2d_conv3x3_wgrad(_p(layer_in[layer]), cin, _p(dy), n, h, w, _p(gw), _p(gb),
+                                                  _p(work), work.numel(), s), "sw2d_conv3x3_wgrad")
 
     def adam(self, lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8):
         self.t += 1
-        check(self.lib.sw2d_adam(_p(self.theta), _p(self.grad), _p(self.m), _p(self.v), self.n_params, self.t,
-                                 ctypes.c_float(lr), ctypes.c_float(beta1), ctypes.c_float(beta2),
-                                 ctypes.c_float(eps), self.stream()), "sw2d_adam")
-        self.cast()
+        cin = (ctypes.c_int32 * 4)(*CIN)
+        wk = (ctypes.c_void_p * 4)(*[t.data_ptr() for t in self.wk])
+        wd = (ctypes.c_void_p * 4)(*[None if t is None else t.data_ptr() for t in self.wd])
+        check(self.lib.sw2d_adam_net(_p(self.theta), _p(self.grad), _p(self.m), _p(self.v), 4, cin, self.t,
+                                     ctypes.c_float(lr), ctypes.c_float(beta1), ctypes.c_float(beta2),
+                                     ctypes.c_float(eps), wk, wd, self.stream()), "sw2d_adam_net")
 
     def state_dict(self):
         return {"theta": self.theta.detach().cpu(), "stats": self.stats, "t": self.t}
@@ -375,7 +380,7 @@ class Trainer:
         self.x16 = torch.empty((batch, ny, nx, 16), dtype=torch.bfloat16, device=self.dev)
         self.tgt = torch.empty((batch, 3, ny, nx), dtype=torch.float32, device=self.dev)
         self.msk = torch.empty((batch, ny, nx), dtype=torch.uint8, device=self.dev)
-        self.dout = torch.empty((batch, ny, nx, 32), dtype=torch.bfloat16, device=self.dev)
+        self.dout = torch.empty((batch, ny, nx, 4), dtype=torch.bfloat16, device=self.dev)
         need = max(self.lib.sw2d_wgrad_workspace_bytes(c, batch, ny, nx) for c in (16, 32))
         self.work = torch.empty(need, dtype=torch.uint8, device=self.dev)
         self.mse_work = torch.empty(self.lib.sw2d_mse_workspace_bytes(), dtype=torch.uint8, device=self.dev)
@@ -412,10 +417,10 @@ class Trainer:
         n = len(idxs)
         n_act = sum(self._pack(j, int(i)) for j, i in enumerate(idxs))
         out = self.net.forward(self.x16, n, self.ny, self.nx)
-        check(self.lib.sw2d_mse_grad(_p(out), _p(self.tgt), self._tp, _p(self.msk), n, self.ny, self.nx,
-                                     ctypes.c_float(1.0 / n_act), _p(self.dout), _p(self.loss), _p(self.mse_work),
-                                     self.mse_work.numel(), self.net.stream()), "sw2d_mse_grad")
-        self.net.backward(self.x16, self.dout, n, self.ny, self.nx, self.work)
+        check(self.lib.sw2d_mse_grad4(_p(out), _p(self.tgt), self._tp, _p(self.msk), n, self.ny, self.nx,
+                                      ctypes.c_float(1.0 / n_act), _p(self.dout), _p(self.loss), _p(self.mse_work),
+                                      self.mse_work.numel(), self.net.stream()), "sw2d_mse_grad4")
+        self.net.backward(self.x16, self.dout, n, self.ny, self.nx, self.work, channels=4)
         return n_act
 
     def fit(self, epochs=1, lr=1e-3, seed=0, log=None, train_idx=None, decay=True):
