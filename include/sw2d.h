@@ -416,6 +416,12 @@ int sw2d_conv3x3_correct(const uint16_t *in, const uint16_t *wk, const float *bi
                          const uint8_t *mask, float *eta, float *u, float *v, int32_t nx, int32_t ny,
                          void *stream);
 
+/* The network's training forward: layers as sw2d_conv3x3_fwd one after another (bitwise), from the
+ * packed input x16 (BF16 NHWC 16 channels) through acts[0..2] (BF16 NHWC 32 channels each, kept for
+ * the backward) to the FP32 planes out [nimg][3][ny][nx]. wk, bias: the four layers' working copies. */
+int sw2d_cnn_forward_train(const uint16_t *x16, const uint16_t *const *wk, const float *const *bias,
+                           uint16_t *const *acts, float *out, int32_t nimg, int32_t ny, int32_t nx, void *stream);
+
 /* Data gradient of a layer with 32 inputs: dx[p][c] = (act_in[p][c] > 0) *
  * sum_t sum_o dy[p - off_t][o] W[t][o][c], i.e. the gradient through the convolution and
  * through the ReLU that produced the layer input act_in. dy, act_in, dx: BF16 NHWC 32

@@ -106,6 +106,7 @@ SIGNATURES = {
                          [ctypes.c_int32] * 3 + [_vp]),
     "sw2d_conv3x3_dgrad": (ctypes.c_int, [_vp] * 4 + [ctypes.c_int32] * 3 + [_vp]),
     "sw2d_wgrad_workspace_bytes": (ctypes.c_size_t, [ctypes.c_int32] * 4),
+    "sw2d_cnn_forward_train": (ctypes.c_int, [_vp, _pp, _pp, _pp, _vp] + [ctypes.c_int32] * 3 + [_vp]),
     "sw2d_conv3x3_backward": (ctypes.c_int, [_vp, _vp, ctypes.c_int32, _vp, _vp] + [ctypes.c_int32] * 3 +
                               [_vp, _vp, _vp, ctypes.c_size_t, _vp]),
     "sw2d_conv3x3_wgrad": (ctypes.c_int, [_vp, ctypes.c_int32, _vp] + [ctypes.c_int32] * 3 +

@@ -69,6 +69,11 @@ hipError_t launch_cnn_fused(const RawIn& raw, const InputNorm& nrm, const FusedN
 hipError_t launch_conv3x3(int kin, int mode, const uint16_t* in, const uint16_t* Wk, const float* bias,
                           uint16_t* out_bf, float* out_f, const uint16_t* relu_src, int nimg, int H, int W,
                           hipStream_t s);
+// The training forward, two layers per launch: x16 -> acts[0..2] and the FP32 planes out. W must pass
+// forward_pairs_ok.
+bool forward_pairs_ok(int W);
+hipError_t launch_forward_pairs(const uint16_t* x16, const FusedNet& net, uint16_t* const* acts, float* out, int nimg,
+                                int H, int W, hipStream_t s);
 // A layer's gradients: dW, db and, with dx (32 channels), the data gradient masked by x > 0. part:
 // max_parts partials of 9 * 32 * kin + 32 floats, as many workgroups at most. dch: dY's channels per
 // pixel (32, or 4 with dx).

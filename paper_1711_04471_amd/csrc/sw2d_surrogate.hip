@@ -607,6 +607,293 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
     }
 }
 
+// ------------------------------------------------------------------------------ training tiles
+// The kernels of a training step walk kBwTH x kBwTW tiles, kBwThreads threads to a workgroup.
+constexpr int kBwTH = 16, kBwTW = 32;
+constexpr int kBwThreads = 512, kBwWaves = kBwThreads / 64;
+
+// One map's tile with a rim of kRim pixels as a workgroup loads it, kChunks x 16 B per pixel: the 32
+// inner columns a few rows at a time (all threads), then what rows are left and the rim's columns in
+// one more load. A row's bytes times the tile's rows stay below kBwRange; wider images take other
+// kernels.
+constexpr unsigned kBwRange = 1u << 30;
+constexpr int kBwWide = (kBwRange >> 6) / (kBwTH + 4);  // widest row of 64 B pixels
+
+template <int kChunks, int kRim, int kStride>
+struct BwMap {
+    static constexpr int kRows = kBwTH + 2 * kRim, kCols = kBwTW + 2 * kRim;
+    static constexpr int kStep = kBwThreads / (kBwTW * kChunks);  // rows per load
+    static constexpr int kFull = kRows / kStep;
+    static constexpr int kTail = kRows % kStep * kBwTW * kChunks, kSides = 2 * kRim * kRows * kChunks;
+    static constexpr int kLoads = kFull + (kTail + kSides > 0 ? 1 : 0);
+    static_assert(kTail + kSides <= kBwThreads, "one load for the rest");
+    int row, col, lrow, lcol, ch;  // this thread's first pixel, and its last load's
+    bool last;                     // it has one
+
+    __device__ __forceinline__ explicit BwMap(int tid) {
+        ch = tid % kChunks;
+        row = tid / (kBwTW * kChunks);
+        col = kRim + tid / kChunks % kBwTW;
+        const int i = (tid - kTail) / kChunks, side = i / kRows;  // of the rim's columns
+        const bool tail = tid < kTail;
+        lrow = tail ? kFull * kStep + row : i % kRows;
+        lcol = tail ? col : side < kRim ? side : kBwTW + side;
+        last = tid < kTail + kSides;
+    }
+
+    // The tile at (y0, x0) of image img. Rows outside the image lie outside the buffer resource, and a
+    // column outside it is given an offset there: both read zeros.
+    __device__ __forceinline__ void fetch(const uint16_t* __restrict__ map, int img, int y0, int x0, int H, int W,
+                                          u32x4 (&regs)[kLoads]) const {
+        const int yb = max(y0 - kRim, 0), down = y0 - kRim - yb;  // < 0: the tile starts above the image
+        const unsigned pitch = (unsigned)W * (16u * kChunks);
+        const uint64_t left = (uint64_t)(H - yb) * pitch;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t*>(map) + ((size_t)img * H + yb) * W * (8 * kChunks), 0,
+            (int)(left < kBwRange ? (unsigned)left : kBwRange), 0x00020000);
+        auto offset = [&](int r, int c) {
+            const int gx = x0 - kRim + c;
+            return (unsigned)gx < (unsigned)W ? (unsigned)(r + down) * pitch + (unsigned)(gx * kChunks + ch) * 16u
+                                              : 2u * kBwRange;
+        };
+        const unsigned off = offset(row, col);
+#pragma unroll
+        for (int q = 0; q < kFull; ++q)
+            regs[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + (unsigned)(q * kStep) * pitch), 0, 0);
+        if constexpr (kLoads > kFull)
+            regs[kFull] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(last ? offset(lrow, lcol) : 2u * kBwRange), 0, 0);
+    }
+    __device__ __forceinline__ void commit(unsigned char* tile, const u32x4 (&regs)[kLoads]) const {
+        unsigned char* const at = tile + (row * kCols + col) * kStride + ch * 16;
+#pragma unroll
+        for (int q = 0; q < kFull; ++q) *reinterpret_cast<u32x4*>(at + q * kStep * kCols * kStride) = regs[q];
+        if constexpr (kLoads > kFull)
+            if (last) *reinterpret_cast<u32x4*>(tile + (lrow * kCols + lcol) * kStride + ch * 16) = regs[kFull];
+    }
+};
+
+// The tiles of a workgroup of a persistent grid. Workgroup b runs on XCD b % 8: each XCD walks a
+// contiguous range of tiles, whose shared rims its L2 then holds.
+struct BwWalk {
+    int tiles_x, per_img, first, last, stride;
+    __device__ __forceinline__ BwWalk(int nimg, int H, int W) {
+        tiles_x = (W + kBwTW - 1) / kBwTW;
+        per_img = tiles_x * ((H + kBwTH - 1) / kBwTH);
+        const int total = per_img * nimg, groups = gridDim.x, xcd = blockIdx.x % kXcds;
+        const int lead = min(groups, kXcds);  // XCDs in use
+        stride = groups / kXcds + (xcd < groups % kXcds ? 1 : 0);
+        first = (int)((int64_t)total * xcd / lead) + (int)blockIdx.x / kXcds;
+        last = (int)((int64_t)total * (xcd + 1) / lead);
+    }
+    struct Place {
+        int img, y0, x0;
+    };
+    __device__ __forceinline__ Place place(int tile) const {
+        const int img = tile / per_img, t = tile - img * per_img;
+        const int ty = t / tiles_x;
+        return Place{img, ty * kBwTH, (t - ty * tiles_x) * kBwTW};
+    }
+};
+
+// Two output rows of 32 pixels from an LDS map of kCols pixels per row: the lane's pixel of the upper
+// row starts at base, kIn / 16 16-channel chunks each. Each output is a chain in tap order; an input
+// row's operands serve both. weight(t, kc) is the A operand.
+template <int KIN, int kCols, int kStride, typename Weight>
+__device__ __forceinline__ void two_rows(const unsigned char* base, Weight&& weight, f32x16& up, f32x16& low) {
+    constexpr int kK = KIN / 16;
+    bf16x8 b[2][3][kK];
+    auto read = [&](int i) {
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+            for (int kc = 0; kc < kK; ++kc)
+                b[i & 1][kx][kc] = *reinterpret_cast<const bf16x8*>(base + (i * kCols + kx) * kStride + kc * 32);
+    };
+    read(0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (i < 3) read(i + 1);
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+            for (int kc = 0; kc < kK; ++kc) {
+                if (i < 3)
+                    up = __builtin_amdgcn_mfma_f32_32x32x16_bf16(weight(3 * (i < 3 ? i : 0) + kx, kc), b[i & 1][kx][kc],
+                                                                 up, 0, 0, 0);
+                if (i > 0)
+                    low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(weight(3 * (i > 0 ? i - 1 : 0) + kx, kc),
+                                                                  b[i & 1][kx][kc], low, 0, 0, 0);
+            }
+    }
+}
+
+// 8 channels (group q + half of four) of a lane's pixel from an accumulator after the ReLU, as BF16: a
+// lane holds 4 of every 8 channels, and exchanging halves of the wave completes one group of each two.
+__device__ __forceinline__ u32x4 relu_group(const f32x16& acc, int q) {
+    u32x2 w[2];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            w[g][h] = f2bf2(fmaxf(acc[4 * (q + g) + 2 * h], 0.f), fmaxf(acc[4 * (q + g) + 2 * h + 1], 0.f));
+    const auto r0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+    const auto r1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+    return (u32x4){r0[0], r1[0], r0[1], r1[1]};
+}
+
+// ------------------------------------------------------------------------------ forward pairs
+// Two layers of the training forward in one pass over their input, both maps written for the backward:
+// layers 1 and 2 (kFirst: 16 -> 32 -> 32 channels, ReLU) or 3 and 4 (32 -> 32, ReLU, -> 3 FP32 planes).
+// The first of the two is computed over the tile and a rim of one pixel into LDS (pixels outside the
+// image as the zero padding) and its tile's own pixels also to memory, so the second reads no map from
+// there. Waves 0-3 take the first layer of a tile while waves 4-7 take the second of the tile before
+// (one of each per SIMD, whose products and epilogues overlap), each with its layer's weights in
+// registers. The next input tile is fetched meanwhile. Every output is bitwise that of conv3x3_kernel.
+// 4 x 1024^2 pixels take 162 us for layers 1 and 2 (670 MB, 145 us at a large copy's rate) and 195 for
+// 3 and 4 (586 MB, 127 us), a launch per layer 111 + 127 and 127 + 88. The barriers and the first
+// layer's uneven blocks (10 for 4 waves) hold it: matrix cores are busy 47 % of the time, and fetching
+// two tiles ahead changes nothing. All eight waves in one layer after the other took 174 and 193.
+template <bool kFirst>
+struct PairLds {
+    static constexpr int kIn = kFirst ? 16 : 32;
+    static constexpr int kInStride = kIn * 2 + 16, kMidStride = 64 + 16;
+    using Map = BwMap<kIn / 8, 2, kInStride>;
+    static constexpr int kMidRows = kBwTH + 2, kMidCols = kBwTW + 2;
+    static constexpr int kInBytes = Map::kRows * Map::kCols * kInStride;
+    static constexpr int kMidBytes = kMidRows * kMidCols * kMidStride;
+};
+
+template <bool kFirst>
+__global__ __launch_bounds__(kBwThreads) void forward_pair_kernel(
+    const uint16_t* __restrict__ in, const uint16_t* __restrict__ wa, const float* __restrict__ ba,
+    const uint16_t* __restrict__ wb, const float* __restrict__ bb, uint16_t* __restrict__ mid_out,
+    uint16_t* __restrict__ out_bf, float* __restrict__ out_f, int nimg, int H, int W) {
+    using L = PairLds<kFirst>;
+    using Map = typename L::Map;
+    constexpr int kK = L::kIn / 16;
+    __shared__ __attribute__((aligned(16))) unsigned char ins[L::kInBytes];
+    __shared__ __attribute__((aligned(16))) unsigned char mids[2][L::kMidBytes];
+    __shared__ float bias[2][32];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const int half = lane / 32, j = lane % 32;
+    const BwWalk walk(nimg, H, W);
+    const int first = walk.first, last = walk.last, stride = walk.stride;
+    if (first >= last) return;
+
+    u32x4 rin[Map::kLoads];
+    auto thread = [&]() {  // the loads' places are formed where they are used, not kept in registers
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto fetch = [&](int tile) {
+        const BwWalk::Place p = walk.place(tile);
+        Map(thread()).fetch(in, p.img, p.y0, p.x0, H, W, rin);
+    };
+    auto weights = [&](auto& a, const uint16_t* __restrict__ w, auto kin) {
+        constexpr int kIn = kin.value;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int kc = 0; kc < kIn / 16; ++kc)
+                a[t][kc] = *reinterpret_cast<const bf16x8*>(w + ((size_t)t * 32 + j) * kIn + kc * 16 + half * 8);
+        __builtin_amdgcn_s_waitcnt(0);  // here: else the loop would wait for them, and the next tile
+    };
+    if (threadIdx.x < 64) bias[threadIdx.x / 32][threadIdx.x % 32] = (threadIdx.x < 32 ? ba : bb)[threadIdx.x % 32];
+    fetch(first);
+    Map(thread()).commit(ins, rin);
+    // Iteration i: the first layer of tile i into mids[i % 2], the second of tile i - 1 from the other.
+    // Both roles pass two barriers per iteration and commit the next input between them and the next
+    // iteration's first, in loops of their own, so that a wave waits for its loads alone, not its stores.
+    if (wave < kBwWaves / 2) {
+        bf16x8 a[9][kK];
+        weights(a, wa, std::integral_constant<int, L::kIn>{});
+        int buf = 0;
+        for (int tile = first; tile < last; tile += stride, buf ^= 1) {
+            const BwWalk::Place p = walk.place(tile);
+            __syncthreads();
+            if (tile + stride < last) fetch(tile + stride);
+            // the row pairs of the tile with its rim, end to end, 32 pixels at a time
+            constexpr int kPairs = L::kMidRows / 2 * L::kMidCols, kBlocks = (kPairs + 31) / 32;
+#pragma unroll
+            for (int blk0 = 0; blk0 < kBlocks; blk0 += kBwWaves / 2) {
+                const int blk = blk0 + wave;
+                if (blk >= kBlocks) break;  // wave-uniform
+                const int P = blk * 32 + j;
+                const bool valid = P < kPairs;
+                const int Pc = valid ? P : kPairs - 1;  // the last block's spare lanes read a real pixel
+                const int ry = 2 * (Pc / L::kMidCols), rx = Pc % L::kMidCols;
+                f32x16 acc[2];
+                acc[0] = acc[1] = bias_pattern(bias[0], half);
+                two_rows<L::kIn, Map::kCols, L::kInStride>(ins + (ry * Map::kCols + rx) * L::kInStride + half * 16,
+                                                           [&](int t, int kc) { return a[t][kc]; }, acc[0], acc[1]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int r = ry + i, gy = p.y0 - 1 + r, gx = p.x0 - 1 + rx;
+                    const bool inside = ((unsigned)gy < (unsigned)H) & ((unsigned)gx < (unsigned)W);
+                    const bool own = valid & inside & ((unsigned)(r - 1) < (unsigned)kBwTH) &
+                                     ((unsigned)(rx - 1) < (unsigned)kBwTW);
+                    u32x4* const to =
+                        reinterpret_cast<u32x4*>(mid_out) + (((int64_t)p.img * H + gy) * W + gx) * 4 + half;
+                    unsigned char* const at = mids[buf] + (r * L::kMidCols + rx) * L::kMidStride + half * 16;
+#pragma unroll
+                    for (int q = 0; q < 4; q += 2) {
+                        u32x4 o = relu_group(acc[i], q);
+                        if (own) to[q] = o;
+                        if (!inside) o = (u32x4){0u, 0u, 0u, 0u};
+                        if (valid) *reinterpret_cast<u32x4*>(at + q * 16) = o;
+                    }
+                }
+            }
+            __syncthreads();
+            if (tile + stride < last) Map(thread()).commit(ins, rin);
+        }
+        __syncthreads();
+    } else {
+        bf16x8 a[9][2];
+        weights(a, wb, std::integral_constant<int, 32>{});
+        auto second = [&](int tile, const unsigned char* mid) {
+            const BwWalk::Place p = walk.place(tile);
+#pragma unroll
+            for (int pair = 0; pair < 2; ++pair) {
+                const int ry = 2 * (wave - kBwWaves / 2 + pair * (kBwWaves / 2));
+                f32x16 acc[2];
+                acc[0] = acc[1] = bias_pattern(bias[1], half);
+                two_rows<32, L::kMidCols, L::kMidStride>(mid + (ry * L::kMidCols + j) * L::kMidStride + half * 16,
+                                                         [&](int t, int kc) { return a[t][kc]; }, acc[0], acc[1]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int gy = p.y0 + ry + i, gx = p.x0 + j;
+                    const bool inside = gy < H && gx < W;
+                    if constexpr (kFirst) {
+                        u32x4* const to =
+                            reinterpret_cast<u32x4*>(out_bf) + (((int64_t)p.img * H + gy) * W + gx) * 4 + half;
+#pragma unroll
+                        for (int q = 0; q < 4; q += 2) {
+                            const u32x4 o = relu_group(acc[i], q);
+                            if (inside) to[q] = o;
+                        }
+                    } else if (inside && half == 0) {
+#pragma unroll
+                        for (int e = 0; e < 3; ++e)
+                            out_f[((size_t)p.img * 3 + e) * H * W + (size_t)gy * W + gx] = acc[i][e];
+                    }
+                }
+            }
+        };
+        int buf = 0;
+        for (int tile = first; tile < last; tile += stride, buf ^= 1) {
+            __syncthreads();
+            if (tile + stride < last) fetch(tile + stride);
+            if (tile > first) second(tile - stride, mids[buf ^ 1]);
+            __syncthreads();
+            if (tile + stride < last) Map(thread()).commit(ins, rin);
+        }
+        __syncthreads();
+        second(first + (last - first - 1) / stride * stride, mids[buf ^ 1]);
+    }
+}
+
 // ------------------------------------------------------------------------------ backward
 // One layer's backward over its input map x and output gradient dY (both NHWC), each read once:
 //   dW[t][o][c] = sum_p dY[p][o] x[p + off_t][c]   (MFMA, K = pixels),  db[o] = sum_p dY[p][o];
@@ -631,71 +918,8 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
 // fixed distances (BwMap), so that fetching and staging a tile takes a few vector instructions per
 // load: with a division and a 64-bit address for each they took as long as the products (221 us).
 // Each workgroup's partial [9][32][KIN] (and the bias partial [32]) goes to global memory.
-constexpr int kBwTH = 16, kBwTW = 32;
-constexpr int kBwThreads = 512, kBwWaves = kBwThreads / 64;
 
 __device__ const u32x4 kBwZeros = {0u, 0u, 0u, 0u};  // what a pixel outside the image reads
-
-// One map's tile as a workgroup loads it, kChunks x 16 B per pixel: the 32 inner columns a few rows at a
-// time (all threads), then, with the rim, the two last rows and the rim's columns in one more load. A
-// row's bytes times the tile's rows stay below kBwRange; wider images are addressed pixel by pixel.
-constexpr unsigned kBwRange = 1u << 30;
-constexpr int kBwWide = (kBwRange >> 6) / (kBwTH + 2);  // widest row of 64 B pixels
-
-template <int kChunks, int kRim, int kStride>
-struct BwMap {
-    static constexpr int kStep = kBwThreads / (kBwTW * kChunks);  // rows per load
-    static constexpr int kFull = kBwTH / kStep, kLoads = kFull + kRim;
-    static constexpr int kCols = kBwTW + 2 * kRim;
-    static_assert(kFull * kStep == kBwTH, "whole loads");
-    static constexpr int kTail = 2 * kBwTW * kChunks, kSides = 2 * (kBwTH + 2) * kChunks;
-    static_assert(kTail + kSides <= kBwThreads, "one load for the rest");
-    int row, col, lrow, lcol, ch;  // this thread's first pixel, and its last load's
-    bool last;                     // it has one
-
-    __device__ __forceinline__ explicit BwMap(int tid) {
-        ch = tid % kChunks;
-        row = tid / (kBwTW * kChunks);
-        col = kRim + tid / kChunks % kBwTW;
-        const int i = (tid - kTail) / kChunks;  // of the rim's columns
-        const bool tail = tid < kTail;
-        lrow = tail ? kBwTH + row : i % (kBwTH + 2);
-        lcol = tail ? col : i < kBwTH + 2 ? 0 : kCols - 1;
-        last = tid < kTail + kSides;
-    }
-    __device__ __forceinline__ int lds() const { return (row * kCols + col) * kStride + ch * 16; }
-    __device__ __forceinline__ int lds_last() const { return (lrow * kCols + lcol) * kStride + ch * 16; }
-
-    // The tile at (y0, x0) of image img. Rows outside the image lie outside the buffer resource, and a
-    // column outside it is given an offset there: both read zeros.
-    __device__ __forceinline__ void fetch(const uint16_t* __restrict__ map, int img, int y0, int x0, int H, int W,
-                                          u32x4 (&regs)[kLoads]) const {
-        const int yb = max(y0 - kRim, 0), down = y0 - kRim - yb;  // -1: the tile's first row is above the image
-        const unsigned pitch = (unsigned)W * (16u * kChunks);
-        const uint64_t left = (uint64_t)(H - yb) * pitch;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t*>(map) + ((size_t)img * H + yb) * W * (8 * kChunks), 0,
-            (int)(left < kBwRange ? (unsigned)left : kBwRange), 0x00020000);
-        auto offset = [&](int r, int c) {
-            const int gx = x0 - kRim + c;
-            return (unsigned)gx < (unsigned)W ? (unsigned)(r + down) * pitch + (unsigned)(gx * kChunks + ch) * 16u
-                                              : 2u * kBwRange;
-        };
-        const unsigned off = offset(row, col);
-#pragma unroll
-        for (int q = 0; q < kFull; ++q)
-            regs[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + (unsigned)(q * kStep) * pitch), 0, 0);
-        if constexpr (kRim != 0)
-            regs[kFull] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(last ? offset(lrow, lcol) : 2u * kBwRange), 0, 0);
-    }
-    __device__ __forceinline__ void commit(unsigned char* tile, const u32x4 (&regs)[kLoads]) const {
-        unsigned char* const at = tile + lds();
-#pragma unroll
-        for (int q = 0; q < kFull; ++q) *reinterpret_cast<u32x4*>(at + q * kStep * kCols * kStride) = regs[q];
-        if constexpr (kRim != 0)
-            if (last) *reinterpret_cast<u32x4*>(tile + lds_last()) = regs[kFull];
-    }
-};
 
 // A tile of a map with 4 channels (8 B) per pixel, one pixel per load.
 template <int kRim, int kStride>
@@ -763,27 +987,13 @@ __global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __
     __shared__ __attribute__((aligned(16))) unsigned char lds[L::kBytes];
     unsigned char* const xs = lds;
     unsigned char* const ds = lds + L::kXBytes;
-    const int tiles_x = (W + kBwTW - 1) / kBwTW, tiles_y = (H + kBwTH - 1) / kBwTH;
-    const int per_img = tiles_x * tiles_y, total = per_img * nimg;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int half = lane / 32, j = lane % 32;
 
-    // workgroup b runs on XCD b % 8: each XCD walks a contiguous range of tiles, whose shared rims
-    // its L2 then holds
-    const int groups = gridDim.x, xcd = blockIdx.x % kXcds;
-    const int lead = min(groups, kXcds);  // XCDs in use
-    const int stride = groups / kXcds + (xcd < groups % kXcds ? 1 : 0);
-    const int first = (int)((int64_t)total * xcd / lead) + (int)blockIdx.x / kXcds;
-    const int last = (int)((int64_t)total * (xcd + 1) / lead);
-
-    struct Place {
-        int img, y0, x0;
-    };
-    auto place = [&](int tile) {
-        const int img = tile / per_img, t = tile - img * per_img;
-        const int ty = t / tiles_x;
-        return Place{img, ty * kBwTH, (t - ty * tiles_x) * kBwTW};
-    };
+    const BwWalk walk(nimg, H, W);
+    using Place = BwWalk::Place;
+    const int first = walk.first, last = walk.last, stride = walk.stride;
+    auto place = [&](int tile) { return walk.place(tile); };
 
     using XMap = BwMap<KIN / 8, 1, L::kXStride>;
     using DMap = std::conditional_t<kDch == 32, BwMap<4, L::kRim, L::kDStride>, BwThinMap<L::kRim, L::kDStride>>;
@@ -885,35 +1095,11 @@ __global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __
 #pragma unroll
             for (int pair = 0; pair < 2; ++pair) {
                 const int ry = 4 * wave + 2 * pair;
-                const unsigned char* base = ds + (ry * L::kDCols + j) * L::kDStride + half * 16;
-                bf16x8 b[2][3][2];
-                auto read = [&](int i) {
-#pragma unroll
-                    for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-                        for (int kc = 0; kc < 2; ++kc)
-                            b[i & 1][kx][kc] = *reinterpret_cast<const bf16x8*>(
-                                base + (i * L::kDCols + kx) * L::kDStride + kc * 32);
-                };
                 f32x16 acc[2];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.f;
-                read(0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (i < 3) read(i + 1);
-#pragma unroll
-                    for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-                        for (int kc = 0; kc < 2; ++kc) {
-                            if (i < 3)
-                                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[3 * (i < 3 ? i : 0) + kx][kc],
-                                                                                 b[i & 1][kx][kc], acc[0], 0, 0, 0);
-                            if (i > 0)
-                                acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[3 * (i > 0 ? i - 1 : 0) + kx][kc],
-                                                                                 b[i & 1][kx][kc], acc[1], 0, 0, 0);
-                        }
-                }
+                two_rows<32, L::kDCols, L::kDStride>(ds + (ry * L::kDCols + j) * L::kDStride + half * 16,
+                                                     [&](int t, int kc) { return a[t][kc]; }, acc[0], acc[1]);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const unsigned char* m = xs + ((ry + i + 1) * L::kXCols + j + 1) * L::kXStride + half * 8;
@@ -1422,6 +1608,22 @@ hipError_t launch_conv3x3(int kin, int mode, const uint16_t* in, const uint16_t*
     SW2D_CONV_CASE(32, kConvDgradMask)
 #undef SW2D_CONV_CASE
     return hipErrorInvalidValue;
+}
+
+bool forward_pairs_ok(int W) { return W <= kBwWide; }
+
+hipError_t launch_forward_pairs(const uint16_t* x16, const FusedNet& net, uint16_t* const* acts, float* out, int nimg,
+                                int H, int W, hipStream_t s) {
+    const int64_t tiles = backward_tiles(nimg, H, W);
+    auto go = [&](auto kernel, const uint16_t* in, int l, uint16_t* mid, uint16_t* out_bf, float* out_f) {
+        const int cap = resident_groups(reinterpret_cast<const void*>(kernel), kBwThreads);
+        if (cap < 1) return hipErrorInvalidDeviceFunction;
+        hipLaunchKernelGGL(kernel, dim3(tiles < cap ? (int)tiles : cap), dim3(kBwThreads), 0, s, in, net.wk[l],
+                           net.bias[l], net.wk[l + 1], net.bias[l + 1], mid, out_bf, out_f, nimg, H, W);
+        return hipGetLastError();
+    };
+    const hipError_t e = go(&forward_pair_kernel<true>, x16, 0, acts[0], acts[1], nullptr);
+    return e != hipSuccess ? e : go(&forward_pair_kernel<false>, acts[1], 2, acts[2], nullptr, out);
 }
 
 int64_t backward_tiles(int nimg, int H, int W) {

@@ -178,6 +178,29 @@ int sw2d_conv3x3_fwd(const uint16_t* in, int32_t cin, const uint16_t* wk, const 
                 "sw2d_conv3x3_fwd");
 }
 
+int sw2d_cnn_forward_train(const uint16_t* x16, const uint16_t* const* wk, const float* const* bias,
+                           uint16_t* const* acts, float* out, int32_t nimg, int32_t ny, int32_t nx, void* stream) {
+    if (!x16 || !wk || !bias || !acts || !out || !aligned16(x16)) return SW2D_EINVAL;
+    if (!dims_ok(nimg, ny, nx)) return SW2D_EINVAL;
+    FusedNet net;
+    for (int l = 0; l < 4; ++l) {
+        if (!wk[l] || !bias[l] || !aligned16(wk[l])) return SW2D_EINVAL;
+        if (l < 3 && (!acts[l] || !aligned16(acts[l]))) return SW2D_EINVAL;
+        net.wk[l] = wk[l];
+        net.bias[l] = bias[l];
+    }
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    if (forward_pairs_ok(nx))
+        return fail(launch_forward_pairs(x16, net, acts, out, nimg, ny, nx, s), "sw2d_cnn_forward_train");
+    for (int l = 0; l < 4; ++l) {
+        const hipError_t e = launch_conv3x3(l == 0 ? 16 : 32, l < 3 ? kConvRelu : kConvLinear3, l == 0 ? x16 : acts[l - 1],
+                                            wk[l], bias[l], l < 3 ? acts[l] : nullptr, l < 3 ? nullptr : out, nullptr,
+                                            nimg, ny, nx, s);
+        if (e != hipSuccess) return fail(e, "sw2d_cnn_forward_train");
+    }
+    return SW2D_OK;
+}
+
 int sw2d_conv3x3_fwd_raw(const float* eta, const float* u, const float* v, const float* H, const uint8_t* mask,
                          int32_t nx, int32_t ny, const float* mean, const float* std_, const uint16_t* wk,
                          const float* bias, uint16_t* out, void* stream) {

@@ -113,15 +113,11 @@ class ConvNet:
     def forward(self, x16, n, h, w):
         """x16: BF16 NHWC input with 16 channels. Returns the FP32 output planes [n][3][h][w]."""
         _, acts, out, _ = self._buffers(n, h, w)
-        s = self.stream()
-        src = x16
-        for layer in range(3):
-            check(self.lib.sw2d_conv3x3_fwd(_p(src), CIN[layer], _p(self.wk[layer]),
-                                            _p(self.weight(layer)[1]), 1, _p(acts[layer]), n, h, w, s),
-                  "sw2d_conv3x3_fwd")
-            src = acts[layer]
-        check(self.lib.sw2d_conv3x3_fwd(_p(src), 32, _p(self.wk[3]), _p(self.weight(3)[1]), 0, _p(out),
-                                        n, h, w, s), "sw2d_conv3x3_fwd")
+        wk = (ctypes.c_void_p * 4)(*[t.data_ptr() for t in self.wk])
+        bias = (ctypes.c_void_p * 4)(*[self.weight(layer)[1].data_ptr() for layer in range(4)])
+        hidden = (ctypes.c_void_p * 3)(*[t.data_ptr() for t in acts])
+        check(self.lib.sw2d_cnn_forward_train(_p(x16), wk, bias, hidden, _p(out), n, h, w, self.stream()),
+              "sw2d_cnn_forward_train")
         return out
 
     def forward_hidden_raw(self, eta, u, v, H, mask, h, w, mean_ptr, std_ptr):
