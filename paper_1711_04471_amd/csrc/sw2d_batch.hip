@@ -13,10 +13,10 @@
 //
 // One persistent launch per chunk of steps (sw2d_batch_kernel) where the caller asks for it:
 // workgroup g of G takes the g-th of G equal runs of the list and meets the others at a grid
-// barrier after each pass. Measured slower at either end: 12 members of 64-256 cells a side 200 us
-// per 50 steps (the barrier takes longer than a launch) against 100; 256 members of 128-1024, 48
-// steps, 10.6 ms (equal runs end up to a quarter apart, and the loop's state spills scalar
-// registers) against 7.0.
+// barrier after each pass. Measured slower at either end, whole calls with the gathering of the states
+// (0.54 ms of it for the 256 members): 12 members of 64-256 cells a side, 50 steps, 200 us (the barrier
+// takes longer than a launch) against 185; 256 members of 128-1024, 48 steps, 11.1 ms (equal runs end
+// up to a quarter apart, and the loop's state spills scalar registers) against 7.6.
 //
 // The barrier uses no contended atomics: every workgroup publishes the epoch it has
 // reached in its own flag (after an agent-scope release), workgroup 0 waits for all
@@ -388,7 +388,9 @@ constexpr int kMaxBatchGrid = 256 * 8;  // flag lines reserved: 8 workgroups on 
 // workgroups of 8 waves per CU, not 4); a grid barrier that waits for a workgroup that never
 // became resident would only end at its deadline.
 constexpr int kBatchWgPerCu = 3;
-constexpr int kBatchRows[3] = {kBlockRowsLow, kBlockRowsMid, kBlockRowsHigh};
+constexpr int kBatchRowsLow = 3, kBatchRowsMid = 5, kBatchRowsHigh = 8;  // rows per wave: tiles of 24, 40 and 64
+constexpr int kBatchRows[3] = {kBatchRowsLow, kBatchRowsMid, kBatchRowsHigh};
+constexpr int kBatchLowTiles = 320;    // most tiles of 24 rows chosen without the caller's word
 constexpr int kBatchHighTiles = 2048;  // fewest tiles of 64 rows chosen without the caller's word
 
 bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLayout& L) {
@@ -417,7 +419,7 @@ bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLa
     int r = 1;
     if (band_rows)
         r = sum_rows < 16 * (int64_t)n ? 0 : sum_rows < 48 * (int64_t)n ? 1 : 2;
-    else if (tiles[0][kBlockMaxK - 1] <= kBlockLowTiles)
+    else if (tiles[0][kBlockMaxK - 1] <= kBatchLowTiles)
         r = 0;
     else if (tiles[2][kBlockMaxK - 1] >= kBatchHighTiles)
         r = 2;
@@ -463,9 +465,9 @@ BatchKernel batch_kernel_of(int K) {
 }
 
 BatchKernel batch_kernel(int K, int R) {
-    return R == kBlockRowsLow   ? batch_kernel_of<kBlockRowsLow>(K)
-           : R == kBlockRowsMid ? batch_kernel_of<kBlockRowsMid>(K)
-                                : batch_kernel_of<kBlockRowsHigh>(K);
+    return R == kBatchRowsLow   ? batch_kernel_of<kBatchRowsLow>(K)
+           : R == kBatchRowsMid ? batch_kernel_of<kBatchRowsMid>(K)
+                                : batch_kernel_of<kBatchRowsHigh>(K);
 }
 
 typedef void (*BatchPassKernel)(const BatchInst*, const int*, BatchPass);
@@ -481,9 +483,9 @@ BatchPassKernel batch_pass_kernel_of(int K) {
 }
 
 BatchPassKernel batch_pass_kernel(int K, int R) {
-    return R == kBlockRowsLow   ? batch_pass_kernel_of<kBlockRowsLow>(K)
-           : R == kBlockRowsMid ? batch_pass_kernel_of<kBlockRowsMid>(K)
-                                : batch_pass_kernel_of<kBlockRowsHigh>(K);
+    return R == kBatchRowsLow   ? batch_pass_kernel_of<kBatchRowsLow>(K)
+           : R == kBatchRowsMid ? batch_pass_kernel_of<kBatchRowsMid>(K)
+                                : batch_pass_kernel_of<kBatchRowsHigh>(K);
 }
 
 // Passes of a chunk of steps: as many of kBlockMaxK steps as it holds, one for the rest.

@@ -47,9 +47,10 @@ hipError_t launch_variant(int K, const float* eta, const float* u, const float* 
     }
 #define SW2D_BLOCK_ROWS(RR) \
     SW2D_BLOCK_CASE(1, RR) SW2D_BLOCK_CASE(2, RR) SW2D_BLOCK_CASE(3, RR) SW2D_BLOCK_CASE(4, RR)
-    SW2D_BLOCK_ROWS(kBlockRowsLow)
-    SW2D_BLOCK_ROWS(kBlockRowsMid)
-    SW2D_BLOCK_ROWS(kBlockRowsHigh)
+    SW2D_BLOCK_ROWS(3)
+    SW2D_BLOCK_ROWS(5)
+    SW2D_BLOCK_ROWS(7)
+    SW2D_BLOCK_ROWS(8)
 #undef SW2D_BLOCK_ROWS
 #undef SW2D_BLOCK_CASE
     return hipErrorInvalidValue;

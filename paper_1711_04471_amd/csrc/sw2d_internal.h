@@ -103,10 +103,8 @@ inline StepGeometry make_geometry(int nx, int ny, int rows, int strip_out = kStr
 // tiles of 40-48 rows: 2048^2 basin 8.4 with 8 waves, 8.6 with 12, 16.4 with 16; 66^2 basin 2.2,
 // 2.4 and 3.3); 4 waves are no faster.
 constexpr int kBlockWaves = 8;
-constexpr int kBlockRowsLow = 3, kBlockRowsMid = 5, kBlockRowsHigh = 8;  // tiles of 24, 40 and 64 rows
+constexpr int kBlockRows[] = {3, 5, 7, 8};  // tiles of 24, 40, 56 and 64 rows
 constexpr int kBlockMaxK = 4;
-constexpr int kBlockLowTiles = 320;     // most tiles of 24 rows at K >= 3
-constexpr int kBlockLowTilesVar = 768;  // at K <= 2 with model variants
 // Grids of at most 2^23 cells, whose state and depth (28 B per cell and step, 235 MB) the 256 MB
 // Infinity Cache holds, take several steps per pass whatever the caller's steps per pass: there is
 // no HBM pass to choose. Larger grids take the caller's, if one was chosen, and else kBlockMaxK:
@@ -147,37 +145,38 @@ inline BlockGeometry make_block_geometry(int nx, int ny, int K, int R, int kvar 
     return g;
 }
 
-// The tile height for K steps. A step of a tile takes 0.8 us at 3 rows per wave, 1.2 at 5 and 1.8
-// at 8, but a tile of 24, 40 or 64 rows owns 4K rows less. Low tiles win while all of them run at
-// once, with little to spare beyond one per CU (us per step at K = 4, 3 and 5 rows: 300 x 221 with
-// 78 and 27 tiles 1.8 and 2.3; 693 x 700 with 602 and 203 tiles 3.1 and 2.5; K = 3 there, with 348
-// and 150 tiles, 3.0 and 2.9). With many tiles the recomputed overlap decides: at K <= 2 it is
-// small and low tiles, which load with the most waves, stay ahead (2048^2, K = 2: 10.5, 10.9 and
-// 12.1 us per step at 3, 5 and 8 rows); at K = 3 and 4 it is not (2048^2, K = 4: 12.3, 8.4, 9.0;
-// 4096 x 2048: 22.7, 14.2, 14.4), and from HBM the re-read rows add to it (8192 x 4096, K = 4: 88,
-// 57.9, 51.7).
-//
-// The variants take more time per cell, so the recomputed overlap weighs more: 64 rows at 4 steps
-// per pass once the 40-row tiles are more than one per CU (friction 1024^2 6.7 us per step against
-// 7.5 at 40 rows; all variants 9.8 against 11.1, 693 x 700 with 238 tiles 9.5 against 6.5), 40 rows
-// for many tiles at K <= 2 (all variants, K = 2, 2047 x 1531: 22.7 against 27.7 at 24 rows; 1024^2,
-// 657 low tiles: 12.5 against 11.9). Wetting and drying is as cheap as the plain step and keeps 40
-// rows (4096 x 2048 20.0 us, 21.8 at 64).
-inline BlockGeometry block_geometry(int nx, int ny, int K, int kvar = 0) {
-    const BlockGeometry low = make_block_geometry(nx, ny, K, kBlockRowsLow, kvar);
-    if ((K <= 2 && kvar == 0) || low.nblocks <= (K <= 2 ? kBlockLowTilesVar : kBlockLowTiles)) return low;
-    const bool cached = (int64_t)nx * ny <= kBlockMaxCells;
-    const BlockGeometry mid = make_block_geometry(nx, ny, K, kBlockRowsMid, kvar);
-    const bool high = kvar == 0 ? K == 4 && !cached
-                                : kvar != kVarWetDry && (cached ? K == 4 && mid.nblocks > kCus : K >= 2);
-    return high ? make_block_geometry(nx, ny, K, kBlockRowsHigh, kvar) : mid;
+// The tile heights for K steps of a model (kvar: its variants). The plain step at K <= 2 loads with the
+// most waves on low tiles and overlaps little (2048^2, K = 2: 10.5, 10.9 and 12.1 us per step at 3, 5
+// and 8 rows); wetting and drying, as cheap as the plain step but with more registers, is no faster on
+// 64 rows (4096 x 2048 21.8 us against 20.0 on 40).
+constexpr bool block_shape(int K, int R, int kvar) {
+    if (R == 3) return true;
+    if (R == 5) return kvar != 0 || K >= 3;
+    if (R == 7) return kvar == 0 && K == 4;
+    return kvar == 0 ? K == 4 : kvar != kVarWetDry && K >= 2;
 }
 
-// The shapes that block_geometry chooses.
-constexpr bool block_shape(int K, int R, int kVar) {
-    if (R == kBlockRowsLow) return true;
-    if (R == kBlockRowsMid) return kVar != 0 || K >= 3;
-    return kVar == 0 ? K == 4 : kVar != kVarWetDry && K >= 2;
+// The tile height for K steps: the one whose tiles take the fewest rows on the CU with the most of
+// them. A step of a tile alone takes 0.8 us at 3 rows per wave, 1.2 at 5 and 1.8 at 8, CUs with several
+// tiles take about as long as their rows together, and a tile owns 4K (with advection 5K) rows less
+// than it steps, so low tiles win while every CU has one, higher ones as the recomputed overlap counts,
+// and between sizes the round that is left nearly empty decides. Plain model, K = 4, us per step at 3,
+// 5, 7 and 8 rows: 300 x 221 1.8, 2.3, 2.8, 3.1; 693 x 700 3.2, 2.55, 3.0, 3.35; 1024^2 4.7, 3.6, 3.2,
+// 3.4; 2048^2 13.8, 8.7, 8.1, 8.8; 2300 x 2200 15.7, 9.4, 9.4, 9.1; 6000 x 5000 79, 52, 48, 47. All
+// variants, K = 4, at 3, 5 and 8 rows: 693 x 700 16.0, 6.5, 9.5; 1024^2 30.5, 11.1, 9.8.
+inline BlockGeometry block_geometry(int nx, int ny, int K, int kvar = 0) {
+    BlockGeometry best{};
+    int64_t least = 0;
+    for (int R : kBlockRows) {
+        if (!block_shape(K, R, kvar)) continue;
+        const BlockGeometry g = make_block_geometry(nx, ny, K, R, kvar);
+        const int64_t rows = (int64_t)((g.nblocks + kCus - 1) / kCus) * R;
+        if (least == 0 || rows < least) {
+            least = rows;
+            best = g;
+        }
+    }
+    return best;
 }
 
 // K = 1..4 steps of the model (kvar: its variants, 0 for the plain step) in one pass over register
