@@ -129,12 +129,21 @@ StepCoef make_coef(const sw2d_params* p) {
     return k;
 }
 
-int flush_folds(sw2d_ctx* h, int pending, int nparts, int stride) {
-    if (pending <= 0) return SW2D_OK;
-    SW2D_HIP(launch_fold(h->part, nparts, stride, pending, h->step - pending + 1, h->ring, kRingCap,
-                         h->p.dx * h->p.dy, h->h_sum, h->stream));
+}  // namespace
+
+// Adds the queued partials; the queue's last step is the handle's.
+int sw2d::detail::flush_folds(sw2d_t h, FoldQueue& q) {
+    if (q.pending > 0)
+        SW2D_HIP(launch_fold(h->part, q.runs, q.pending, h->step - q.pending + 1, h->ring, kRingCap, h->p.dx * h->p.dy,
+                             h->h_sum, h->stream));
+    q = FoldQueue{};
     return SW2D_OK;
 }
+
+namespace {
+
+using sw2d::detail::flush_folds;
+using sw2d::detail::FoldQueue;
 
 // Whether the grid's steps and depth stay in the Infinity Cache (kBlockMaxCells).
 bool cached_grid(const sw2d_ctx* h) { return (int64_t)h->p.nx * h->p.ny <= kBlockMaxCells; }
@@ -165,14 +174,14 @@ int add_pass_times(hipEvent_t* ev, int passes, double* total_ms) {
 }
 
 // Enqueue nsteps steps in passes of pass_steps steps (a remainder takes one shorter pass), over
-// register tiles or through the row pipelines. The fold partials of successive passes with the
-// same number of workgroups are buffered while slots last, then added by one fold launch. With
-// events (2 per pass, at most kFoldChunk passes between folds) the step kernels are timed.
-int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms) {
+// register tiles or through the row pipelines. The fold partials of successive passes are left in the
+// queue while slots last, then added by one fold launch. With events (2 per pass, at most kFoldChunk
+// passes between folds) the step kernels are timed.
+int enqueue_steps(sw2d_ctx* h, int32_t nsteps, FoldQueue& q, hipEvent_t* ev, double* total_ms) {
     const int kmax = pass_steps(h);
     BlockGeometry bg{};
     int bg_k = 0;
-    int pending = 0, nparts = 0, passes = 0;
+    int passes = 0;
     int32_t done = 0;
     while (done < nsteps) {
         const int k = (nsteps - done < kmax) ? nsteps - done : kmax;
@@ -183,21 +192,22 @@ int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms)
         }
         const StepGeometry& g = (k >= 2) ? h->geok[k] : h->geo;
         const int nblocks = tiles ? bg.nblocks : g.nblocks;
-        if (pending > 0 && (nblocks != nparts || (size_t)(pending + k) * nblocks > h->part_slots ||
-                            pending + k > kRingCap || (ev && passes == kFoldChunk))) {
-            int rc = flush_folds(h, pending, nparts, nparts);
+        auto new_run = [&]() { return q.runs.n == 0 || q.runs.run[q.runs.n - 1].nparts != nblocks; };
+        if (q.pending > 0 && (q.used + (int64_t)k * nblocks > (int64_t)h->part_slots || q.pending + k > kRingCap ||
+                              (q.runs.n == FoldRuns::kMax && new_run()) || (ev && passes == kFoldChunk))) {
+            int rc = flush_folds(h, q);
             if (rc == SW2D_OK && ev) rc = add_pass_times(ev, passes, total_ms);
             if (rc) return rc;
-            pending = 0;
             passes = 0;
         }
+        if (new_run()) q.runs.run[q.runs.n++] = {q.used, nblocks, nblocks, q.pending};
         float* const* src = h->state[h->cur];
         float* const* dst = h->state[h->cur ^ 1];
-        FoldPartial* part = h->part + (size_t)pending * nblocks;
+        FoldPartial* part = h->part + q.used;
         if (ev) SW2D_HIP(hipEventRecord(ev[2 * passes], h->stream));
         if (tiles)
-            SW2D_HIP(launch_block(k, (int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, bg, h->coef,
-                                  h->stream));
+            SW2D_HIP(launch_block(k, (int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, bg,
+                                  h->coef, h->stream));
         else if (k >= 2)
             SW2D_HIP(launch_stepk(k, (int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part,
                                   nblocks, g, h->coef, h->stream));
@@ -207,14 +217,14 @@ int enqueue_steps(sw2d_ctx* h, int32_t nsteps, hipEvent_t* ev, double* total_ms)
         if (ev) SW2D_HIP(hipEventRecord(ev[2 * passes + 1], h->stream));
         h->cur ^= 1;
         h->step += k;
-        pending += k;
-        nparts = nblocks;
+        q.pending += k;
+        q.used += (int64_t)k * nblocks;
         ++passes;
         done += k;
     }
-    int rc = flush_folds(h, pending, nparts, nparts);
-    if (rc == SW2D_OK && ev && passes > 0) rc = add_pass_times(ev, passes, total_ms);
-    return rc;
+    if (!ev) return SW2D_OK;
+    const int rc = flush_folds(h, q);
+    return rc == SW2D_OK && passes > 0 ? add_pass_times(ev, passes, total_ms) : rc;
 }
 
 }  // namespace
@@ -224,6 +234,10 @@ namespace detail {
 bool params_valid(const sw2d_params* p) { return params_ok(p); }
 StepCoef make_coef(const sw2d_params* p) { return ::make_coef(p); }
 void set_hip_message(const char* msg) { std::snprintf(g_hip_msg, sizeof g_hip_msg, "%s", msg); }
+int step_queued(sw2d_t h, int32_t nsteps, FoldQueue& q) {
+    if (!h || nsteps < 0) return SW2D_ESTATE;
+    return enqueue_steps(h, nsteps, q, nullptr, nullptr);
+}
 bool handle_info(sw2d_t h, hipStream_t* stream, int* nx, int* ny) {
     if (!h) return false;
     *stream = h->stream;
@@ -311,7 +325,10 @@ int sw2d_create(const sw2d_params* p, const float* d_H, const uint8_t* d_mask, f
 
 int sw2d_step(sw2d_t h, int32_t nsteps) {
     if (!h || nsteps < 0) return SW2D_ESTATE;
-    return enqueue_steps(h, nsteps, nullptr, nullptr);
+    FoldQueue q;
+    const int rc = enqueue_steps(h, nsteps, q, nullptr, nullptr);
+    const int rf = flush_folds(h, q);
+    return rc != SW2D_OK ? rc : rf;
 }
 
 int sw2d_step_timed(sw2d_t h, int32_t nsteps, double* mean_step_ms) {
@@ -325,7 +342,8 @@ int sw2d_step_timed(sw2d_t h, int32_t nsteps, double* mean_step_ms) {
         }
     }
     double total_ms = 0.0;
-    int rc = enqueue_steps(h, nsteps, ev, &total_ms);
+    FoldQueue q;
+    int rc = enqueue_steps(h, nsteps, q, ev, &total_ms);
     for (int i = 0; i < 2 * kFoldChunk; ++i) (void)hipEventDestroy(ev[i]);
     if (rc == SW2D_OK) {
         hipError_t e = hipStreamSynchronize(h->stream);
@@ -345,22 +363,22 @@ int sw2d_step_unfused(sw2d_t h, int32_t nsteps, float* d_scratch, size_t scratch
     if (h->p.flags != 0) return SW2D_EINVAL;  // the comparison path has no model variants
     if (scratch_bytes < sw2d_unfused_scratch_bytes(&h->p)) return SW2D_ENOSPC;
     const int nparts = h->part_capacity < 1024 ? h->part_capacity : 1024;
-    int pending = 0;
+    FoldQueue q;
     for (int32_t s = 0; s < nsteps; ++s) {
         float* const* src = h->state[h->cur];
         float* const* dst = h->state[h->cur ^ 1];
         SW2D_HIP(launch_unfused_step(src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], d_scratch, h->p.nx,
-                                     h->p.ny, h->coef, h->part + (size_t)pending * h->part_capacity, nparts,
-                                     h->stream));
+                                     h->p.ny, h->coef, h->part + q.used, nparts, h->stream));
+        if (q.runs.n == 0) q.runs.run[q.runs.n++] = {0, nparts, h->part_capacity, 0};
         h->cur ^= 1;
         h->step += 1;
-        if (++pending == kFoldChunk) {
-            int rc = flush_folds(h, pending, nparts, h->part_capacity);
+        q.used += h->part_capacity;
+        if (++q.pending == kFoldChunk) {
+            const int rc = flush_folds(h, q);
             if (rc) return rc;
-            pending = 0;
         }
     }
-    return flush_folds(h, pending, nparts, h->part_capacity);
+    return flush_folds(h, q);
 }
 
 int sw2d_set_band_rows(sw2d_t h, int32_t rows) {

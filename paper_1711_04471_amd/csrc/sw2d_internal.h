@@ -196,10 +196,18 @@ hipError_t launch_step(int kvar, const float* eta, const float* u, const float* 
 hipError_t launch_stepk(int K, int kvar, const float* eta, const float* u, const float* v, const float* hp,
                         float* eta_o, float* u_o, float* v_o, FoldPartial* part, int stride,
                         const StepGeometry& geo, const StepCoef& k, hipStream_t s);
-// Partials of step s of the chunk start at part + s * stride; nparts of them are valid.
-hipError_t launch_fold(const FoldPartial* part, int nparts, int stride, int nsteps,
-                       int64_t first_step, sw2d_red* ring, int ring_cap, double cell_area,
-                       double h_sum, hipStream_t s);
+// Runs of steps whose partials wait to be folded: step i of a run has its parts at
+// part + offset + i * stride. Several runs, as a call of 4 + 1 steps leaves, go into one launch.
+struct FoldRuns {
+    static constexpr int kMax = 4;
+    int n;
+    struct {
+        int64_t offset;
+        int nparts, stride, first;  // first: its first step among the steps of all runs
+    } run[kMax];
+};
+hipError_t launch_fold(const FoldPartial* part, const FoldRuns& runs, int nsteps, int64_t first_step, sw2d_red* ring,
+                       int ring_cap, double cell_area, double h_sum, hipStream_t s);
 // Validation + packing, then sum_wet H; scratch holds kHsumBlocks doubles.
 // The paper-shaped split: dyn, shapiro, velocity update, then a fold over the new state
 // into part[0..nparts). scratch holds 3 nx ny floats.

@@ -221,14 +221,21 @@ __global__ __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(3
 // Final level of the folds: one workgroup per step adds that step's partials in a
 // fixed order and writes the ring entry. h_sum = sum over water cells of H.
 __global__ __launch_bounds__(kFoldThreads) void sw2d_fold_kernel(const FoldPartial* __restrict__ part,
-                                                                 int nparts, int stride,
-                                                                 int64_t first_step,
+                                                                 FoldRuns runs, int64_t first_step,
                                                                  sw2d_red* __restrict__ ring,
                                                                  int ring_cap, double cell_area,
                                                                  double h_sum) {
     __shared__ double s_disp[kFoldThreads];
     __shared__ float s_mu[kFoldThreads], s_mv[kFoldThreads];
-    const FoldPartial* p = part + (size_t)blockIdx.x * stride;
+    int64_t at = 0;
+    int nparts = 0;
+#pragma unroll
+    for (int i = 0; i < FoldRuns::kMax; ++i)
+        if (i < runs.n && (int)blockIdx.x >= runs.run[i].first) {
+            at = runs.run[i].offset + (int64_t)((int)blockIdx.x - runs.run[i].first) * runs.run[i].stride;
+            nparts = runs.run[i].nparts;
+        }
+    const FoldPartial* p = part + at;
     double disp = 0.0;
     float mu = 0.f, mv = 0.f;
     for (int i = threadIdx.x; i < nparts; i += kFoldThreads) {
@@ -399,11 +406,10 @@ hipError_t launch_stepk(int K, int kvar, const float* eta, const float* u, const
     return hipGetLastError();
 }
 
-hipError_t launch_fold(const FoldPartial* part, int nparts, int stride, int nsteps,
-                       int64_t first_step, sw2d_red* ring, int ring_cap, double cell_area,
-                       double h_sum, hipStream_t s) {
-    hipLaunchKernelGGL(sw2d_fold_kernel, dim3(nsteps), dim3(kFoldThreads), 0, s, part, nparts,
-                       stride, first_step, ring, ring_cap, cell_area, h_sum);
+hipError_t launch_fold(const FoldPartial* part, const FoldRuns& runs, int nsteps, int64_t first_step, sw2d_red* ring,
+                       int ring_cap, double cell_area, double h_sum, hipStream_t s) {
+    hipLaunchKernelGGL(sw2d_fold_kernel, dim3(nsteps), dim3(kFoldThreads), 0, s, part, runs, first_step, ring, ring_cap,
+                       cell_area, h_sum);
     return hipGetLastError();
 }
 

@@ -67,20 +67,24 @@ int scratch_for_stream(hipStream_t s, float** out) {
     return SW2D_OK;
 }
 
-// n corrected coarse steps with the network output staged in `delta` (3 planes of the grid).
+// n corrected coarse steps with the network output staged in `delta` (3 planes of the grid). The
+// steps' folds are added together where the partials have room (a launch of their own each took 3 of
+// the 23 us of a corrected step on a small grid).
 int advance_corrected(sw2d_t coarse, hipStream_t s, int nx, int ny, int32_t nsteps, const float* H,
                       const uint8_t* mask, const float* mean, const float* std_, const uint16_t* const* wk,
                       const float* const* bias, const float* t_std, float* delta) {
-    for (int32_t n = 0; n < nsteps; ++n) {
+    sw2d::detail::FoldQueue folds;
+    int rc = SW2D_OK;
+    for (int32_t n = 0; n < nsteps && rc == SW2D_OK; ++n) {
         float *e, *u, *v;
-        int rc = sw2d_state(coarse, &e, &u, &v);
+        rc = sw2d_state(coarse, &e, &u, &v);
         if (rc == SW2D_OK) rc = sw2d_cnn_forward(e, u, v, H, mask, nx, ny, mean, std_, wk, bias, delta, s);
-        if (rc == SW2D_OK) rc = sw2d_step(coarse, 1);
+        if (rc == SW2D_OK) rc = sw2d::detail::step_queued(coarse, 1, folds);
         if (rc == SW2D_OK) rc = sw2d_state(coarse, &e, &u, &v);
         if (rc == SW2D_OK) rc = fail(launch_correct(e, u, v, delta, mask, ny, nx, t_std, s), "sw2d_surrogate_advance");
-        if (rc != SW2D_OK) return rc;
     }
-    return SW2D_OK;
+    const int rf = sw2d::detail::flush_folds(coarse, folds);
+    return rc != SW2D_OK ? rc : rf;
 }
 
 bool adam_hyper(int32_t t, float lr, float beta1, float beta2, float eps, AdamHyper* hp) {
