@@ -318,37 +318,43 @@ __global__ __launch_bounds__(kConvThreads) void conv3x3_kernel(const uint16_t* _
 }
 
 // ------------------------------------------------------------------------------ fused forward
-// The four layers of one image in one pass (inference). A workgroup owns a kFuTH x kFuTW tile
+// The four layers of one image in one pass (inference). A workgroup owns a TH x kFuTW tile
 // of output pixels and computes every layer over the tile grown by the receptive field still
 // ahead of it: layer 1 over (TH + 6) x (TW + 6) pixels of the (TH + 8) x (TW + 8) packed input,
 // layer 2 over (TH + 4) x (TW + 4), layer 3 over (TH + 2) x (TW + 2), layer 4 over the tile.
 // The maps stay in LDS, two buffers used in turn; a map's pixels outside the image are stored
-// as 0, which is the next layer's zero padding. A layer's pixels are taken 32 at a time in
-// row-major order of its region (the lane's address carries the row wrap), so the MFMA blocks
-// do not depend on the region's width. Taps, channel chunks, the packing of the input and the
-// epilogues are those of the layer-by-layer kernels: the output is bitwise theirs.
-constexpr int kFuTH = 16;
+// as 0, which is the next layer's zero padding. A layer's pixels are taken 32 at a time along the
+// pairs of rows of its region (the lane's address carries the wrap), two rows per block, so that an
+// input row's operands serve both. Taps, channel chunks, the packing of the input and the epilogues
+// are those of the layer-by-layer kernels: the output is bitwise theirs.
+// Bound by the matrix cores and the barriers between the layers: a 16 x 32 tile takes 21,000 cycles
+// with 11,500 of products on the busiest SIMD (26,700 with one row per block, weights read by all
+// waves with bank conflicts and waits behind the output's stores); a 1024^2 image 78-85 us (before
+// 106), of which its 21 MB take 5.
 constexpr int kFuTW = 32;
 constexpr int kFuThreads = 512;
 constexpr int kFuWaves = kFuThreads / 64;
 
-template <int L>  // the region of layer L's output; L = 0 is the packed input
+template <int TH, int L>  // the region of layer L's output; L = 0 is the packed input
 struct FuRegion {
     static constexpr int kHalo = 4 - L;
-    static constexpr int kRows = kFuTH + 2 * kHalo;
+    static constexpr int kRows = TH + 2 * kHalo;
     static constexpr int kCols = kFuTW + 2 * kHalo;
     static constexpr int kPix = kRows * kCols;
     static constexpr int kStride = (L == 0 ? 32 : 64) + 16;  // bytes per pixel, 16 B aligned, spreads banks
     static constexpr int kBytes = kPix * kStride;
 };
-// buffer A holds layer 1's map, then layer 3's; buffer B the packed input, then layer 2's map
-constexpr int kFuBufA = FuRegion<1>::kBytes;
-constexpr int kFuBufB = FuRegion<0>::kBytes > FuRegion<2>::kBytes ? FuRegion<0>::kBytes : FuRegion<2>::kBytes;
-static_assert(FuRegion<3>::kBytes + 9 * 32 * 16 * 2 <= kFuBufA, "layer 3 map and layer 1 weights in buffer A");
 constexpr int kFuWSlot = 9 * 32 * 32 * 2;  // one layer's BF16 weights (the widest)
-constexpr int kFuBiasBytes = 4 * 32 * 4;
-constexpr int kFuLds = kFuBufA + kFuBufB + 2 * kFuWSlot + kFuBiasBytes;
-constexpr int kFuRawPer = (FuRegion<0>::kPix + kFuThreads - 1) / kFuThreads;  // input pixels per thread
+
+template <int TH>
+struct FuLds {
+    // buffer A holds layer 1's map, then layer 3's; buffer B the packed input, then layer 2's map
+    static constexpr int kBufA = FuRegion<TH, 1>::kBytes;
+    static constexpr int kBufB =
+        FuRegion<TH, 0>::kBytes > FuRegion<TH, 2>::kBytes ? FuRegion<TH, 0>::kBytes : FuRegion<TH, 2>::kBytes;
+    static_assert(FuRegion<TH, 3>::kBytes + 9 * 32 * 16 * 2 <= kBufA, "layer 3 map and layer 1 weights in buffer A");
+    static constexpr int kBytes = kBufA + kBufB + 2 * kFuWSlot + 4 * 32 * 4;
+};
 
 typedef short i16x2 __attribute__((ext_vector_type(2)));
 
@@ -370,11 +376,11 @@ __device__ __forceinline__ f32x16 bias_pattern(const float* __restrict__ bias, i
 }
 
 // Output of a block row: pixel (ry, rx) of the region, channels 8 q + 4 half + (0..3) of this lane.
-template <int L, bool kLast>
+template <int TH, int L, bool kLast>
 __device__ __forceinline__ void fused_store(const f32x16& acc, unsigned char* __restrict__ out_lds,
                                             float* __restrict__ out_f, int ry, int rx, bool valid, int y0, int x0,
                                             int H, int W, int half) {
-    using Out = FuRegion<L>;
+    using Out = FuRegion<TH, L>;
     const int gy = y0 - Out::kHalo + ry, gx = x0 - Out::kHalo + rx;
     const bool inside = valid && gy >= 0 && gy < H && gx >= 0 && gx < W;
     if constexpr (!kLast) {
@@ -423,18 +429,17 @@ __device__ __forceinline__ void fused_weights(bf16x8 (&a)[9][2], const unsigned 
 // (or the next block's first) are read while the current row's products run. The weights a are
 // replaced by the next layer's (KNEXT channels, in next_slot) once the wave's last products are
 // issued, beside its last stores.
-template <int L, int KIN, bool kLast, int KNEXT>
+template <int TH, int L, int KIN, bool kLast, int KNEXT>
 __device__ __forceinline__ void fused_layer(const unsigned char* __restrict__ in_lds, unsigned char* __restrict__ out_lds,
                                             bf16x8 (&a)[9][2], const unsigned char* __restrict__ next_slot, const float* __restrict__ bias_lds,
                                             float* __restrict__ out_f, int y0, int x0, int H, int W, int wave,
                                             int half, int j) {
-    using In = FuRegion<L - 1>;
-    using Out = FuRegion<L>;
+    using In = FuRegion<TH, L - 1>;
+    using Out = FuRegion<TH, L>;
     constexpr int kK = KIN / 16;
     constexpr int kPairs = Out::kRows / 2 * Out::kCols;
     constexpr int kBlocks = (kPairs + 31) / 32;
     static_assert(Out::kRows % 2 == 0, "row pairs");
-    static_assert(kBlocks >= kFuWaves, "every wave has a block");
     const f32x16 bias = bias_pattern(bias_lds, half);
     bf16x8 b[2][3][kK];
     auto place = [&](int blk, int& ry, int& rx) {
@@ -480,20 +485,23 @@ __device__ __forceinline__ void fused_layer(const unsigned char* __restrict__ in
             fused_weights<KNEXT>(a, next_slot, 32 * half + j);
             if constexpr (kLast) __builtin_amdgcn_s_waitcnt(0);  // the staged weights, before the stores
         }
-        fused_store<L, kLast>(up, out_lds, out_f, cy, cx, valid, y0, x0, H, W, half);
-        fused_store<L, kLast>(low, out_lds, out_f, cy + 1, cx, valid, y0, x0, H, W, half);
+        fused_store<TH, L, kLast>(up, out_lds, out_f, cy, cx, valid, y0, x0, H, W, half);
+        fused_store<TH, L, kLast>(low, out_lds, out_f, cy + 1, cx, valid, y0, x0, H, W, half);
     }
+    if (kBlocks < kFuWaves && wave >= kBlocks) fused_weights<KNEXT>(a, next_slot, 32 * half + j);
 }
 
+template <int TH>
 __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputNorm nrm, FusedNet net,
                                                                float* __restrict__ out_f, int H, int W) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[kFuLds];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[FuLds<TH>::kBytes];
     unsigned char* bufA = lds;
-    unsigned char* bufB = lds + kFuBufA;
-    unsigned char* wslot[2] = {lds + kFuBufA + kFuBufB, lds + kFuBufA + kFuBufB + kFuWSlot};
-    float* bias_lds = reinterpret_cast<float*>(lds + kFuBufA + kFuBufB + 2 * kFuWSlot);
+    unsigned char* bufB = lds + FuLds<TH>::kBufA;
+    unsigned char* wslot[2] = {lds + FuLds<TH>::kBufA + FuLds<TH>::kBufB, lds + FuLds<TH>::kBufA + FuLds<TH>::kBufB + kFuWSlot};
+    float* bias_lds = reinterpret_cast<float*>(lds + FuLds<TH>::kBufA + FuLds<TH>::kBufB + 2 * kFuWSlot);
+    constexpr int kFuRawPer = (FuRegion<TH, 0>::kPix + kFuThreads - 1) / kFuThreads;  // input pixels per thread
     const int tiles_x = (W + kFuTW - 1) / kFuTW;
-    const int total = tiles_x * ((H + kFuTH - 1) / kFuTH);
+    const int total = tiles_x * ((H + TH - 1) / TH);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int half = lane / 32, j = lane % 32;
     if (threadIdx.x < 128) bias_lds[threadIdx.x] = net.bias[threadIdx.x / 32][threadIdx.x % 32];
@@ -506,9 +514,9 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
     auto raw_pixel = [&](int tile, int q, bool& in) -> unsigned {
         const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
         const int e = threadIdx.x + q * kFuThreads;
-        const int r = e / FuRegion<0>::kCols, c = e - r * FuRegion<0>::kCols;
-        const int gy = ty * kFuTH - FuRegion<0>::kHalo + r, gx = tx * kFuTW - FuRegion<0>::kHalo + c;
-        in = e < FuRegion<0>::kPix && gy >= 0 && gy < H && gx >= 0 && gx < W;
+        const int r = e / FuRegion<TH, 0>::kCols, c = e - r * FuRegion<TH, 0>::kCols;
+        const int gy = ty * TH - FuRegion<TH, 0>::kHalo + r, gx = tx * kFuTW - FuRegion<TH, 0>::kHalo + c;
+        in = e < FuRegion<TH, 0>::kPix && gy >= 0 && gy < H && gx >= 0 && gx < W;
         return in ? (unsigned)gy * (unsigned)W + (unsigned)gx : 0u;
     };
     auto fetch = [&](int tile) {
@@ -529,12 +537,12 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
             const int e = threadIdx.x + q * kFuThreads;
             bool in;
             raw_pixel(tile, q, in);
-            if (e < FuRegion<0>::kPix) {
+            if (e < FuRegion<TH, 0>::kPix) {
                 const float x[5] = {rx_[q][0], rx_[q][1], rx_[q][2], rx_[q][3], rm_[q] ? 1.f : 0.f};
                 uint4 ca, cb;
                 pack_values(x, 0, nrm, ca, cb);  // no noise at inference
                 if (!in) ca = cb = make_uint4(0u, 0u, 0u, 0u);
-                uint4* dst = reinterpret_cast<uint4*>(bufB + e * FuRegion<0>::kStride);
+                uint4* dst = reinterpret_cast<uint4*>(bufB + e * FuRegion<TH, 0>::kStride);
                 dst[0] = ca;
                 dst[1] = cb;
             }
@@ -569,7 +577,7 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
     // its last read. Layers 2-4 take two slots in turn, whose roles swap from tile to tile; layer 1
     // has the tail of buffer A, free from layer 3 on. All copies land beside a long layer, and none
     // is waited for behind layer 4's stores.
-    unsigned char* const s1 = bufA + FuRegion<3>::kBytes;
+    unsigned char* const s1 = bufA + FuRegion<TH, 3>::kBytes;
     bf16x8 w[9][2];
     wstage(0, s1);
     wstage(1, wslot[0]);
@@ -582,24 +590,24 @@ __global__ __launch_bounds__(kFuThreads) void cnn_fused_kernel(RawIn raw, InputN
     fused_weights<16>(w, s1, lane);
     for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
         const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-        const int y0 = ty * kFuTH, x0 = tx * kFuTW;
+        const int y0 = ty * TH, x0 = tx * kFuTW;
         const int next = tile + (int)gridDim.x;
         __syncthreads();  // packed input, layer 2's and 3's weights in place; the last tile's layer 4 done
-        fused_layer<1, 16, false, 32>(bufB, bufA, w, wslot[0], bias_lds, nullptr, y0, x0, H, W, wave, half, j);
+        fused_layer<TH, 1, 16, false, 32>(bufB, bufA, w, wslot[0], bias_lds, nullptr, y0, x0, H, W, wave, half, j);
         __syncthreads();
         wstage(3, wslot[0]);
         fetch(next < total ? next : tile);  // no branch: its loads stay in flight
-        fused_layer<2, 32, false, 32>(bufA, bufB, w, wslot[1], bias_lds + 32, nullptr, y0, x0, H, W, wave, half, j);
+        fused_layer<TH, 2, 32, false, 32>(bufA, bufB, w, wslot[1], bias_lds + 32, nullptr, y0, x0, H, W, wave, half, j);
         publish();
         wstage(0, s1);
-        fused_layer<3, 32, false, 32>(bufB, bufA, w, wslot[0], bias_lds + 64, nullptr, y0, x0, H, W, wave, half, j);
+        fused_layer<TH, 3, 32, false, 32>(bufB, bufA, w, wslot[0], bias_lds + 64, nullptr, y0, x0, H, W, wave, half, j);
         publish();
         wstage(1, wslot[1]);
         wstage(2, wslot[0]);
         // buffer B is free: layer 4 reads buffer A only. One half of the waves packs the next input
         // before its products, the other after, so the two share a SIMD's units.
         if (next < total && wave < kFuWaves / 2) commit(next);
-        fused_layer<4, 32, true, 16>(bufA, nullptr, w, s1, bias_lds + 96, out_f, y0, x0, H, W, wave, half, j);
+        fused_layer<TH, 4, 32, true, 16>(bufA, nullptr, w, s1, bias_lds + 96, out_f, y0, x0, H, W, wave, half, j);
         if (next < total && wave >= kFuWaves / 2) commit(next);
         unsigned char* const t = wslot[0];
         wslot[0] = wslot[1];
@@ -1536,7 +1544,7 @@ hipError_t launch_pack_input(const float* eta, const float* u, const float* v, c
 // Workgroups of `kernel` the current device holds at once (CUs x occupancy), cached per
 // device and kernel; 0 when the query fails.
 int resident_groups(const void* kernel, int threads) {
-    constexpr int kDevs = 16, kSlots = 16;
+    constexpr int kDevs = 16, kSlots = 32;
     static thread_local const void* keys[kDevs][kSlots] = {};
     static thread_local int vals[kDevs][kSlots] = {};
     int dev = 0;
@@ -1576,14 +1584,34 @@ hipError_t launch_conv3x3_correct(const uint16_t* in, const uint16_t* Wk, const 
     return hipGetLastError();
 }
 
+// The tile height. A tile takes about as long as 10 rows and its own (a round of 256 workgroups, the
+// whole corrected step around it: 23.5 us at 16 rows, 22.1 at 12, 21.4 at 10, 18.9 at 6), so higher
+// tiles recompute less and lower ones serve images that leave CUs idle or a last round nearly empty
+// (us per corrected step at 16, 12, 10 and 6 rows: 64^2 21.3, 20.6, 20.0, 19.0; 300 x 221 23.5, 22.1,
+// 21.4, 26.7; 400^2 34.2, 31.9, 37.3, 41.0; 450^2 35.2, 40.3, 38.6, 48.0).
 hipError_t launch_cnn_fused(const RawIn& raw, const InputNorm& nrm, const FusedNet& net, float* out_f, int H,
                             int W, hipStream_t s) {
-    const int tiles = ((W + kFuTW - 1) / kFuTW) * ((H + kFuTH - 1) / kFuTH);
-    const int cap = resident_groups(reinterpret_cast<const void*>(&cnn_fused_kernel), kFuThreads);
-    if (cap < 1) return hipErrorInvalidDeviceFunction;
-    hipLaunchKernelGGL(cnn_fused_kernel, dim3(tiles < cap ? tiles : cap), dim3(kFuThreads), 0, s, raw, nrm, net, out_f,
-                       H, W);
-    return hipGetLastError();
+    auto tiles = [&](int th) { return (int64_t)((W + kFuTW - 1) / kFuTW) * ((H + th - 1) / th); };
+    auto go = [&](auto kernel, int th) {
+        const int cap = resident_groups(reinterpret_cast<const void*>(kernel), kFuThreads);
+        if (cap < 1) return hipErrorInvalidDeviceFunction;
+        const int64_t n = tiles(th);
+        hipLaunchKernelGGL(kernel, dim3(n < cap ? (int)n : cap), dim3(kFuThreads), 0, s, raw, nrm, net, out_f, H, W);
+        return hipGetLastError();
+    };
+    int th = 0;
+    int64_t least = 0;
+    for (const int h : {16, 12, 10, 6}) {
+        const int64_t cost = (tiles(h) + kCus - 1) / kCus * (h + 10);
+        if (th == 0 || cost < least) {
+            th = h;
+            least = cost;
+        }
+    }
+    if (th == 6) return go(&cnn_fused_kernel<6>, 6);
+    if (th == 10) return go(&cnn_fused_kernel<10>, 10);
+    if (th == 12) return go(&cnn_fused_kernel<12>, 12);
+    return go(&cnn_fused_kernel<16>, 16);
 }
 
 hipError_t launch_conv3x3(int kin, int mode, const uint16_t* in, const uint16_t* Wk, const float* bias,
