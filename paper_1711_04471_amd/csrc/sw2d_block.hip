@@ -14,10 +14,17 @@ __global__ __launch_bounds__(kWave * kBlockWaves) void sw2d_block_kernel(
     constexpr int W = kBlockWaves;
     __shared__ BlockShared<W, kVar> sh;
     __shared__ BlockFoldShared<W> fsh;
-    // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of tiles
-    const int q = geo.nblocks / kXcds, rem = geo.nblocks % kXcds;
-    const int x = blockIdx.x % kXcds;
-    const int tile = x * q + min(x, rem) + (int)blockIdx.x / kXcds;
+    // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of tiles, or, of a grid read from
+    // HBM (which takes the highest tiles), runs of kBlockRun tiles in turn
+    const int b = blockIdx.x, x = b % kXcds;
+    int tile;
+    if (R < 8 || geo.contiguous) {
+        const int q = geo.nblocks / kXcds, rem = geo.nblocks % kXcds;
+        tile = x * q + min(x, rem) + b / kXcds;
+    } else {
+        constexpr int kTurn = kBlockRun * kXcds;
+        tile = b < geo.nblocks / kTurn * kTurn ? b / kTurn * kTurn + x * kBlockRun + b % kTurn / kXcds : b;
+    }
     const int band = tile / geo.strips, strip = tile - band * geo.strips;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
     constexpr int T = W * R, kSouth = block_south(kVar) * K, kNorth = 2 * K, kWest = block_west_lanes(K, kVar);
