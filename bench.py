@@ -5,9 +5,9 @@ Shapiro filter, velocity update and the per-step folds) of the 8192 x 8192 basin
 (dx = 250 m, seeded bathymetry, land disks and 8 bumps), with the state resident in HBM.
 value = nx * ny * steps / wall time, in Mcell-steps/s, from the median of REPS timed
 repetitions of exactly ``--steps`` steps each (every repetition bracketed by device
-synchronisations). By default the step kernel advances 4 steps per pass over the grid with
-two adjacent columns per lane (temporal blocking; the state equals single steps bit for bit
-and the folds are still taken every step). The roofline object prices the step kernel
+synchronisations). By default the step kernel advances 4 steps per pass over tiles held in
+registers (temporal blocking; the state equals single steps bit for bit and the folds are
+still taken every step). The roofline object prices the step kernel
 against HBM: read eta, u, v, H and write eta, u, v once per launch (28 B per cell and pass)
 against MI355X's 8 TB/s, with the launch duration from HIP events recorded on the library's
 stream around the whole timed sequence divided by its step-kernel launches (so it includes
@@ -150,9 +150,16 @@ SURROGATE_PASS = (4, 56)
 N_COARSE, JUDGE_EVERY, THRESHOLD = 500, 50, 1e-3
 
 
+def steps_per_launch(case, spp):
+    """Steps a launch advances: grids held in the last-level cache take 4 over register tiles whatever
+    the steps per pass."""
+    return 4 if case.nx * case.ny <= 1 << 23 else spp
+
+
 def kernel_name(spp):
-    # both workloads have an even number of columns: the 8-byte row-access instance
-    return "sw2d_step_kernel<0>" if spp == 1 else f"sw2d_stepk_pair_kernel<{spp}, true>"
+    # 4 steps go over register tiles; the row pipelines' 8-byte row-access instance otherwise (both
+    # workloads have an even number of columns)
+    return {1: "sw2d_step_kernel<0>", 4: "sw2d_block_kernel<4, R, 0>"}.get(spp, f"sw2d_stepk_pair_kernel<{spp}, true>")
 
 
 def counter_record(spp):
@@ -160,7 +167,7 @@ def counter_record(spp):
     VALU activity), or None when there is none for this kernel or its sources have changed
     since it was taken."""
     import hashlib
-    tag = "sw2d_step_kernel" if spp == 1 else f"sw2d_stepk{spp}_pair_kernel"
+    tag = {1: "sw2d_step_kernel", 4: "sw2d_block_kernel"}.get(spp, f"sw2d_stepk{spp}_pair_kernel")
     path = os.path.join(ROOT, "profiles", f"{tag}_basin_8192_traffic.json")
     if not os.path.exists(path):
         return None
@@ -242,12 +249,12 @@ def cpu_model() -> str:
 
 
 BATCH_PASS = 3  # steps per pass of the batched kernel
-BATCH_LAUNCH_PASSES = 16  # passes per persistent launch
+BATCH_LAUNCH_PASSES = 16  # passes per launch where the launch is persistent
 
 
 def batched_leg(steps, warmup, log, rows_uniform=0, sequential=True):
     """The 256-member ensemble (sides 128..1024, own bathymetry, mask, bumps and dt each)
-    advanced by the persistent batched launch at BATCH_PASS steps per pass, against the same
+    advanced together at BATCH_PASS steps per pass (one launch per pass, a recorded graph), against the same
     members stepped one after another through sw2d_step on the same GPU (at one step per
     pass and at BATCH_PASS with 32-row bands; the faster is the comparison)."""
     import tempfile
@@ -309,7 +316,7 @@ def batched_leg(steps, warmup, log, rows_uniform=0, sequential=True):
         "roofline": {"bound": "hbm", "achieved": round(cells * BYTES_PER_CELL_STEP / K / (ev_ms * 1e-3) / 1e9, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(cells * BYTES_PER_CELL_STEP / K / (ev_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                     "basis": f"whole persistent sequence (HIP events), 28 B per cell and pass of {K} steps"},
+                     "basis": f"whole launch sequence (HIP events), 28 B per cell and pass of {K} steps"},
         "grid_workgroups": grid,
         "band_rows_by_class": {"%d-%d" % (lo, hi - 1): sorted({r for c, r in zip(cases, rows)
                                                               if autotune.size_class(int(c.nx)) == (lo, hi)})
@@ -528,7 +535,7 @@ def surrogate_leg(args, log):
 
 
 def variants_leg(case, steps, log):
-    """The single-step kernel with each model variant (bottom friction, velocity filter,
+    """One step per pass with each model variant (bottom friction, velocity filter,
     advection, all three, wetting and drying) on the same basin: same 28 B per cell-step,
     more arithmetic per cell. The kernels take every decision with selects, not branches,
     so their time does not depend on how many cells are dry. Friction, the velocity filter
@@ -551,7 +558,7 @@ def variants_leg(case, steps, log):
         gbs = cells * BYTES_PER_CELL_STEP / (ms * 1e-3) / 1e9
         out[name] = {"ms_per_step": round(ms, 5), "value": round(cells / ms / 1e3, 1),
                      "hbm_frac": round(gbs / HBM_PEAK_GBS, 4), "band_rows": VARIANT_ROWS[name]}
-    # the variants that also take several steps per pass (one column per lane), at their best
+    # variants at several steps per pass
     for name, flags in (("friction", FRICTION), ("filter_uv", FILTER_UV), ("wetdry", WETDRY)):
         K, rows = VARIANT_PASS[name]
         with Sw2d.from_case(case, flags=flags, cd=0.0025, hmin=0.0625) as sim:
@@ -768,12 +775,13 @@ def main():
     med = order[REPS // 2]
     wall = walls[med]
     red = sim.reduce(min(args.steps, 16))
-    launches = -(-args.steps // spp)
+    spl = steps_per_launch(case, spp)
+    launches = -(-args.steps // spl)
     launch_ms = sorted(spans)[REPS // 2] / launches
     cells = case.nx * case.ny
     value = cells * args.steps / wall / 1e6
     achieved = cells * BYTES_PER_CELL_STEP / (launch_ms * 1e-3) / 1e9
-    flops = cells * spp * FLOP_PER_CELL_STEP / (launch_ms * 1e-3) / 1e12
+    flops = cells * spl * FLOP_PER_CELL_STEP / (launch_ms * 1e-3) / 1e12
     rec = counter_record(spp) if args.workload == "basin_8192" else None
     traffic = rec["hbm_bytes_per_launch"] if rec else None
     valu_busy = round(rec["valu"]["valu_busy"], 3) if rec and "valu" in rec else None
@@ -807,11 +815,11 @@ def main():
         "roofline": {**hbm,
                      "traffic": round(traffic / 1e9, 4) if traffic else None,
                      "traffic_unit": "GB per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-                     "kernel": kernel_name(spp), "kernel_ms": round(launch_ms, 5),
+                     "kernel": kernel_name(spl), "kernel_ms": round(launch_ms, 5),
                      "kernel_ms_basis": f"HIP events on the library's stream around each timed repetition "
                                         f"(median of {REPS}) / {launches} step-kernel launches, fold launches "
                                         "included",
-                     "steps_per_launch": spp, "other_bound": alu},
+                     "steps_per_launch": spl, "other_bound": alu},
         "reps": REPS,
         "rep_ms_per_step": [round(w / args.steps * 1e3, 5) for w in walls],
         "folds_last_step": {"vol_total": float(red["vol_total"][-1]),
