@@ -400,7 +400,7 @@ def _cnn_timings(net, trainer, case):
     # 128 B per pixel against 18,432 FLOP, 144 FLOP/B, below the BF16 ridge (2.5 PFLOP/s over
     # 8 TB/s, 312 FLOP/B), so HBM bounds it
     gbs = n * h * w * 128 / (ms * 1e-3) / 1e9
-    out["wgrad_32"] = {"kernel": "wgrad_kernel<32> + wgrad_reduce_kernel", "minibatch": f"{n}x{w}x{h}",
+    out["wgrad_32"] = {"kernel": "backward_kernel<32, false> + wgrad_reduce_kernel", "minibatch": f"{n}x{w}x{h}",
                        "ms": round(ms, 4), "bound": "hbm", "achieved_gbs": round(gbs, 1), "peak_gbs": HBM_PEAK_GBS,
                        "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes_per_pixel": 128,
                        "achieved_tflops": round(tf, 1), "peak_tflops": BF16_PEAK_TFLOPS,
@@ -465,6 +465,7 @@ def surrogate_leg(args, log):
     for seed in seeds:
         case = S.fine_basin(seed, n)
         with Sw2d.from_case(case) as plain:
+            plain.set_time_blocking(1)
             plain.step(10)
             t_single = plain.step_timed(4 * n_coarse) * 4 * n_coarse * 1e-3  # s for 2000 fine steps
         with fine_sim(case) as plain:
@@ -591,10 +592,8 @@ def shard_leg(case, log, parts=8):
         halo = 2 * spp
         strip = inputs.row_strip(case, j_lo, j_lo + own, halo)
         with Sw2d.from_case(strip) as sim:
-            if spp > 1:
-                sim.set_time_blocking(spp, rows=rows)
-            else:
-                sim.band_rows = rows
+            sim.band_rows = rows
+            sim.set_time_blocking(spp, rows=rows)
             sim.step(16)
             torch.cuda.synchronize()
             ms = sorted(sim.step_timed(96) for _ in range(REPS))[REPS // 2]
