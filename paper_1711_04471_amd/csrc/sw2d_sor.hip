@@ -13,22 +13,23 @@
 // f, and writes its own array - 16 B per cell and iteration, no half-used cache lines. The
 // split and the merge back to [nz][ny][nx] are one pass each per solve. A sweep thread owns one
 // position of its colour per plane (threads run along the rows of a plane, so they coalesce
-// across row ends) and takes 1 or 4 planes, all of its loads issued before the first is used
-// (walked one after another, 8 planes cost 8 load latencies: a sweep of 65 x 47 x 33 took 7.2 us
-// instead of 2.7, one of 300 x 300 x 90 13.5 us instead of 11.5; its 65 MB take 7.8 us at the
-// rate of a large copy inside the cache). The residual r = f - L p of
+// across row ends) and takes 4 planes, all of its loads issued before the first is used (walked one
+// after another, 8 planes cost 8 load latencies: a sweep of 300 x 300 x 90 took 13.5 us instead of
+// 11.5; its 65 MB take 7.8 us at the rate of a large copy inside the cache). Small grids take both
+// colours in one launch (sor_pair_kernel). The residual r = f - L p of
 // the state after iteration m is folded without an extra pass: a black cell's neighbours
 // are all red, so the black sweep of iteration m knows its residual right after the update;
 // a red cell's residual needs the black values of iteration m, which the red sweep of
 // iteration m + 1 reads before it overwrites the red cell. One residual-only pass per colour
-// covers the initial black cells and the final red cells. One pass per iteration (both colours in one
-// launch, new red values of a tile and its ring in LDS) was slower at every size and is gone: 2311 us
-// per solve of 300 x 300 x 90 against 1198, 1445 against 278 on 65 x 47 x 33. Workgroup partials (FP64 sum of
+// covers the initial black cells and the final red cells. One pass per iteration by walking planes
+// (new red values of a tile and its ring in LDS) was slower at every size and is gone: 2311 us per
+// solve of 300 x 300 x 90 against 1198, 1445 against 278 on 65 x 47 x 33. Workgroup partials (FP64 sum of
 // r^2, max |r| as magnitude bits) are added per iteration in a fixed order.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdio>
+#include <utility>
 
 #include "sw2d_internal.h"
 
@@ -53,13 +54,16 @@ struct SorGeometry {
     int nx, ny, nz, w, rows_q, planes, gx, gz, nblocks;  // w = ceil(nx / 2); rows_q = (ny - 2) w
 };
 
-// Planes per thread of a sweep. A thread's loads are all in flight at once, so a sweep of a small
-// grid costs a launch and one load latency, least with its cells spread over the device; a larger
-// one is bound by the cache's rate and its requests, and walking planes reads a z neighbour once
-// for the three cells that use it (us per 50-iteration solve at 1, 2, 4 and 8 planes: 65 x 47 x 33
-// 278, 370, 344, 418; 40 x 300 x 20 (107,000 positions) 292, 335, 368, 431; 128 x 128 x 64 (500,000)
-// 421, 417, 403, 456; 300 x 300 x 90 1699, 1400, 1238, 1211).
-constexpr int sor_planes(int64_t positions) { return positions < (1 << 18) ? 1 : 4; }
+// Grids of fewer positions than this take an iteration per launch (sor_pair_kernel), the others two
+// sweeps of 4 planes per thread. A small grid costs a launch and one load latency, whatever a thread
+// reads beside its own cells; a larger one is bound by the cache's rate and its requests (32 values per
+// position against 16), and walking planes reads a z neighbour once for the three cells that use it (us per
+// 50-iteration solve, an iteration per launch and the sweeps: 65 x 47 x 33 198 and 379, 40 x 300 x 20 222 and
+// 335, 128 x 128 x 64 (500,000 positions) 375 and 385, 160 x 120 x 60 (547,500) 402 and 414, 200 x 128 x 64
+// (781,000) 497 and 472, 300 x 300 x 90 1746 and 1232; sweeps of 1, 2, 4 and 8 planes on the last 1699, 1400,
+// 1238, 1211).
+constexpr int64_t kSorPairPositions = 5 << 17;
+constexpr int sor_planes(int64_t positions) { return positions < kSorPairPositions ? 1 : 4; }
 
 // Tile b of n in an order that gives each XCD (workgroup b runs on XCD b % 8) a contiguous range.
 __device__ __forceinline__ int sor_tile(int b, int n) {
@@ -124,10 +128,12 @@ __device__ __forceinline__ void sor_fold_group(double sum, unsigned mx, SorParti
     }
 }
 
-// [nz][ny][nx] -> the two colour arrays, for p and f, a position (two adjacent cells) per thread.
+// [nz][ny][nx] -> the two colour arrays, for p (twice where a second pair is given) and f, a
+// position (two adjacent cells) per thread.
 __global__ __launch_bounds__(256) void sor_split_kernel(const float* __restrict__ p, const float* __restrict__ f,
                                                         float* __restrict__ red, float* __restrict__ black,
                                                         float* __restrict__ f_red, float* __restrict__ f_black,
+                                                        float* __restrict__ red2, float* __restrict__ black2,
                                                         SorGeometry g) {
     const int per = (g.ny * g.w + 255) / 256;  // workgroups per plane
     const int k = blockIdx.x / per, q = (blockIdx.x - k * per) * 256 + threadIdx.x;
@@ -141,10 +147,12 @@ __global__ __launch_bounds__(256) void sor_split_kernel(const float* __restrict_
     if (both || !odd) {
         red[o] = odd ? p1 : p0;
         f_red[o] = odd ? f1 : f0;
+        if (red2) red2[o] = odd ? p1 : p0;
     }
     if (both || odd) {
         black[o] = odd ? p0 : p1;
         f_black[o] = odd ? f0 : f1;
+        if (black2) black2[o] = odd ? p0 : p1;
     }
 }
 
@@ -225,6 +233,70 @@ __global__ __launch_bounds__(kSorThreads) void sor_sweep_kernel(float* __restric
     sor_fold_group<kSorThreads>(acc, mx, part + tile);
 }
 
+// One iteration, both colours, in one launch (small grids): a thread updates the red and the black cell of its
+// position from the old arrays into the new ones. The black cell's six red neighbours are computed
+// from the old black cells around them as their own threads compute them (19 black values, 6 red and 7
+// right-hand sides, all loaded before the first is used), so a launch costs one load latency and
+// neither waits for another thread nor exchanges anything: the state is bitwise that of the two sweeps.
+__global__ __launch_bounds__(kSorThreads) void sor_pair_kernel(const float* __restrict__ R, const float* __restrict__ B,
+                                                               const float* __restrict__ FR,
+                                                               const float* __restrict__ FB, float* __restrict__ Rn,
+                                                               float* __restrict__ Bn, SorGeometry geo, SorCoef c,
+                                                               SorPartial* __restrict__ red_part,
+                                                               SorPartial* __restrict__ black_part) {
+#pragma clang fp contract(off)
+    const int nx = geo.nx, ny = geo.ny, nz = geo.nz, w = geo.w;
+    const int tile = sor_tile(blockIdx.x, geo.nblocks);
+    const int bz = tile / geo.gx, bx = tile - bz * geo.gx;
+    const int q = bx * kSorThreads + threadIdx.x;
+    const bool row_ok = q < geo.rows_q;
+    const int qc = row_ok ? q : 0;
+    const int j = 1 + qc / w, m = qc - (j - 1) * w, k = 1 + bz;
+    const int s = (j + k) & 1;      // the red cell is i = 2 m + s, the black one 2 m + 1 - s
+    const int d = s ? -1 : 1;       // towards the black cell's outer red neighbour
+    const int mf = min(max(m + d, 0), w - 1), mb = min(max(m - d, 0), w - 1);
+    const size_t plane = (size_t)ny * w;
+    const int jn2 = min(j + 2, ny - 1), js2 = max(j - 2, 0), ku2 = min(k + 2, nz - 1), kd2 = max(k - 2, 0);
+    const size_t row = (size_t)k * plane + (size_t)j * w, o = row + m, of = row + mf;
+    const size_t on = o + w, os = o - w, ou = o + plane, od = o - plane;
+    // black: own, the position ahead and behind, the rows and planes around, and around those
+    const float b = B[o], bf = B[of], bb = B[row + mb];
+    const float bn = B[on], bs = B[os], bu = B[ou], bd = B[od];
+    const float bfn = B[of + w], bfs = B[of - w], bfu = B[of + plane], bfd = B[of - plane];
+    const float bn2 = B[(size_t)k * plane + (size_t)jn2 * w + m], bs2 = B[(size_t)k * plane + (size_t)js2 * w + m];
+    const float bu2 = B[(size_t)ku2 * plane + (size_t)j * w + m], bd2 = B[(size_t)kd2 * plane + (size_t)j * w + m];
+    const float bnu = B[on + plane], bnd = B[on - plane], bsu = B[os + plane], bsd = B[os - plane];
+    const float r = R[o], rf = R[of], rn = R[on], rs = R[os], ru = R[ou], rd = R[od];
+    const float fr = FR[o], ff = FR[of], fn = FR[on], fs = FR[os], fu = FR[ou], fd = FR[od], fb = FB[o];
+    auto around = [&](float sx, float sy, float sz) { return fmaf(c.cz, sz, fmaf(c.cy, sy, c.cx * sx)); };
+    auto update = [&](float nb, float f, float pc) {
+        const float g = (nb - f) * c.inv_diag;
+        return fmaf(c.omega, g - pc, pc);
+    };
+    // new red values; a cell of the boundary layer keeps its own
+    const int ir = 2 * m + s, ib = 2 * m + 1 - s, inner = nx - 2;
+    const float nb_r = around(b + bb, bn + bs, bu + bd);
+    const bool red_in = ir >= 1 && ir <= inner;
+    const float r_new = red_in ? update(nb_r, fr, r) : r;
+    const int i_f = ir + 2 * d;  // the red cell ahead
+    const float f_new = i_f >= 1 && i_f <= inner ? update(around(bf + b, bfn + bfs, bfu + bfd), ff, rf) : rf;
+    // the red cells of the rows and planes around lie at the black cell's i
+    const bool col = ib >= 1 && ib <= inner;
+    const float n_new = col && j + 1 <= ny - 2 ? update(around(bn + bfn, bn2 + b, bnu + bnd), fn, rn) : rn;
+    const float s_new = col && j - 1 >= 1 ? update(around(bs + bfs, b + bs2, bsu + bsd), fs, rs) : rs;
+    const float u_new = col && k + 1 <= nz - 2 ? update(around(bu + bfu, bnu + bsu, bu2 + b), fu, ru) : ru;
+    const float d_new = col && k - 1 >= 1 ? update(around(bd + bfd, bnd + bsd, b + bd2), fd, rd) : rd;
+    const float nb_b = around(r_new + f_new, n_new + s_new, u_new + d_new);
+    const float b_new = update(nb_b, fb, b);
+    const bool live_r = row_ok && red_in, live_b = row_ok && col;
+    if (live_r) Rn[o] = r_new;
+    if (live_b) Bn[o] = b_new;
+    const float res_r = live_r ? fr - fmaf(-c.diag, r, nb_r) : 0.f;       // of the state before
+    const float res_b = live_b ? fb - fmaf(-c.diag, b_new, nb_b) : 0.f;   // of the new one
+    sor_fold_group<kSorThreads>((double)res_r * (double)res_r, __float_as_uint(res_r) & 0x7fffffffu, red_part + tile);
+    sor_fold_group<kSorThreads>((double)res_b * (double)res_b, __float_as_uint(res_b) & 0x7fffffffu, black_part + tile);
+}
+
 // Residual of state m = red partials of slot m + black partials of slot m, each added in
 // block order by a fixed tree; one workgroup per m.
 __global__ __launch_bounds__(kSorFoldThreads) void sor_fold_kernel(const SorPartial* __restrict__ red,
@@ -280,18 +352,22 @@ template <int COLOR, int MODE>
 hipError_t launch_sweep(float* own, const float* other, const float* f_own, const SorGeometry& g, const SorCoef& c,
                         SorPartial* part, hipStream_t s) {
     const dim3 grid(g.nblocks), block(kSorThreads);
-    if (g.planes == 1)
-        hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE, 1>), grid, block, 0, s, own, other, f_own, g, c, part);
-    else
+    if (g.planes == 4) {
         hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE, 4>), grid, block, 0, s, own, other, f_own, g, c, part);
-    return hipGetLastError();
+        return hipGetLastError();
+    }
+    if constexpr (MODE == kSorResidualOnly) {  // small grids update both colours in one launch
+        hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE, 1>), grid, block, 0, s, own, other, f_own, g, c, part);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 dim3 split_grid(const SorGeometry& g) { return dim3((unsigned)((g.ny * g.w + 255) / 256) * g.nz); }
 
 hipError_t launch_split(const float* p, const float* f, float* red, float* black, float* f_red, float* f_black,
-                        const SorGeometry& g, hipStream_t s) {
-    hipLaunchKernelGGL(sor_split_kernel, split_grid(g), dim3(256), 0, s, p, f, red, black, f_red, f_black, g);
+                        float* red2, float* black2, const SorGeometry& g, hipStream_t s) {
+    hipLaunchKernelGGL(sor_split_kernel, split_grid(g), dim3(256), 0, s, p, f, red, black, f_red, f_black, red2, black2, g);
     return hipGetLastError();
 }
 
@@ -312,10 +388,10 @@ extern "C" {
 size_t sw2d_sor_workspace_bytes(const sw2d_sor_params* p, int32_t iters) {
     if (!sor_params_ok(p) || iters < 0) return 0;
     const SorGeometry g = sor_geometry(p->nx, p->ny, p->nz);
-    // red, black, f red, f black (256 B aligned each), then the residual partials: iters + 1 slots per
-    // colour
+    // red, black, f red, f black (and a second red and black where an iteration is one launch; 256 B aligned
+    // each), then the residual partials: iters + 1 slots per colour
     const size_t arr = (colour_floats(g) * sizeof(float) + 255) / 256 * 256;
-    return 4 * arr + 2 * (size_t)(iters + 1) * g.nblocks * sizeof(SorPartial);
+    return (g.planes == 1 ? 6 : 4) * arr + 2 * (size_t)(iters + 1) * g.nblocks * sizeof(SorPartial);
 }
 
 int sw2d_sor_run(const sw2d_sor_params* p, float* d_p, const float* d_f, int32_t iters, sw2d_sor_res* d_res,
@@ -338,11 +414,23 @@ int sw2d_sor_run(const sw2d_sor_params* p, float* d_p, const float* d_f, int32_t
     float* FR = reinterpret_cast<float*>(base + 2 * arr);
     float* FB = reinterpret_cast<float*>(base + 3 * arr);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    auto* red = reinterpret_cast<SorPartial*>(base + 4 * arr);
+    const bool pairs = g.planes == 1;
+    float* R2 = pairs ? reinterpret_cast<float*>(base + 4 * arr) : nullptr;
+    float* B2 = pairs ? reinterpret_cast<float*>(base + 5 * arr) : nullptr;
+    auto* red = reinterpret_cast<SorPartial*>(base + (pairs ? 6 : 4) * arr);
     SorPartial* black = red + (size_t)(iters + 1) * g.nblocks;
-    hipError_t e = launch_split(d_p, d_f, R, B, FR, FB, g, s);
+    // both pairs start as the split state: the boundary layer is never written again
+    hipError_t e = launch_split(d_p, d_f, R, B, FR, FB, R2, B2, g, s);
     if (e == hipSuccess) e = launch_sweep<1, kSorResidualOnly>(B, R, FB, g, c, black, s);  // black part of state 0
     for (int32_t n = 0; n < iters && e == hipSuccess; ++n) {
+        if (pairs) {
+            hipLaunchKernelGGL(sor_pair_kernel, dim3(g.nblocks), dim3(kSorThreads), 0, s, R, B, FR, FB, R2, B2, g, c,
+                               red + (size_t)n * g.nblocks, black + (size_t)(n + 1) * g.nblocks);
+            e = hipGetLastError();
+            std::swap(R, R2);
+            std::swap(B, B2);
+            continue;
+        }
         e = launch_sweep<0, kSorUpdate>(R, B, FR, g, c, red + (size_t)n * g.nblocks, s);
         if (e == hipSuccess) e = launch_sweep<1, kSorUpdate>(B, R, FB, g, c, black + (size_t)(n + 1) * g.nblocks, s);
     }

@@ -1,6 +1,6 @@
-// sw2d_tile.h - the per-wave tile routine of the fused 2DSW step, shared by the
-// single-grid kernel and the batched persistent kernel (one arithmetic path, so a
-// batched instance is bitwise equal to the same basin stepped alone).
+// sw2d_tile.h - the formulas of the 2DSW step, shared by every kernel whatever its lane layout (one
+// arithmetic path, so the register tiles, the row pipelines and the ensembles give bitwise the same
+// state), and the row pipelines of one column per lane.
 #pragma once
 
 #include <hip/hip_runtime.h>

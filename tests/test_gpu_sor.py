@@ -134,3 +134,38 @@ def test_sweep_shapes_match_oracle(shape):
     _say(f"sor sweeps {shape}")
     p, res = _gpu(c)
     _check(c, p, res, c.iters)
+
+
+def _fma(a, b, c):
+    """FP32 fused multiply-add: exact product, one rounding (64-bit significand, then to 24)."""
+    return (np.longdouble(a) * np.longdouble(b) + np.longdouble(c)).astype(np.float32)
+
+
+@pytest.mark.parametrize("shape", [(3, 3, 3), (4, 5, 6), (9, 8, 7), (20, 7, 5), (33, 6, 9), (6, 40, 4)])
+def test_small_grids_bitwise(shape):
+    """The two-colour sweeps in FP32 with their fused multiply-adds, cell by cell as defined."""
+    from paper_1711_04471_amd.sw2d import SorSolver
+    nx, ny, nz = shape
+    rng = np.random.Generator(np.random.PCG64(nx * ny + nz))
+    p = rng.standard_normal((nz, ny, nx)).astype(np.float32)
+    f = rng.standard_normal((nz, ny, nx)).astype(np.float32)
+    hx, omega, iters = (4.0, 3.0, 2.0), 1.7, 4
+    cs = [1.0 / h**2 for h in hx]
+    cx, cy, cz, diag, inv, om = (np.float32(v) for v in (*cs, 2 * sum(cs), 1.0 / (2 * sum(cs)), omega))
+    gp, gf = torch.from_numpy(p.copy()).cuda(), torch.from_numpy(f).cuda()
+    solver = SorSolver(nx, ny, nz, *hx, omega, iters)
+    solver.run(gp, gf)
+    i, j, k = (np.arange(n) for n in (nx, ny, nz))
+    colour = (k[:, None, None] + j[None, :, None] + i[None, None, :]) % 2
+    inner = np.zeros(p.shape, dtype=bool)
+    inner[1:-1, 1:-1, 1:-1] = True
+    for _ in range(iters):
+        for c in (0, 1):
+            sx, sy, sz = np.zeros_like(p), np.zeros_like(p), np.zeros_like(p)
+            sx[:, :, 1:-1] = p[:, :, 2:] + p[:, :, :-2]
+            sy[:, 1:-1] = p[:, 2:] + p[:, :-2]
+            sz[1:-1] = p[2:] + p[:-2]
+            nb = _fma(cz, sz, _fma(cy, sy, cx * sx))
+            g = (nb - f) * inv
+            p = np.where(inner & (colour == c), _fma(om, g - p, p), p)
+    assert np.array_equal(gp.cpu().numpy(), p)
