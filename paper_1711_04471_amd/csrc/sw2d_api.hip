@@ -175,9 +175,11 @@ int add_pass_times(hipEvent_t* ev, int passes, double* total_ms) {
 
 // Enqueue nsteps steps in passes of pass_steps steps (a remainder takes one shorter pass), over
 // register tiles or through the row pipelines. The fold partials of successive passes are left in the
-// queue while slots last, then added by one fold launch. With events (2 per pass, at most kFoldChunk
+// queue while slots last, then added by one fold launch. A correction (one step over tiles only) is added
+// as the state is stored. With events (2 per pass, at most kFoldChunk
 // passes between folds) the step kernels are timed.
-int enqueue_steps(sw2d_ctx* h, int32_t nsteps, FoldQueue& q, hipEvent_t* ev, double* total_ms) {
+int enqueue_steps(sw2d_ctx* h, int32_t nsteps, FoldQueue& q, hipEvent_t* ev, double* total_ms,
+                  const StepCorrection* fix = nullptr) {
     const int kmax = pass_steps(h);
     BlockGeometry bg{};
     int bg_k = 0;
@@ -205,7 +207,10 @@ int enqueue_steps(sw2d_ctx* h, int32_t nsteps, FoldQueue& q, hipEvent_t* ev, dou
         float* const* dst = h->state[h->cur ^ 1];
         FoldPartial* part = h->part + q.used;
         if (ev) SW2D_HIP(hipEventRecord(ev[2 * passes], h->stream));
-        if (tiles)
+        if (fix)
+            SW2D_HIP(launch_block_corrected(src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, bg, h->coef,
+                                            *fix, h->stream));
+        else if (tiles)
             SW2D_HIP(launch_block(k, (int)h->p.flags, src[0], src[1], src[2], h->hp, dst[0], dst[1], dst[2], part, bg,
                                   h->coef, h->stream));
         else if (k >= 2)
@@ -237,6 +242,11 @@ void set_hip_message(const char* msg) { std::snprintf(g_hip_msg, sizeof g_hip_ms
 int step_queued(sw2d_t h, int32_t nsteps, FoldQueue& q) {
     if (!h || nsteps < 0) return SW2D_ESTATE;
     return enqueue_steps(h, nsteps, q, nullptr, nullptr);
+}
+bool corrects_in_step(sw2d_t h) { return h && h->p.flags == 0 && cached_grid(h) && tile_pass(h, 1); }
+int step_corrected(sw2d_t h, const StepCorrection& fix, FoldQueue& q) {
+    if (!corrects_in_step(h)) return SW2D_ESTATE;
+    return enqueue_steps(h, 1, q, nullptr, nullptr, &fix);
 }
 bool handle_info(sw2d_t h, hipStream_t* stream, int* nx, int* ny) {
     if (!h) return false;

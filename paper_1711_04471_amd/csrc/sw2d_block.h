@@ -106,13 +106,16 @@ struct BlockFolds {
     float max_u = 0.f, max_v = 0.f;
 };
 
-template <int K, int R, int W, int kVar = 0>
+struct BlockNoFix {};  // the state is stored as the steps leave it
+
+// Fix: what is done to the cells of a row before they are stored, after the folds.
+template <int K, int R, int W, int kVar = 0, typename Fix = BlockNoFix>
 __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const float* __restrict__ u_i,
                                            const float* __restrict__ v_i, const float* __restrict__ hp_i,
                                            float* __restrict__ eta_o, float* __restrict__ u_o,
                                            float* __restrict__ v_o, int nx, int ny, int rbase, int wave, int lane,
                                            int c0, bool owned, int j0, int j1, const StepCoef& k,
-                                           BlockShared<W, kVar>& sh, BlockFolds (&F)[K]) {
+                                           BlockShared<W, kVar>& sh, BlockFolds (&F)[K], const Fix& fix = Fix()) {
 #pragma clang fp contract(off)
     constexpr bool kFriction = (kVar & kVarFriction) != 0, kFilterUV = (kVar & kVarFilterUV) != 0;
     constexpr bool kAdv = (kVar & kVarAdvection) != 0, kWetDry = (kVar & kVarWetDry) != 0;
@@ -441,6 +444,7 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
     for (int r = 0; r < R; ++r) {
         const int row = rbase + r;
         if (row >= j0 && row < j1) {
+            if constexpr (!std::is_same_v<Fix, BlockNoFix>) fix(io, row, e[r], u[r], v[r]);
             io.store(eta_o, row, owned, e[r]);
             io.store(u_o, row, owned, u[r]);
             io.store(v_o, row, owned, v[r]);

@@ -19,6 +19,10 @@ struct FoldQueue {
     int64_t used = 0;   // slots
 };
 int step_queued(sw2d_t h, int32_t nsteps, FoldQueue& q);
+// Whether a single step of the handle can add a correction as it stores its state (plain model over
+// tiles), and such a step.
+bool corrects_in_step(sw2d_t h);
+int step_corrected(sw2d_t h, const StepCorrection& fix, FoldQueue& q);
 int flush_folds(sw2d_t h, FoldQueue& q);
 }  // namespace detail
 }  // namespace sw2d

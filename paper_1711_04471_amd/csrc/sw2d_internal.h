@@ -194,6 +194,19 @@ hipError_t launch_block(int K, int kvar, const float* eta, const float* u, const
                         float* eta_o, float* u_o, float* v_o, FoldPartial* part, const BlockGeometry& geo,
                         const StepCoef& k, hipStream_t s);
 
+// A correction added to the state that a step leaves: scale times delta's three planes [3][ny][nx], on
+// the water cells of mask and the faces between two of them.
+struct StepCorrection {
+    const float* delta;
+    const uint8_t* mask;
+    float scale[3];
+};
+// One step of the plain model over tiles (geometry for K = 1) with the correction added as the new state
+// is stored; the folds are of the state before it.
+hipError_t launch_block_corrected(const float* eta, const float* u, const float* v, const float* hp, float* eta_o,
+                                  float* u_o, float* v_o, FoldPartial* part, const BlockGeometry& geo,
+                                  const StepCoef& k, const StepCorrection& fix, hipStream_t s);
+
 // kvar: the model variants (0 for the plain step).
 hipError_t launch_step(int kvar, const float* eta, const float* u, const float* v, const float* hp,
                        float* eta_o, float* u_o, float* v_o, FoldPartial* part,

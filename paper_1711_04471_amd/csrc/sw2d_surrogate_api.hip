@@ -74,11 +74,17 @@ int advance_corrected(sw2d_t coarse, hipStream_t s, int nx, int ny, int32_t nste
                       const uint8_t* mask, const float* mean, const float* std_, const uint16_t* const* wk,
                       const float* const* bias, const float* t_std, float* delta) {
     sw2d::detail::FoldQueue folds;
+    const bool in_step = sw2d::detail::corrects_in_step(coarse);
+    const StepCorrection fix{delta, mask, {t_std[0], t_std[1], t_std[2]}};
     int rc = SW2D_OK;
     for (int32_t n = 0; n < nsteps && rc == SW2D_OK; ++n) {
         float *e, *u, *v;
         rc = sw2d_state(coarse, &e, &u, &v);
         if (rc == SW2D_OK) rc = sw2d_cnn_forward(e, u, v, H, mask, nx, ny, mean, std_, wk, bias, delta, s);
+        if (in_step) {
+            if (rc == SW2D_OK) rc = sw2d::detail::step_corrected(coarse, fix, folds);
+            continue;
+        }
         if (rc == SW2D_OK) rc = sw2d::detail::step_queued(coarse, 1, folds);
         if (rc == SW2D_OK) rc = sw2d_state(coarse, &e, &u, &v);
         if (rc == SW2D_OK) rc = fail(launch_correct(e, u, v, delta, mask, ny, nx, t_std, s), "sw2d_surrogate_advance");
