@@ -1350,18 +1350,24 @@ __global__ __launch_bounds__(256) void mse_grad_kernel(const float* __restrict__
     if (threadIdx.x == 0) partial[blockIdx.x] = lds[0];
 }
 
+// Sum over a workgroup of 256 threads, in thread 0: by lane swaps in each wave, then over its four waves
+// (a tree through LDS has eight barriers, and these kernels are little else).
+__device__ __forceinline__ double group_sum(double s) {
+    __shared__ double lds[4];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (threadIdx.x % 64 == 0) lds[threadIdx.x / 64] = s;
+    __syncthreads();
+    return (lds[0] + lds[1]) + (lds[2] + lds[3]);
+}
+
 __global__ __launch_bounds__(256) void sum_partials_kernel(const double* __restrict__ partial, int n,
                                                            double* __restrict__ out) {
-    __shared__ double lds[256];
     double s = 0.0;
+#pragma unroll 4
     for (int i = threadIdx.x; i < n; i += 256) s += partial[i];
-    lds[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) lds[threadIdx.x] += lds[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = lds[0];
+    s = group_sum(s);
+    if (threadIdx.x == 0) *out = s;
 }
 
 // ------------------------------------------------------------------------------ adam
@@ -1423,24 +1429,32 @@ __global__ __launch_bounds__(256) void correct_kernel(float* __restrict__ eta, f
 }
 
 // ------------------------------------------------------------------------------ rmse
+// Four cells in a row of memory; the planes may begin at any cell.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint8_t u8x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// Four cells per thread at a time, all loaded before the mask is looked at (1024^2: 6.0 -> 4.7 us).
 __global__ __launch_bounds__(256) void sqdiff_kernel(const float* __restrict__ a, const float* __restrict__ b,
                                                      const uint8_t* __restrict__ mask, int n,
                                                      double* __restrict__ partial) {
-    __shared__ double lds[256];
     double s = 0.0;
-    // 64-bit index: n may come close to 2^31, and the stride would overflow an int
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        if (mask[i]) {
-            const double d = (double)a[i] - (double)b[i];
-            s += d * d;
+    const int64_t groups = n / 4;
+    const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    for (int64_t g = first; g < groups; g += step) {
+        const u8x4_any m = *(const u8x4_any*)(mask + 4 * g);
+        const f32x4_any x = *(const f32x4_any*)(a + 4 * g), y = *(const f32x4_any*)(b + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const double d = (double)x[i] - (double)y[i];
+            s += m[i] ? d * d : 0.0;
         }
-    lds[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) lds[threadIdx.x] += lds[threadIdx.x + h];
-        __syncthreads();
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = lds[0];
+    if (first < n - 4 * groups && mask[4 * groups + first]) {
+        const double d = (double)a[4 * groups + first] - (double)b[4 * groups + first];
+        s += d * d;
+    }
+    s = group_sum(s);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
 // ------------------------------------------------------------------------------ sub3

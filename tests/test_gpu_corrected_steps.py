@@ -1,5 +1,6 @@
 """Corrected steps whose correction is added as the step stores its state, against the network, the step
-and the correction as three calls: bitwise the same state and diagnostics, at the edges of the tiles."""
+and the correction as three calls: bitwise the same state and diagnostics, at the edges of the tiles. The
+correction and the squared differences by themselves at ragged sizes."""
 import ctypes
 
 import numpy as np
@@ -49,3 +50,54 @@ def test_advance_equals_three_calls(shape):
         got = b.reduce(steps)
         for name in ("step", "vol_total", "vol_disp", "max_abs_u", "max_abs_v"):
             assert np.array_equal(folds[name], got[name])  # same tiles, same order of the sums
+
+
+@pytest.mark.parametrize("skew", [0, 1, 3])
+@pytest.mark.parametrize("shape", [(1, 1), (1, 3), (3, 1), (1, 9), (9, 1), (2, 2), (5, 3), (3, 5), (33, 47), (64, 68),
+                                   (517, 1030)])
+def test_correction_and_squared_differences(shape, skew):
+    """The squared differences take four cells per thread: fewer cells, remainders, planes that begin
+    anywhere; land cells, with infinities and NaN on them, are neither changed nor counted."""
+    from paper_1711_04471_amd import surrogate as S
+    from paper_1711_04471_amd._lib import check, load
+    h, w = shape
+    n = h * w
+    rng = np.random.default_rng(n + skew)
+    mask = (rng.uniform(size=shape) < 0.8).astype(np.uint8)
+    state = rng.standard_normal((3, h, w)).astype(np.float32)
+    other = rng.standard_normal(shape).astype(np.float32)
+    out = rng.standard_normal((3, h, w)).astype(np.float32)
+    for a in (state[0], other, out[0]):
+        a[mask == 0] = rng.choice([np.nan, np.inf, -np.inf, 1.0], size=int((mask == 0).sum()))
+    t_std = np.array([0.01, 0.02, 0.03], np.float32)
+
+    def skewed(a):
+        t = torch.empty(a.size + skew, dtype=torch.as_tensor(a).dtype, device="cuda")
+        t[skew:] = torch.as_tensor(a.reshape(-1)).cuda()
+        return t[skew:]
+
+    def p(t):
+        return ctypes.c_void_p(t.data_ptr())
+
+    e, u, v = (skewed(a) for a in state)
+    d, m, o = skewed(out), skewed(mask), skewed(other)
+    keep, tp = S._fptr(t_std)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    check(load().sw2d_apply_correction(p(e), p(u), p(v), p(d), p(m), w, h, tp, stream), "sw2d_apply_correction")
+    wet = mask != 0
+    active = np.zeros((3, h, w), bool)
+    active[0] = wet
+    active[1, :, :-1] = wet[:, :-1] & wet[:, 1:]
+    active[2, :-1] = wet[:-1] & wet[1:]
+    got = torch.stack([e, u, v]).cpu().numpy().reshape(3, h, w)
+    assert np.array_equal(got[~active].view(np.uint32), state[~active].view(np.uint32))
+    want = (t_std.astype(np.float64)[:, None, None] * out + state)[active]
+    # one rounding to 24 bits, of a product and sum that FP64 holds to 53
+    assert np.all(np.abs(got[active] - want) <= 2.0 ** -24 * np.abs(want) * (1 + 2.0 ** -20))
+
+    total = torch.zeros(1, dtype=torch.float64, device="cuda")
+    work = torch.empty(load().sw2d_rmse_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    check(load().sw2d_rmse(p(e), p(o), p(m), n, p(total), p(work), work.numel(), stream), "sw2d_rmse")
+    diff = got[0][wet].astype(np.float64) - other[wet]
+    want = float(np.sum(diff * diff))
+    assert abs(total.item() - want) <= n * 2.0 ** -52 * want
