@@ -134,7 +134,10 @@ int sw2d_create(const sw2d_params *p, const float *d_H, const uint8_t *d_mask, f
                 void *d_work, size_t work_bytes, void *hip_stream, sw2d_t *out);
 
 /* Enqueue nsteps >= 0 time steps (and their folds) on the handle's stream. No host
- * synchronisation, no host-device copy. */
+ * synchronisation, no host-device copy: calls may be captured in a HIP graph. Each pass over the
+ * grid swaps the two state buffers, so a replayed graph goes on from its own result if it holds an
+ * even number of passes of sw2d_time_blocking steps (a captured call keeps their parity where it
+ * takes more steps per pass); the handle's counter and folds are those of the capture. */
 int sw2d_step(sw2d_t h, int32_t nsteps);
 
 /* Benchmark form of sw2d_step: the same launches, with a HIP event pair recorded on the

@@ -180,13 +180,16 @@ int add_pass_times(hipEvent_t* ev, int passes, double* total_ms) {
 // passes between folds) the step kernels are timed.
 int enqueue_steps(sw2d_ctx* h, int32_t nsteps, FoldQueue& q, hipEvent_t* ev, double* total_ms,
                   const StepCorrection* fix = nullptr) {
-    const int kmax = pass_steps(h);
+    const int kmax = pass_steps(h), spp = h->steps_per_pass;
+    int singles = nsteps > 1 && kmax != spp && captured(h->stream)
+                      ? single_steps(nsteps, kmax, ((nsteps - 1) / spp + 1) % 2 != 0)
+                      : 0;
     BlockGeometry bg{};
     int bg_k = 0;
     int passes = 0;
     int32_t done = 0;
     while (done < nsteps) {
-        const int k = (nsteps - done < kmax) ? nsteps - done : kmax;
+        const int k = singles > 0 ? 1 : (nsteps - done < kmax) ? nsteps - done : kmax;
         const bool tiles = tile_pass(h, k);
         if (tiles && k != bg_k) {
             bg = block_geometry(h->p.nx, h->p.ny, k, (int)h->p.flags);
@@ -226,6 +229,7 @@ int enqueue_steps(sw2d_ctx* h, int32_t nsteps, FoldQueue& q, hipEvent_t* ev, dou
         q.used += (int64_t)k * nblocks;
         ++passes;
         done += k;
+        if (singles > 0) --singles;
     }
     if (!ev) return SW2D_OK;
     const int rc = flush_folds(h, q);

@@ -187,6 +187,25 @@ inline BlockGeometry block_geometry(int nx, int ny, int K, int kvar = 0) {
     return best;
 }
 
+// Whether the caller is capturing the stream (the null stream cannot be captured).
+inline bool captured(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!s) return false;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st == hipStreamCaptureStatusActive;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Each pass swaps a state's two buffers. A replayed capture starts from the buffer that it was recorded
+// with, so it goes on from its own result only if it holds an even number of passes. The number of
+// steps that a pass takes is the library's choice; for the caller, passes are of the steps per pass that
+// the handle reports, and a captured call keeps their parity: single_steps steps are taken one at a time
+// first, and the n steps then make an odd (or an even) number of passes of at most k steps.
+inline int single_steps(int n, int k, bool odd) {
+    if ((((n - 1) / k + 1) % 2 != 0) == odd) return 0;
+    return n % k == 1 ? 2 : 1;  // one pass more
+}
+
 // K = 1..4 steps of the model (kvar: its variants, 0 for the plain step) in one pass over register
 // tiles (geometry from block_geometry); the partials of step s of the pass go to
 // part[s * geo.nblocks + 0..nblocks).
