@@ -291,7 +291,8 @@ int32_t sw2d_batch_time_blocking(sw2d_batch_t b);
 
 /* Enqueue nsteps steps of every instance on the stream (no host synchronisation). With
  * graphs on, the first call for a given nsteps records the graph; later calls with the
- * same nsteps replay it. */
+ * same nsteps replay it. With graphs off, a call may be captured in the caller's graph (the state
+ * pointers stay right over its replays if nsteps is an even number of passes of K steps). */
 int sw2d_batch_step(sw2d_batch_t b, int32_t nsteps);
 
 /* sw2d_batch_step bracketed by HIP events on the stream; synchronises and writes the mean

@@ -499,7 +499,8 @@ int32_t chunk_steps(const sw2d_bctx* b, int32_t nsteps) {
     return b->steps_per_launch >= K ? b->steps_per_launch / K * K : K;
 }
 
-int enqueue_passes(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
+// nsteps steps, a launch per pass; the first `singles` of them one at a time.
+int enqueue_passes(sw2d_bctx* b, int32_t nsteps, int singles, hipStream_t s) {
     BatchPass a{};
     a.inst = b->d_inst;
     a.ring = b->d_ring;
@@ -509,7 +510,7 @@ int enqueue_passes(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
     for (int K = 1; K <= kBlockMaxK; ++K) most = std::max(most, (size_t)K * b->n_tiles[K - 1]);
     auto fold_blocks = [&]() { return (b->n * a.fold_steps + kBlockWaves - 1) / kBlockWaves; };
     while (a.step < nsteps) {
-        const int K = nsteps - a.step < kBlockMaxK ? nsteps - a.step : kBlockMaxK;
+        const int K = a.step < singles ? 1 : nsteps - a.step < kBlockMaxK ? nsteps - a.step : kBlockMaxK;
         a.member = b->d_member[K - 1];
         a.n_tiles = b->n_tiles[K - 1];
         a.part = b->d_part + (a.pass & 1) * most;
@@ -529,8 +530,9 @@ int enqueue_passes(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
     return SW2D_OK;
 }
 
-int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
-    if (!b->persistent) return enqueue_passes(b, nsteps, s);
+// nsteps steps in chunks; the first `singles` (of the first chunk) one at a time.
+int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, int singles, hipStream_t s) {
+    if (!b->persistent) return enqueue_passes(b, nsteps, singles, s);
     BatchArgs a;
     a.inst = b->d_inst;
     a.part = b->d_part;
@@ -539,21 +541,27 @@ int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, hipStream_t s) {
     a.flags = b->d_flags;
     a.n_inst = b->n;
     a.timeout_ticks = b->timeout_ticks;
+    auto launch = [&](int K, int32_t steps) -> int {  // in passes of K
+        if (steps == 0) return SW2D_OK;
+        a.steps = steps;
+        a.n_tiles = b->n_tiles[K - 1];
+        // no more workgroups than have tiles, or folds beside them, to do
+        const int64_t useful = (int64_t)a.n_tiles + ((int64_t)b->n * K + kBlockWaves - 1) / kBlockWaves;
+        const int grid = useful < b->grid ? (int)useful : b->grid;
+        hipLaunchKernelGGL(batch_kernel(K, b->tile_rows), dim3(grid), dim3(kBatchThreads), 0, s, a);
+        SW2D_BHIP(hipGetLastError());
+        return SW2D_OK;
+    };
     const int32_t per_launch = chunk_steps(b, nsteps);
     for (int32_t done = 0; done < nsteps;) {
         const int32_t chunk = nsteps - done < per_launch ? nsteps - done : per_launch;
-        const int32_t rest = chunk % kBlockMaxK;
-        for (const int K : {kBlockMaxK, (int)rest}) {
-            a.steps = K == rest ? rest : chunk - rest;
-            if (a.steps == 0) continue;
-            a.n_tiles = b->n_tiles[K - 1];
-            // no more workgroups than have tiles, or folds beside them, to do
-            const int64_t useful = (int64_t)a.n_tiles + ((int64_t)b->n * K + kBlockWaves - 1) / kBlockWaves;
-            const int grid = useful < b->grid ? (int)useful : b->grid;
-            hipLaunchKernelGGL(batch_kernel(K, b->tile_rows), dim3(grid), dim3(kBatchThreads), 0, s, a);
-            SW2D_BHIP(hipGetLastError());
-        }
+        const int32_t rest = (chunk - singles) % kBlockMaxK;
+        int rc = launch(1, singles);
+        if (rc == SW2D_OK) rc = launch(kBlockMaxK, chunk - singles - rest);
+        if (rc == SW2D_OK && rest > 0) rc = launch(rest, rest);
+        if (rc) return rc;
         done += chunk;
+        singles = 0;
     }
     return SW2D_OK;
 }
@@ -746,14 +754,24 @@ int sw2d_batch_step(sw2d_batch_t b, int32_t nsteps) {
     if (!b || nsteps < 0) return SW2D_ESTATE;
     if (nsteps == 0) return SW2D_OK;
     if (nsteps % b->steps_per_pass != 0) return SW2D_EINVAL;
+    const int32_t per_launch = chunk_steps(b, nsteps);
+    int64_t passes = (int64_t)(nsteps / per_launch) * chunk_passes(per_launch) + chunk_passes(nsteps % per_launch);
     if (!b->use_graph) {
-        int rc = enqueue_chunks(b, nsteps, b->stream);
+        // under the caller's capture the passes keep the parity of passes of the caller's K, so that the
+        // buffer of sw2d_batch_state stays the current one over replays
+        int singles = 0;
+        if ((passes - nsteps / b->steps_per_pass) % 2 != 0 && captured(b->stream)) {
+            const int32_t first = nsteps < per_launch ? nsteps : per_launch;
+            singles = single_steps(first, kBlockMaxK, chunk_passes(first) % 2 == 0);
+            ++passes;
+        }
+        int rc = enqueue_chunks(b, nsteps, singles, b->stream);
         if (rc) return rc;
     } else {
         if (b->graph_n != nsteps) {
             drop_graph(b);
             SW2D_BHIP(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
-            int rc = enqueue_chunks(b, nsteps, b->capture);
+            int rc = enqueue_chunks(b, nsteps, 0, b->capture);
             hipGraph_t g = nullptr;
             hipError_t e = hipStreamEndCapture(b->capture, &g);
             if (rc) {
@@ -772,8 +790,7 @@ int sw2d_batch_step(sw2d_batch_t b, int32_t nsteps) {
         SW2D_BHIP(hipGraphLaunch(b->exec, b->stream));
     }
     b->steps_done += nsteps;
-    const int32_t per_launch = chunk_steps(b, nsteps);
-    b->passes_done += (int64_t)(nsteps / per_launch) * chunk_passes(per_launch) + chunk_passes(nsteps % per_launch);
+    b->passes_done += passes;
     return SW2D_OK;
 }
 

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_1711_04471_amd import inputs
-from paper_1711_04471_amd.sw2d import Sw2d
+from paper_1711_04471_amd.sw2d import Sw2d, Sw2dBatch
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +54,19 @@ def test_recorded_steps_of_a_default_handle(n, shape, flags):
     make_case = inputs.shore_basin if flags == 8 else inputs.small_basin
     c = make_case(*shape, seed=sum(shape))
     _replays(lambda: Sw2d.from_case(c, flags=flags, cd=0.0025, hmin=0.0625), lambda s: s.step(n), lambda s: s.state())
+
+
+@pytest.mark.parametrize("grid,launch", [(0, 50), (64, 50), (64, 7)])
+@pytest.mark.parametrize("n,K", [(2, 1), (4, 1), (6, 1), (10, 1), (20, 1), (4, 2), (12, 2), (6, 3), (12, 3), (18, 3)])
+def test_recorded_ensemble_steps_go_on_at_every_replay(n, K, grid, launch):
+    """Without the library's own graph, a launch per pass or persistent launches."""
+    assert n // K % 2 == 0
+    cases = [inputs.small_basin(*s, seed=3) for s in ((64, 64), (200, 180))]
+
+    def make():
+        b = Sw2dBatch(cases)
+        b.set_time_blocking(K)
+        b.set_launch(launch, False, grid)
+        return b
+
+    _replays(make, lambda b: b.step(n), lambda b: [x for k in range(b.n) for x in b.state(k)])
