@@ -488,7 +488,10 @@ __device__ __forceinline__ void fused_layer(const unsigned char* __restrict__ in
         fused_store<TH, L, kLast>(up, out_lds, out_f, cy, cx, valid, y0, x0, H, W, half);
         fused_store<TH, L, kLast>(low, out_lds, out_f, cy + 1, cx, valid, y0, x0, H, W, half);
     }
-    if (kBlocks < kFuWaves && wave >= kBlocks) fused_weights<KNEXT>(a, next_slot, 32 * half + j);
+    if (kBlocks < kFuWaves && wave >= kBlocks) {  // a wave without a block
+        fused_weights<KNEXT>(a, next_slot, 32 * half + j);
+        if constexpr (kLast) __builtin_amdgcn_s_waitcnt(0);  // the staged weights here too
+    }
 }
 
 template <int TH>
