@@ -37,6 +37,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -971,9 +972,9 @@ struct BwLds {
     static constexpr int kRim = kDgrad ? 1 : 0;
     static constexpr int kDCols = kBwTW + 2 * kRim, kDPix = (kBwTH + 2 * kRim) * kDCols;
     static constexpr int kXBytes = kXPix * kXStride, kDBytes = kDPix * kDStride;
-    static constexpr int kSum = 9 * 32 * 32 * 4;
-    static constexpr int kBytes = kXBytes + kDBytes;
-    static_assert(kBytes >= kSum + kBwWaves * 64 * 4, "the partial sums reuse the tile");
+    static constexpr int kAcc = KIN == 32 ? 9 : 5;  // 32 x 32 products of a wave
+    static constexpr int kSum = kAcc * 32 * 32, kBias = kBwWaves * 64;  // floats
+    static constexpr int kBytes = kXBytes + kDBytes + (kSum + kBias) * 4;
 };
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -1076,8 +1077,10 @@ __global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __
     };
 
     constexpr int kWgradWaves = kDgrad ? kBwWaves / 2 : kBwWaves;
-    float* const sums = reinterpret_cast<float*>(lds);               // [9][32][32], after the last tile
-    float* const bsums = reinterpret_cast<float*>(lds + L::kSum);    // [waves][64]
+    // [kAcc][q][lane][e] as the accumulators lie: output 8 q + 4 (lane / 32) + e, column lane % 32
+    float* const sums = reinterpret_cast<float*>(lds + L::kXBytes + L::kDBytes);
+    float* const bsums = sums + L::kSum;                                          // [waves][64]
+    for (int e = threadIdx.x; e < L::kSum + L::kBias; e += kBwThreads) sums[e] = 0.f;
 
     if constexpr (kDch < 32) {
         for (int e = threadIdx.x; e < L::kDPix * 4; e += kBwThreads)
@@ -1141,7 +1144,7 @@ __global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __
         for (int r = 0; r < kWgradWaves; ++r) __syncthreads();
     } else {
         constexpr int kRows = kBwTH / kWgradWaves;
-        constexpr int kAcc = KIN == 32 ? 9 : 5;
+        constexpr int kAcc = L::kAcc;
         const int turn = kDgrad ? wave - kBwWaves / 2 : wave, row0 = turn * kRows;
         // the lane's pixel and channels in a transpose read: 4 pixels x 16 channels per 16 lanes
         const int tp = 8 * half + lane % 16 / 4, tc = 4 * (lane % 4), upper = lane / 16 % 2;
@@ -1165,6 +1168,31 @@ __global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __
             }
             return av;
         };
+        // the wave's sums onto the workgroup's, 16 B per lane and access
+        auto add_sums = [&]() {
+            f32x4* const at = reinterpret_cast<f32x4*>(sums) + lane;
+#pragma unroll
+            for (int t = 0; t < kAcc; ++t) {
+                f32x4 sum[4];  // a product's reads in flight together
+#pragma unroll
+                for (int q = 0; q < 4; ++q) sum[q] = at[(t * 4 + q) * 64];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[q][e] += acc[t][4 * q + e];
+                    at[(t * 4 + q) * 64] = sum[q];
+                }
+            }
+            bsums[turn * 64 + lane] += bsum;
+        };
+        // A wave sums at most kChain pixels in one chain, whatever the image: each adds its sums in a tile of
+        // its own, two after the wave's before it, whose barriers keep the additions apart and in a fixed
+        // order. With one chain per launch the error grew with the image (dW against 64 bits, zero-mean
+        // maps, 4 x 1024^2 and 16 x 1024^2 pixels: 2.5e-7 and 5.4e-7; so 1.6e-7 and 2.2e-7, with the
+        // partials added in FP64); it costs 5 us of 128 per gradient of 4 x 1024^2, 0.9 % of a training step.
+        constexpr int kChain = 1024, kPeriod = kChain / (kRows * kBwTW);
+        static_assert(kPeriod == 2 * kWgradWaves, "a tile per wave and none beside it");
+        int left = 2 * turn + 1;
         for (int tile = first; tile < last; tile += stride) {
             __syncthreads();
             commit();
@@ -1210,30 +1238,29 @@ __global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __
                     }
                 }
             }
+            if (--left == 0) {  // wave-uniform
+                add_sums();
+#pragma unroll
+                for (int t = 0; t < kAcc; ++t)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+                bsum = 0.f;
+                left = kPeriod;
+            }
         }
         __syncthreads();
-        // the waves' sums added in wave order: acc[t][e] is output 8 (e / 4) + 4 half + e % 4, column j
+        // what is left, in wave order
 #pragma unroll 1  // one copy of the code, in the instruction cache after the first wave's turn
         for (int r = 0; r < kWgradWaves; ++r) {
-            if (r == turn) {
-#pragma unroll
-                for (int t = 0; t < kAcc; ++t) {
-                    float* const at = sums + (t * 32 + 4 * half) * 32 + j;
-                    float sum[16];  // a product's reads in flight together
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) sum[e] = r == 0 ? 0.f : at[(8 * (e / 4) + e % 4) * 32];
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) at[(8 * (e / 4) + e % 4) * 32] = sum[e] + acc[t][e];
-                }
-                bsums[turn * 64 + lane] = bsum;
-            }
+            if (r == turn) add_sums();
             __syncthreads();
         }
     }
     float* const out = part_w + (size_t)blockIdx.x * 9 * 32 * KIN;
     for (int e = threadIdx.x; e < 9 * 32 * KIN; e += kBwThreads) {
         const int t = e / (32 * KIN), o = e / KIN % 32, c = e % KIN;
-        out[e] = KIN == 32 ? sums[e] : sums[(t / 2 * 32 + o) * 32 + t % 2 * 16 + c];
+        const int product = KIN == 32 ? t : t / 2, col = KIN == 32 ? c : t % 2 * 16 + c;
+        out[e] = sums[((product * 4 + o / 8) * 64 + o / 4 % 2 * 32 + col) * 4 + o % 4];
     }
     if (threadIdx.x < 32) {
         float s = 0.f;
@@ -1242,7 +1269,7 @@ __global__ __launch_bounds__(kBwThreads) void backward_kernel(const uint16_t* __
     }
 }
 
-// dW[i] = sum over chunks of part[chunk][i], in a fixed order: a workgroup takes 32
+// dW[i] = sum over chunks of part[chunk][i] in FP64, in a fixed order: a workgroup takes 32
 // weights, its 32 slices of 32 threads add the chunks k = slice (mod 32) in increasing k, and
 // the 32 slice sums are added in slice order. Entries nw .. nw+31 are the bias.
 constexpr int kRedW = 32, kRedSlices = 32;
@@ -1251,10 +1278,10 @@ __global__ __launch_bounds__(kRedW* kRedSlices) void wgrad_reduce_kernel(const f
                                                                         const float* __restrict__ part_b,
                                                                         int chunks, int nw, float* __restrict__ dW,
                                                                         float* __restrict__ db) {
-    __shared__ float red[kRedSlices][kRedW];
+    __shared__ double red[kRedSlices][kRedW];
     const int w = threadIdx.x % kRedW, slice = threadIdx.x / kRedW;
     const int i = blockIdx.x * kRedW + w;
-    float acc = 0.f;
+    double acc = 0.0;
     if (i < nw) {
 #pragma unroll 8
         for (int k = slice; k < chunks; k += kRedSlices) acc += part_w[(size_t)k * nw + i];
@@ -1264,13 +1291,13 @@ __global__ __launch_bounds__(kRedW* kRedSlices) void wgrad_reduce_kernel(const f
     red[slice][w] = acc;
     __syncthreads();
     if (slice == 0) {
-        float t = red[0][w];
+        double t = red[0][w];
 #pragma unroll
         for (int q = 1; q < kRedSlices; ++q) t += red[q][w];
         if (i < nw)
-            dW[i] = t;
+            dW[i] = (float)t;
         else if (i < nw + 32)
-            db[i - nw] = t;
+            db[i - nw] = (float)t;
     }
 }
 
