@@ -65,6 +65,10 @@ struct SorGeometry {
 constexpr int64_t kSorPairPositions = 5 << 17;
 constexpr int sor_planes(int64_t positions) { return positions < kSorPairPositions ? 1 : 4; }
 
+// Workgroups of one launch: its threads have to stay below 2^32 (the runtime cuts the count off there
+// without an error). Long narrow columns (3 x 3 x 17,000,000 cells) take several launches.
+constexpr int kSorGroups = 1 << 23;
+
 // Tile b of n in an order that gives each XCD (workgroup b runs on XCD b % 8) a contiguous range.
 __device__ __forceinline__ int sor_tile(int b, int n) {
     const int x = b % kXcds;
@@ -134,9 +138,9 @@ __global__ __launch_bounds__(256) void sor_split_kernel(const float* __restrict_
                                                         float* __restrict__ red, float* __restrict__ black,
                                                         float* __restrict__ f_red, float* __restrict__ f_black,
                                                         float* __restrict__ red2, float* __restrict__ black2,
-                                                        SorGeometry g) {
+                                                        SorGeometry g, int first) {
     const int per = (g.ny * g.w + 255) / 256;  // workgroups per plane
-    const int k = blockIdx.x / per, q = (blockIdx.x - k * per) * 256 + threadIdx.x;
+    const int b = first + blockIdx.x, k = b / per, q = (b - k * per) * 256 + threadIdx.x;
     if (q >= g.ny * g.w) return;
     const int j = q / g.w, m = q - j * g.w;
     const size_t row = (size_t)k * g.ny + j;
@@ -158,9 +162,9 @@ __global__ __launch_bounds__(256) void sor_split_kernel(const float* __restrict_
 
 // The colour arrays back into p.
 __global__ __launch_bounds__(256) void sor_merge_kernel(float* __restrict__ p, const float* __restrict__ red,
-                                                        const float* __restrict__ black, SorGeometry g) {
+                                                        const float* __restrict__ black, SorGeometry g, int first) {
     const int per = (g.ny * g.w + 255) / 256;  // workgroups per plane
-    const int k = blockIdx.x / per, q = (blockIdx.x - k * per) * 256 + threadIdx.x;
+    const int b = first + blockIdx.x, k = b / per, q = (b - k * per) * 256 + threadIdx.x;
     if (q >= g.ny * g.w) return;
     const int j = q / g.w, m = q - j * g.w;
     const size_t row = (size_t)k * g.ny + j;
@@ -178,10 +182,10 @@ template <int COLOR, int MODE, int P>
 __global__ __launch_bounds__(kSorThreads) void sor_sweep_kernel(float* __restrict__ own,
                                                                 const float* __restrict__ other,
                                                                 const float* __restrict__ f_own, SorGeometry geo,
-                                                                SorCoef c, SorPartial* __restrict__ part) {
+                                                                SorCoef c, SorPartial* __restrict__ part, int first) {
 #pragma clang fp contract(off)
     const int nx = geo.nx, ny = geo.ny, nz = geo.nz, w = geo.w;
-    const int tile = sor_tile(blockIdx.x, geo.nblocks);
+    const int tile = sor_tile(first + blockIdx.x, geo.nblocks);
     const int bz = tile / geo.gx, bx = tile - bz * geo.gx;
     const int q = bx * kSorThreads + threadIdx.x;
     const bool row_ok = q < geo.rows_q;
@@ -348,32 +352,37 @@ bool sor_params_ok(const sw2d_sor_params* p) {
     return p->omega > 0.0 && p->omega < 2.0 && (p->fused == 0 || p->fused == 1);
 }
 
+// n workgroups of 256 threads in launches of at most kSorGroups; each gets its first one's number.
+template <typename Kernel, typename... Args>
+hipError_t launch_groups(Kernel kernel, int n, hipStream_t s, Args... args) {
+    for (int first = 0; first < n; first += kSorGroups) {
+        const int groups = n - first < kSorGroups ? n - first : kSorGroups;
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(256), 0, s, args..., first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <int COLOR, int MODE>
 hipError_t launch_sweep(float* own, const float* other, const float* f_own, const SorGeometry& g, const SorCoef& c,
                         SorPartial* part, hipStream_t s) {
-    const dim3 grid(g.nblocks), block(kSorThreads);
-    if (g.planes == 4) {
-        hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE, 4>), grid, block, 0, s, own, other, f_own, g, c, part);
-        return hipGetLastError();
-    }
-    if constexpr (MODE == kSorResidualOnly) {  // small grids update both colours in one launch
-        hipLaunchKernelGGL((sor_sweep_kernel<COLOR, MODE, 1>), grid, block, 0, s, own, other, f_own, g, c, part);
-        return hipGetLastError();
-    }
+    static_assert(kSorThreads == 256, "launch_groups");
+    if (g.planes == 4) return launch_groups(sor_sweep_kernel<COLOR, MODE, 4>, g.nblocks, s, own, other, f_own, g, c, part);
+    if constexpr (MODE == kSorResidualOnly)  // small grids update both colours in one launch
+        return launch_groups(sor_sweep_kernel<COLOR, MODE, 1>, g.nblocks, s, own, other, f_own, g, c, part);
     return hipErrorInvalidValue;
 }
 
-dim3 split_grid(const SorGeometry& g) { return dim3((unsigned)((g.ny * g.w + 255) / 256) * g.nz); }
+int split_groups(const SorGeometry& g) { return (g.ny * g.w + 255) / 256 * g.nz; }
 
 hipError_t launch_split(const float* p, const float* f, float* red, float* black, float* f_red, float* f_black,
                         float* red2, float* black2, const SorGeometry& g, hipStream_t s) {
-    hipLaunchKernelGGL(sor_split_kernel, split_grid(g), dim3(256), 0, s, p, f, red, black, f_red, f_black, red2, black2, g);
-    return hipGetLastError();
+    return launch_groups(sor_split_kernel, split_groups(g), s, p, f, red, black, f_red, f_black, red2, black2, g);
 }
 
 hipError_t launch_merge(float* p, const float* red, const float* black, const SorGeometry& g, hipStream_t s) {
-    hipLaunchKernelGGL(sor_merge_kernel, split_grid(g), dim3(256), 0, s, p, red, black, g);
-    return hipGetLastError();
+    return launch_groups(sor_merge_kernel, split_groups(g), s, p, red, black, g);
 }
 
 size_t colour_floats(const SorGeometry& g) { return (size_t)g.nz * g.ny * g.w; }
