@@ -148,9 +148,14 @@ using sw2d::detail::FoldQueue;
 // Whether the grid's steps and depth stay in the Infinity Cache (kBlockMaxCells).
 bool cached_grid(const sw2d_ctx* h) { return (int64_t)h->p.nx * h->p.ny <= kBlockMaxCells; }
 
+// Whether every pass is streamed as the caller's settings say: where that was chosen, and on grids whose
+// passes of the library's choice (8-row bands of 256 threads, tiles of 512) could need 2^32 threads of a
+// launch, which the runtime cuts off without an error; there the caller's band height keeps them fewer.
+bool streams(const sw2d_ctx* h) { return h->streaming || h->p.ny >= 1 << 27; }
+
 // Whether a pass of k steps goes over register tiles (see kBlockMaxCells).
 bool tile_pass(const sw2d_ctx* h, int k) {
-    if (h->streaming) return false;
+    if (streams(h)) return false;
     if (cached_grid(h) || k == kBlockMaxK) return true;
     return h->p.flags != 0 && (h->p.flags != kVarWetDry || k >= 2);
 }
@@ -158,7 +163,7 @@ bool tile_pass(const sw2d_ctx* h, int k) {
 // Steps per pass of the handle: over tiles of a cached grid, or when the caller has chosen none, as
 // many as are fastest, else the caller's.
 int pass_steps(const sw2d_ctx* h) {
-    if (h->streaming || (h->spp_chosen && !cached_grid(h))) return h->steps_per_pass;
+    if (streams(h) || (h->spp_chosen && !cached_grid(h))) return h->steps_per_pass;
     const bool divides = (h->p.flags & kVarFriction) && (int64_t)h->p.nx * h->p.ny > kBlockFrictionCells;
     return divides ? 2 : kBlockMaxK;
 }
