@@ -275,7 +275,8 @@ int sw2d_batch_create(int32_t n, const sw2d_params *p, const float *const *d_H,
                       void *d_work, size_t work_bytes, void *hip_stream, sw2d_batch_t *out);
 
 /* Launch shape: whether sw2d_batch_step records and replays a HIP graph (default 1), and the
- * persistent launch: grid = 0 (the default) takes one launch per pass; another value takes
+ * persistent launch: grid = 0 (the default) takes one launch per pass (persistent ones where a pass
+ * has 2^23 tiles or more); another value takes
  * persistent launches of that many workgroups (at most what the device holds at once, larger
  * values are rejected so the grid barrier always has every workgroup resident; never more
  * are launched than have work), each of steps_per_launch steps (>= 1, default 50). Drops any

@@ -342,7 +342,8 @@ struct sw2d_bctx {
     int tile_rows;            // R, rows per wave
     int max_grid;
     int grid;
-    bool persistent;          // the caller chose the persistent launch
+    bool persistent;          // persistent launches: chosen by the caller, or too many tiles
+    bool many_tiles;          // more than a launch per pass holds
     int steps_per_launch;
     int steps_per_pass;       // the caller's K, 1..kMaxBatchK: step counts are multiples of it
     bool use_graph;
@@ -624,7 +625,12 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
     b->graph = nullptr;
     b->exec = nullptr;
     b->graph_n = -1;
-    b->persistent = false;
+    // a launch holds fewer than 2^32 threads
+    b->many_tiles = false;
+    for (int K = 1; K <= kBlockMaxK; ++K)
+        if ((int64_t)L.n_tiles[K - 1] + ((int64_t)n * kBlockMaxK + kBlockWaves - 1) / kBlockWaves >= (1 << 23))
+            b->many_tiles = true;
+    b->persistent = b->many_tiles;
     b->steps_per_launch = 50;
     b->use_graph = true;
     b->steps_done = 0;
@@ -743,7 +749,7 @@ int sw2d_batch_set_launch(sw2d_batch_t b, int32_t steps_per_launch, int32_t use_
     if (steps_per_launch < 1 || grid < 0) return SW2D_EINVAL;
     if (grid > b->max_grid) return SW2D_EINVAL;  // must stay co-resident
     b->grid = grid > 0 ? grid : b->max_grid;
-    b->persistent = grid > 0;
+    b->persistent = grid > 0 || b->many_tiles;
     b->steps_per_launch = steps_per_launch;
     b->use_graph = use_graph != 0;
     drop_graph(b);

@@ -3,7 +3,7 @@ holds: windows of the result against the same rows stepped as a basin of their o
 import pytest
 import torch
 
-from paper_1711_04471_amd.sw2d import Sw2d
+from paper_1711_04471_amd.sw2d import Sw2d, Sw2dBatch
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,22 @@ def test_more_rows_than_a_launch_of_low_bands_holds(steps):
         sim.band_rows = 64
         sim.step(steps)
         _check_windows(case, sim.state(), steps)
+
+
+@pytest.mark.parametrize("launch", [None, (50, True, 0), (50, False, 64)])
+def test_more_tiles_than_a_launch_per_pass_holds(launch):
+    """24-row tiles own 8 rows at 4 steps per pass."""
+    cases, steps = [_Column(40), _Column((1 << 26) + 1001), _Column(70)], 5
+    with Sw2dBatch(cases, band_rows=[8] * 3) as b:
+        if launch:
+            b.set_launch(*launch)
+        b.step(steps)
+        for k, case in enumerate(cases):
+            if case.ny < 512:
+                with Sw2d.from_case(case) as sim:
+                    sim.step(steps)
+                    for x, y in zip(b.state(k), sim.state()):
+                        assert torch.equal(x, y), k
+            else:
+                _check_windows(case, b.state(k), steps)
+        assert (b.reduce()["step"] == steps).all()
