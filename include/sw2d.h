@@ -276,17 +276,17 @@ int sw2d_batch_create(int32_t n, const sw2d_params *p, const float *const *d_H,
 
 /* Launch shape: whether sw2d_batch_step records and replays a HIP graph (default 1), and the
  * persistent launch: grid = 0 (the default) takes one launch per pass (persistent ones where a pass
- * has 2^23 tiles or more); another value takes
- * persistent launches of that many workgroups (at most what the device holds at once, larger
- * values are rejected so the grid barrier always has every workgroup resident; never more
- * are launched than have work), each of steps_per_launch steps (>= 1, default 50). Drops any
+ * has 2^23 tiles or more); another value takes persistent launches of that many workgroups, each
+ * of steps_per_launch steps (>= 1, default 50). At most 6, 5 and 4 workgroups per CU may be asked
+ * for at 1, 2 and 3 steps per pass (SW2D_EINVAL above); no more are launched than the device holds
+ * at once, so that the grid barrier has every workgroup resident, or than have work. Drops any
  * recorded graph. */
 int sw2d_batch_set_launch(sw2d_batch_t b, int32_t steps_per_launch, int32_t use_graph, int32_t grid);
 
 /* Steps that a caller of the batched kernel takes together: 1 (default), 2 or 3. Afterwards
  * sw2d_batch_step takes multiples of K only. A pass advances up to 4 steps of a launch
  * whatever K; the states equal single steps bit for bit and the folds of every step are kept.
- * Drops a recorded graph. SW2D_EINVAL for K outside 1..3. */
+ * Lowers the grid to the largest for K, drops a recorded graph. SW2D_EINVAL for K outside 1..3. */
 int sw2d_batch_set_time_blocking(sw2d_batch_t b, int32_t steps_per_pass);
 int32_t sw2d_batch_time_blocking(sw2d_batch_t b);
 
@@ -316,7 +316,8 @@ int64_t sw2d_batch_steps_done(sw2d_batch_t b);
  * zero deadline to exercise that path. Drops any recorded graph. */
 int sw2d_batch_set_barrier_timeout(sw2d_batch_t b, double seconds);
 
-/* Most workgroups (512 threads each) of a persistent launch. */
+/* The grid asked for, or the largest that may be: the most workgroups (512 threads each) of a
+ * persistent launch, where the device holds as many at once. */
 int32_t sw2d_batch_grid(sw2d_batch_t b);
 
 /* Release the handle, its graph and its private stream. NULL is accepted. */

@@ -340,8 +340,9 @@ struct sw2d_bctx {
     unsigned long long* d_flags;
     int n_tiles[kBlockMaxK];  // tiles of all members at K = 1.. steps per pass
     int tile_rows;            // R, rows per wave
-    int max_grid;
-    int grid;
+    int cus;
+    int resident;             // workgroups of the persistent launch that the device holds at once
+    int grid;                 // the caller's, or the most it may ask for
     bool persistent;          // persistent launches: chosen by the caller, or too many tiles
     bool many_tiles;          // more than a launch per pass holds
     int steps_per_launch;
@@ -389,6 +390,9 @@ constexpr int kMaxBatchGrid = 256 * 8;  // flag lines reserved: 8 workgroups on 
 // workgroups of 8 waves per CU, not 4); a grid barrier that waits for a workgroup that never
 // became resident would only end at its deadline.
 constexpr int kBatchWgPerCu = 3;
+// Workgroups per CU that a caller may ask for at K = 1, 2 and 3 steps per pass; a launch takes no more of
+// them than are resident.
+constexpr int kBatchGridPerCu[kMaxBatchK] = {6, 5, 4};
 constexpr int kBatchRowsLow = 3, kBatchRowsMid = 5, kBatchRowsHigh = 8;  // rows per wave: tiles of 24, 40 and 64
 constexpr int kBatchRows[3] = {kBatchRowsLow, kBatchRowsMid, kBatchRowsHigh};
 constexpr int kBatchLowTiles = 320;    // most tiles of 24 rows chosen without the caller's word
@@ -548,7 +552,7 @@ int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, int singles, hipStream_t s) {
         a.n_tiles = b->n_tiles[K - 1];
         // no more workgroups than have tiles, or folds beside them, to do
         const int64_t useful = (int64_t)a.n_tiles + ((int64_t)b->n * K + kBlockWaves - 1) / kBlockWaves;
-        const int grid = useful < b->grid ? (int)useful : b->grid;
+        const int grid = (int)std::min<int64_t>(useful, std::min(b->grid, b->resident));
         hipLaunchKernelGGL(batch_kernel(K, b->tile_rows), dim3(grid), dim3(kBatchThreads), 0, s, a);
         SW2D_BHIP(hipGetLastError());
         return SW2D_OK;
@@ -569,10 +573,8 @@ int enqueue_chunks(sw2d_bctx* b, int32_t nsteps, int singles, hipStream_t s) {
 
 // Workgroups of the tile kernels the device holds at once (capped, see kBatchWgPerCu): the least
 // of the passes of every length.
-int resident_grid(int R, int* out) {
-    int dev = 0, cus = 0, least = kBatchWgPerCu;
-    SW2D_BHIP(hipGetDevice(&dev));
-    SW2D_BHIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+int resident_grid(int R, int cus, int* out) {
+    int least = kBatchWgPerCu;
     for (int K = 1; K <= kBlockMaxK; ++K) {
         int per_cu = 0;
         SW2D_BHIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -584,6 +586,9 @@ int resident_grid(int R, int* out) {
     *out = g < kMaxBatchGrid ? g : kMaxBatchGrid;
     return SW2D_OK;
 }
+
+// The largest grid that a caller may ask for.
+int max_grid(const sw2d_bctx* b) { return std::min(b->cus * kBatchGridPerCu[b->steps_per_pass - 1], kMaxBatchGrid); }
 
 void drop_graph(sw2d_bctx* b) {
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
@@ -721,10 +726,11 @@ int sw2d_batch_create(int32_t n, const sw2d_params* p, const float* const* d_H,
     int dev = 0, clock_khz = 0;
     e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return fail(batch_hip_fail(e, "device query"));
-    const int rc = resident_grid(b->tile_rows, &b->max_grid);
+    const int rc = resident_grid(b->tile_rows, b->cus, &b->resident);
     if (rc) return fail(rc);
-    b->grid = b->max_grid;
+    b->grid = max_grid(b);
     if (clock_khz <= 0) clock_khz = 100000;
     b->timeout_ticks = (unsigned long long)clock_khz * 1000ull * 2ull;  // 2 s per barrier
     e = hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking);
@@ -738,6 +744,7 @@ int sw2d_batch_set_time_blocking(sw2d_batch_t b, int32_t steps_per_pass) {
     if (steps_per_pass < 1 || steps_per_pass > kMaxBatchK) return SW2D_EINVAL;
     if (steps_per_pass == b->steps_per_pass) return SW2D_OK;
     b->steps_per_pass = steps_per_pass;
+    b->grid = std::min(b->grid, max_grid(b));
     drop_graph(b);
     return SW2D_OK;
 }
@@ -747,8 +754,8 @@ int32_t sw2d_batch_time_blocking(sw2d_batch_t b) { return b ? b->steps_per_pass 
 int sw2d_batch_set_launch(sw2d_batch_t b, int32_t steps_per_launch, int32_t use_graph, int32_t grid) {
     if (!b) return SW2D_ESTATE;
     if (steps_per_launch < 1 || grid < 0) return SW2D_EINVAL;
-    if (grid > b->max_grid) return SW2D_EINVAL;  // must stay co-resident
-    b->grid = grid > 0 ? grid : b->max_grid;
+    if (grid > max_grid(b)) return SW2D_EINVAL;
+    b->grid = grid > 0 ? grid : max_grid(b);
     b->persistent = grid > 0 || b->many_tiles;
     b->steps_per_launch = steps_per_launch;
     b->use_graph = use_graph != 0;
