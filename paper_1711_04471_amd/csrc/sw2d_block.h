@@ -157,8 +157,10 @@ __device__ __forceinline__ void block_pass(const float* __restrict__ eta, const 
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             w[r + 1][c] = __ballot(hp[r][c] > 0.f);
-            // the surface of a land cell is never used (wetting and drying compares it)
-            if constexpr (!kWetDry) e[r][c] = lane_bit(w[r + 1][c]) ? e[r][c] : 0.f;
+            // The surface of a land cell is never used (wetting and drying compares it), but one that is
+            // not finite makes the flux through a shut face, 0 times its depth, NaN: it stays so. (The
+            // surface as it was loaded gives the same, 0.7 % slower on 2048^2.)
+            if constexpr (!kWetDry) e[r][c] = lane_bit(w[r + 1][c]) ? e[r][c] : 0.f * e[r][c];
         }
     }
     auto pack = [](const float (&x)[2]) { return make_float2(x[0], x[1]); };
