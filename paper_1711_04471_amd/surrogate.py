@@ -166,9 +166,11 @@ class ConvNet:
         check(self.lib.sw2d_conv3x3_correct(_p(hidden), _p(self.wk[3]), _p(self.weight(3)[1]), tstd_ptr, _p(mask),
                                             _p(eta), _p(u), _p(v), w, h, self.stream()), "sw2d_conv3x3_correct")
 
-    def backward(self, x16, d_out, n, h, w, work, channels=32):
-        """Gradients of every layer into self.grad, for dL/dout = d_out (BF16 NHWC with
-        32 or 4 channels per pixel)."""
+    def backward(self, x16, d_out, n, h, w, work, channels=None):
+        """Gradients of every layer into self.grad, for dL/dout = d_out (BF16 NHWC with 32 or 4
+        channels per pixel: ``channels``, or 4 where d_out's last dimension is)."""
+        if channels is None:
+            channels = 4 if d_out.dim() > 1 and d_out.shape[-1] == 4 else 32
         _, acts, _, dz = self._buffers(n, h, w)
         s = self.stream()
         dy, dy_channels = d_out, channels
@@ -416,7 +418,7 @@ class Trainer:
         check(self.lib.sw2d_mse_grad4(_p(out), _p(self.tgt), self._tp, _p(self.msk), n, self.ny, self.nx,
                                       ctypes.c_float(1.0 / n_act), _p(self.dout), _p(self.loss), _p(self.mse_work),
                                       self.mse_work.numel(), self.net.stream()), "sw2d_mse_grad4")
-        self.net.backward(self.x16, self.dout, n, self.ny, self.nx, self.work, channels=4)
+        self.net.backward(self.x16, self.dout, n, self.ny, self.nx, self.work)
         return n_act
 
     def fit(self, epochs=1, lr=1e-3, seed=0, log=None, train_idx=None, decay=True):
