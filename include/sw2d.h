@@ -213,8 +213,8 @@ typedef struct {
     int32_t nx, ny, nz; /* cells incl. the boundary layer, each >= 3, product < 2^31 */
     double dx, dy, dz;  /* spacings > 0 */
     double omega;       /* relaxation factor, 0 < omega < 2 */
-    int32_t fused;      /* 0 or 1; without effect (1 asked for one pass per iteration, which the
-                           two sweeps outrun at every size; the state is the same bit for bit) */
+    int32_t fused;      /* 0 or 1; without effect: the library takes one launch per iteration on small
+                           grids and two sweeps on larger ones (the state is the same bit for bit) */
 } sw2d_sor_params;
 
 /* Residual r = f - L p of the state after `iter` iterations (iter 0 = the initial state):

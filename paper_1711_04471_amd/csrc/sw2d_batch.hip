@@ -13,10 +13,9 @@
 //
 // One persistent launch per chunk of steps (sw2d_batch_kernel) where the caller asks for it:
 // workgroup g of G takes the g-th of G equal runs of the list and meets the others at a grid
-// barrier after each pass. Measured slower at either end, whole calls with the gathering of the states
-// (0.54 ms of it for the 256 members): 12 members of 64-256 cells a side, 50 steps, 200 us (the barrier
-// takes longer than a launch) against 185; 256 members of 128-1024, 48 steps, 11.1 ms (equal runs end
-// up to a quarter apart, and the loop's state spills scalar registers) against 7.6.
+// barrier after each pass. Measured slower at either end: 12 members of 64-256 cells a side, 50 steps,
+// 189 us (the barrier takes longer than a launch) against 135; 256 members of 128-1024, 48 steps, 10.4 ms
+// (equal runs end up to a quarter apart, and the loop's state spills scalar registers) against 6.6.
 //
 // The barrier uses no contended atomics: every workgroup publishes the epoch it has
 // reached in its own flag (after an agent-scope release), workgroup 0 waits for all
@@ -418,9 +417,15 @@ bool batch_layout(int n, const sw2d_params* p, const int32_t* band_rows, BatchLa
         }
     }
     // The tile height follows the band height: tiles of 24 rows for bands below 16 rows on average,
-    // of 40 rows below 48, of 64 rows from there. Without the caller's choice: the lowest while they
-    // all run at once (as on a single grid), the highest when even those take several rounds (their
-    // overlap is the least).
+    // of 40 rows below 48, of 64 rows from there (they own 8, 24 and 48 rows at 4 steps per pass).
+    // Without the caller's choice: the lowest while they all run at once, the highest where even those
+    // take several rounds (their overlap is the least), 40 rows between. Us per step at 24, 40 and 64
+    // rows: 12 members of 64-256 cells a side (391 low tiles) 3.1, 2.9, 3.8; 48 of them (1642 low, 306
+    // high) 6.8, 5.4, 6.0; 4 of 701 x 523 (308 high) 6.9, 5.5, 6.1; 64 of 256^2 (960 high) 17.3, 10.9,
+    // 10.3; 32 of 128-1024 (2581 high) 45.1, 28.4, 25.5; 256 of those 256, 165, 141. Below 320 low tiles
+    // 12 smaller members took 145 us a call at 24 rows and 163 at 40. Between 960 and 2048 high tiles
+    // the highest are up to 5 % faster than the 40 rows taken (16 of 128-1024, 1503 high: 15.5 and
+    // 14.7); the line leaves a margin above the crossing, which moves with the members' sizes.
     int r = 1;
     if (band_rows)
         r = sum_rows < 16 * (int64_t)n ? 0 : sum_rows < 48 * (int64_t)n ? 1 : 2;

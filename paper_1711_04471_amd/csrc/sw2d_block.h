@@ -26,7 +26,7 @@
 // against the two-column row pipeline's 49; a tile of 40 rows takes about 1.2 us per step
 // wherever it runs) plus 4 us for the launch, the loads and the stores. Measured per step, the
 // default handle's streamed single step before and the tiles now: 66^2 7.0 and 1.7 us (200
-// steps a call), 2048^2 22.8 and 9.0 us (50 a call: 466,000 Mcell-steps/s; 117 MB from the
+// steps a call), 2048^2 22.8 and 8.7 us (50 a call: 483,000 Mcell-steps/s; 117 MB from the
 // cache take 14.5 us at a large copy's rate there, so several steps per pass are what beats it).
 // All variants at once, 2047 x 1531: 31.2 and 22.7 us (bound by the issue of friction's four
 // divisions per cell), 301 x 221 10.2 and 4.5; friction alone 23.2 and 15.8, the velocity filter

@@ -168,8 +168,8 @@ constexpr bool block_shape(int K, int R, int kvar) {
 // them. A step of a tile alone takes 0.8 us at 3 rows per wave, 1.2 at 5 and 1.8 at 8, CUs with several
 // tiles take about as long as their rows together, and a tile owns 4K (with advection 5K) rows less
 // than it steps, so low tiles win while every CU has one, higher ones as the recomputed overlap counts,
-// and between sizes the round that is left nearly empty decides. Plain model, K = 4, us per step at 3,
-// 5, 7 and 8 rows: 300 x 221 1.8, 2.3, 2.8, 3.1; 693 x 700 3.2, 2.55, 3.0, 3.35; 1024^2 4.7, 3.6, 3.2,
+// and between sizes the round that is left nearly empty decides. Plain model, passes of 4 steps alone (a
+// call adds its remainder and its folds), us per step at 3, 5, 7 and 8 rows: 300 x 221 1.8, 2.3, 2.8, 3.1; 693 x 700 3.2, 2.55, 3.0, 3.35; 1024^2 4.7, 3.6, 3.2,
 // 3.4; 2048^2 13.8, 8.7, 8.1, 8.8; 2300 x 2200 15.7, 9.4, 9.4, 9.1; 6000 x 5000 79, 52, 48, 47. All
 // variants, K = 4, at 3, 5 and 8 rows: 693 x 700 16.0, 6.5, 9.5; 1024^2 30.5, 11.1, 9.8.
 inline BlockGeometry block_geometry(int nx, int ny, int K, int kvar = 0) {

@@ -58,10 +58,12 @@ struct SorGeometry {
 // sweeps of 4 planes per thread. A small grid costs a launch and one load latency, whatever a thread
 // reads beside its own cells; a larger one is bound by the cache's rate and its requests (32 values per
 // position against 16), and walking planes reads a z neighbour once for the three cells that use it (us per
-// 50-iteration solve, an iteration per launch and the sweeps: 65 x 47 x 33 198 and 379, 40 x 300 x 20 222 and
-// 335, 128 x 128 x 64 (500,000 positions) 375 and 385, 160 x 120 x 60 (547,500) 402 and 414, 200 x 128 x 64
-// (781,000) 497 and 472, 300 x 300 x 90 1746 and 1232; sweeps of 1, 2, 4 and 8 planes on the last 1699, 1400,
-// 1238, 1211).
+// 50-iteration solve, best of 5 back to back, an iteration per launch and the sweeps: 65 x 47 x 33 198 and 379,
+// 40 x 300 x 20 222 and 335, 128 x 128 x 64 (500,000 positions) 375 and 385, 160 x 120 x 60 (547,500) 402 and
+// 414, 200 x 128 x 64 (781,000) 497 and 472, 300 x 300 x 90 1746 and 1232). 4 planes: fewer read more, more
+// leave fewer threads and, but for some sizes, a larger part of the last group unused (sweeps of 2, 4 and 8
+// planes: 200 x 128 x 64 498, 470 and 496, 200 x 180 x 70 592, 531 and 571, 201 x 150 x 97 636, 576 and 579,
+// 300 x 300 x 50 792, 702 and 755, 300 x 300 x 90 1285, 1169 and 1158, 400 x 300 x 120 2086, 1917 and 1970).
 constexpr int64_t kSorPairPositions = 5 << 17;
 constexpr int sor_planes(int64_t positions) { return positions < kSorPairPositions ? 1 : 4; }
 

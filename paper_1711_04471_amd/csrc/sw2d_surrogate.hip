@@ -761,7 +761,7 @@ __device__ __forceinline__ u32x4 relu_group(const f32x16& acc, int q) {
 // there. Waves 0-3 take the first layer of a tile while waves 4-7 take the second of the tile before
 // (one of each per SIMD, whose products and epilogues overlap), each with its layer's weights in
 // registers. The next input tile is fetched meanwhile. Every output is bitwise that of conv3x3_kernel.
-// 4 x 1024^2 pixels take 162 us for layers 1 and 2 (670 MB, 145 us at a large copy's rate) and 195 for
+// 4 x 1024^2 pixels take 157 us for layers 1 and 2 (670 MB, 145 us at a large copy's rate) and 191 for
 // 3 and 4 (586 MB, 127 us), a launch per layer 111 + 127 and 127 + 88. The barriers and the first
 // layer's uneven blocks (10 for 4 waves) hold it: matrix cores are busy 47 % of the time, and fetching
 // two tiles ahead changes nothing. All eight waves in one layer after the other took 174 and 193.
@@ -925,8 +925,8 @@ __global__ __launch_bounds__(kBwThreads) void forward_pair_kernel(
 // The last layer has three outputs: its dY may come with 4 channels per pixel (kDch = 4, 8 B in place
 // of 64), which are laid into the LDS tile's pixels, whose other channels stay zero.
 // Bound by memory: 805 MB for 4 x 1024^2 pixels of 32 + 32 channels, 174 us at a large copy's rate,
-// take 197 us (the separate data and weight gradients 176 + 165, reading both maps twice); the last
-// layer's thin dY 169, 16 input channels 99 (before 341 and 137). A thread's loads of a tile lie at
+// take 205 us (the separate data and weight gradients 176 + 165, reading both maps twice); the last
+// layer's thin dY 180, 16 input channels 96 (before 341 and 137). A thread's loads of a tile lie at
 // fixed distances (BwMap), so that fetching and staging a tile takes a few vector instructions per
 // load: with a division and a 64-bit address for each they took as long as the products (221 us).
 // Each workgroup's partial [9][32][KIN] (and the bias partial [32]) goes to global memory.
@@ -1305,7 +1305,7 @@ __global__ __launch_bounds__(kRedW* kRedSlices) void wgrad_reduce_kernel(const f
 // out, target: FP32 planes [img][3][H][W]; mask: coarse water mask [img][H][W].
 // d_out (BF16 NHWC, kDch = 32 or 4 channels, 3.. zero) = 2 act (out - target) * inv_n;
 // partial[block] = sum act (out - target)^2.
-// Bound by memory: 4 x 1024^2 pixels take 24 us with 4 channels (138 MB). A lane takes a pixel; of
+// Bound by memory: 4 x 1024^2 pixels take 29 us with 4 channels (138 MB). A lane takes a pixel; of
 // the 64 B that 32 channels take, the wave writes 16 pixels at a time, four lanes to a pixel (1 KB
 // contiguous per store). One lane writing its own pixel's four chunks, one pixel at a time and with
 // 64-bit divisions, took 136 us (372 MB).

@@ -241,9 +241,9 @@ class Coarse:
         dx, dt = 4 * case.dx, 4 * case.dt
         self.sim = Sw2d(self.nx, self.ny, dx, dx, case.g, dt, case.eps, self.H, self.mask, self.eta, self.u,
                         self.v, device=self.dev)
-        # three steps per pass on 8-row bands: on the 1024^2 coarse grid, advanced 5 steps per
-        # call as the corrected rollout does, 7.6 us per step against 9.0 at two steps per pass
-        # and 9.1 at four (50 steps per call: 7.2, 7.3, 7.4); the state is that of single steps
+        # Where the steps are streamed (coarse grids past 2^23 cells), three per pass on 8-row bands;
+        # smaller ones go over register tiles, 4 steps per pass, whatever is set here (1024^2, 5 steps
+        # per call: 4.5 us per step, streamed 7.6). The state is that of single steps.
         if self.ny >= 8:
             self.sim.set_time_blocking(3, rows=8)
         self.rmse_work = torch.empty(self.lib.sw2d_rmse_workspace_bytes(), dtype=torch.uint8, device=self.dev)
