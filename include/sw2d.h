@@ -166,7 +166,8 @@ int sw2d_set_state(sw2d_t h, const float *d_eta, const float *d_u, const float *
  * most 2^23 cells, whose state and depth stay in the 256 MB last-level cache, always (up to 4 steps
  * per launch whatever the handle's steps per pass); on larger ones with as many steps per pass as
  * are fastest unless sw2d_set_time_blocking has chosen, and then where tiles are the faster way
- * for that many. Other passes are streamed through row pipelines as the two settings below say.
+ * for that many. Other passes are streamed through row pipelines as the two settings below say, as
+ * are all passes of a grid of 2^27 rows or more.
  * on != 0 streams every pass of the handle (0, the default, restores the tiles); sw2d_streaming
  * returns 1 if its steps are streamed, 0 if they go over tiles, -1 for a NULL handle. */
 int sw2d_set_streaming(sw2d_t h, int32_t on);
